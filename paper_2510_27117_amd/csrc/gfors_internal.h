@@ -93,7 +93,109 @@ constexpr int kLightHole = 0x7fffffff;   // signed-index slot of a heavy item in
 constexpr int kHgChunk = 512;   // entries per workgroup of the heavy shift-group primal
 constexpr int kHgWidth = 16;    // variables per shift group (32 measured slower: fewer entries in flight)
 
+// ------------------------------------------------- sums over a wavefront's lanes
+// v[l] + v[l ^ D] in every lane, on the vector ALU (row permutations and the
+// half / quarter swaps of gfx950; a shuffle through LDS takes about ten times
+// as long).  The addends are those of v + __shfl_xor(v, D), so are the bits.
+template <int CTRL, int BANKS = 0xf>
+__device__ __forceinline__ float dpp_move(float old, float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), CTRL, 0xf, BANKS, false));
+}
+template <int D>
+__device__ __forceinline__ float xor_sum(float v) {
+    if constexpr (D == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    } else if constexpr (D == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    } else if constexpr (D == 8) {
+        return v + dpp_move<0x128>(v, v);                       // row_ror:8
+    } else if constexpr (D == 4) {
+        float t = dpp_move<0x104, 0x5>(v, v);                   // row_shl:4 into banks 0, 2
+        t = dpp_move<0x114, 0xa>(t, v);                         // row_shr:4 into banks 1, 3
+        return v + t;
+    } else if constexpr (D == 2) {
+        return v + dpp_move<0x4e>(v, v);                        // quad_perm 2 3 0 1
+    } else {
+        return v + dpp_move<0xb1>(v, v);                        // quad_perm 1 0 3 2
+    }
+}
+// Sums of a, b, c, d over the wavefront (the same tree as xor_sum<32> .. <1>
+// each) for the price of one and a half: lane 0 holds a's, 16 c's, 32 b's, 48 d's.
+__device__ __forceinline__ float wave_sum4(float a, float b, float c, float d) {
+    const auto ab = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    const auto cd = __builtin_amdgcn_permlane32_swap(__float_as_uint(c), __float_as_uint(d), false, false);
+    const float p = __uint_as_float(ab[0]) + __uint_as_float(ab[1]), q = __uint_as_float(cd[0]) + __uint_as_float(cd[1]);
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(p), __float_as_uint(q), false, false);
+    float v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    v = xor_sum<8>(v);
+    v = v + dpp_move<0x124>(v, v);                              // row_ror:4 (the row repeats every 8 lanes)
+    v = xor_sum<2>(v);
+    return xor_sum<1>(v);
+}
+// Which of wave_sum4's operands (0..3) a lane's quarter holds.
+__device__ __forceinline__ int wave_sum4_of(int lane) {
+    const int q = lane >> 4;
+    return ((q & 1) << 1) | (q >> 1);
+}
+
+// Eight int16 values of a 16-byte load as floats.
+__device__ __forceinline__ void unpack8(const int4 q, float *a) {
+    const uint32_t w[4] = {static_cast<uint32_t>(q.x), static_cast<uint32_t>(q.y), static_cast<uint32_t>(q.z),
+                           static_cast<uint32_t>(q.w)};
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        a[2 * h] = static_cast<float>(static_cast<int16_t>(w[h] & 0xffffu));
+        a[2 * h + 1] = static_cast<float>(static_cast<int16_t>(w[h] >> 16));
+    }
+}
+
 // ------------------------------------------------------------------ PDHG
+// The updates that end a row's / a variable's sum (Algorithm 2, Q = 0).
+__device__ __forceinline__ float dual_update(float s, float om, float rt, float tau2, float y_in, bool ineq) {
+    const float t = rt - om * s;
+    float y = y_in + tau2 * t;
+    if (ineq) y = fmaxf(y, 0.f);
+    return y;
+}
+__device__ __forceinline__ float primal_update(float s, float ct, float rh, float tau1, float xi) {
+    float g = ct + rh;
+    g -= s;
+    g -= 2.f * rh * xi;
+    return fminf(fmaxf(xi - tau1 * g, 0.f), 1.f);
+}
+
+// Runs of PDHG steps with each instance in one workgroup (k_steps_*).
+constexpr int kResidentThreads = 1024;   // largest workgroup
+struct ResidentArgs {
+    int m1 = 0, m = 0;
+    const int64_t *inst_var0 = nullptr, *inst_nvar = nullptr;
+    const int *inst_rows = nullptr;   // [T+1][2] first inequality / equality row; null: one instance
+    const int *rp = nullptr, *ci = nullptr, *val = nullptr, *rpT = nullptr, *ciT = nullptr, *valT = nullptr;
+    const float *omega = nullptr, *rt = nullptr, *ct = nullptr, *tau1 = nullptr, *tau2 = nullptr;
+    const double *rho = nullptr;
+    // dense rows in int16 (k_steps_dense16): the padded copy of the dense-block kernels
+    const int *blk_row0 = nullptr, *blk_nrow = nullptr, *blk_rows = nullptr;
+    const int64_t *pbase = nullptr;
+    const int16_t *pval = nullptr;
+    // state before; after (x_k, x_{k-1}, y_k, y_{k-1}, xbar, wy); xbar before the last step if wanted
+    const float *x_in = nullptr, *y_in = nullptr, *xbar_in = nullptr;
+    float *x_out = nullptr, *x_prev = nullptr, *y_out = nullptr, *y_prev = nullptr, *xbar = nullptr, *wy = nullptr;
+    float *xbar_save = nullptr;
+    DevCounters *ctr = nullptr;
+};
+// What the launch needs to know of the problem: bytes of a stored coefficient
+// (0 when all are 1, 2 or 4), dense rows, the largest instance and its longest
+// row / variable, and the LDS that the form with the matrix in LDS takes.
+struct ResidentShape {
+    int vb = 0, nv = 0, nr = 0, len_r = 0, len_c = 0;
+    bool dense = false, dense16 = false;
+    size_t lds = 0;
+};
+void launch_steps_resident(hipStream_t s, const ResidentArgs &A, int T, const ResidentShape &sh, int nsteps, int lpr_d,
+                           int lpr_p);
+
 // val16: the coefficients as int16 when every |a| <= 32767 (else null)
 void launch_dual(hipStream_t s, int lpr, bool unit, bool batched, int m, int m1,
                  const int *rp, const int *ci, const int *val, const int16_t *val16, const float *omega,
