@@ -122,7 +122,9 @@ static size_t carve(gfors_problem *P, Carver &cv, int64_t n, int64_t m1, int64_t
     P->primal_order = cv.take<int>(n);
     P->cover_ids = cv.take<int>(b.et);
     P->general_ids = cv.take<int>(b.et);
-    P->a3_part = cv.take<int>(2 * kA3MaxN);
+    // one instance: the 3D-assignment sampler's scratch; several: their row ranges
+    P->a3_part = T == 1 ? cv.take<int>(2 * kA3MaxN) : nullptr;
+    P->inst_rows = T > 1 ? cv.take<int>(2 * (static_cast<int64_t>(T) + 1)) : nullptr;
     P->rep_rp = cv.take<int>(prm->repair_row0 >= 0 ? m1 + 1 : 1);
     P->rep_var = cv.take<int>(prm->repair_row0 >= 0 ? nnzK : 1);
     P->mf_cap = prm->eval_mfma && m > 0 ? mf_digit_cap(nnzK, m) : 0;
@@ -275,6 +277,9 @@ void gfors_destroy_problem(gfors_problem *P) {
 static int device_norms(gfors_problem *P);
 static int autotune(gfors_problem *P, bool with_eval);
 static void launch_eval_general_rows(gfors_problem *P, int K);
+static int setup_resident(gfors_problem *P, const std::vector<int64_t> &off, const std::vector<int> &rp,
+                          const std::vector<int> &rpT);
+static void resident_cfg(gfors_problem *P);
 static int setup_repair(gfors_problem *P, const gfors_csr *A, const int64_t *b, const gfors_csr *B,
                         const gfors_csr *Q, const int64_t *c);
 
@@ -1247,11 +1252,119 @@ int gfors_create_problem(const gfors_csr *A, const int64_t *b, const gfors_csr *
         P->cfg.slices_dual = kXcdSlices;
         P->cfg.lpr_dual = pick(static_cast<double>(P->nnzK) / m / kXcdSlices);
     }
+    if ((rc = setup_resident(P, off, rp, rpT))) return rc;
     if (prm->repair_row0 >= 0 && (rc = setup_repair(P, A, b, B, Q, c))) return rc;
     if ((rc = sync(P))) return rc;
     if (prm->autotune && (rc = autotune(P, true))) return rc;
     *out = guard.release();
     return GFORS_OK;
+}
+
+// Whether every instance fits one workgroup (coefficients in its LDS, by rows
+// and by variables, dense rows once), and then its steps run there: no launch
+// per step.  Wherever it fits it is taken: an iteration costs about a
+// microsecond of LDS latency per instance against two dispatches.
+static int setup_resident(gfors_problem *P, const std::vector<int64_t> &off, const std::vector<int> &rp,
+                          const std::vector<int> &rpT) {
+    P->res_ok = P->res_on = false;
+    if (P->hasQ || P->m == 0) return GFORS_OK;
+    const int T = P->T;
+    ResidentShape sh;
+    sh.vb = P->unitK ? 0 : (P->use16 ? 2 : 4);
+    sh.dense = P->dense_block;
+    sh.dense16 = P->dense_block && P->blk.pval != nullptr;
+    int64_t mv = 0, mr = 0;
+    for (int t = 0; t < T; ++t) {
+        const int64_t nv = P->inst_nvar[t], a0 = off[3 * t + 1], a1 = off[3 * (t + 1) + 1];
+        const int64_t q0 = P->m1 + off[3 * t + 2], q1 = P->m1 + off[3 * (t + 1) + 2];
+        const int64_t nr = (a1 - a0) + (q1 - q0);
+        const int64_t nz = (static_cast<int64_t>(rp[a1]) - rp[a0]) + (static_cast<int64_t>(rp[q1]) - rp[q0]);
+        if (nv > 65535 || nr > 65535) return GFORS_OK;   // 16-bit local indices
+        const size_t vec = 4 * static_cast<size_t>(3 * nv + 4 * nr);
+        size_t need;
+        if (sh.dense16) need = static_cast<size_t>(nr) * ((nv + 7) / 8 * 16);
+        else if (sh.dense) need = vec + static_cast<size_t>(nv * nr * sh.vb);
+        else need = vec + 4 * static_cast<size_t>(nr + nv + 2) + static_cast<size_t>(2 * nz) * (2 + sh.vb);
+        sh.lds = std::max(sh.lds, (need + 15) & ~static_cast<size_t>(15));
+        mv = std::max(mv, nv);
+        mr = std::max(mr, nr);
+        if (sh.dense16 && nv > kBlockCols * (kResidentThreads / 256)) return GFORS_OK;
+    }
+    int dev = 0, lds_max = 0;
+    HIP_TRY(hipGetDevice(&dev));
+    HIP_TRY(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
+    // the dense form also holds up to 8.5 KiB of row sums
+    if (sh.lds + (sh.dense16 ? 9216 : 0) > static_cast<size_t>(lds_max)) return GFORS_OK;
+    sh.nv = static_cast<int>(mv);
+    sh.nr = static_cast<int>(mr);
+    for (int64_t j = 0; j < P->m; ++j) sh.len_r = std::max(sh.len_r, rp[j + 1] - rp[j]);
+    for (int64_t i = 0; i < P->n; ++i) sh.len_c = std::max(sh.len_c, rpT[i + 1] - rpT[i]);
+    if (P->inst_rows) {
+        std::vector<int> ir(2 * (static_cast<size_t>(T) + 1));
+        for (int t = 0; t <= T; ++t) {
+            ir[2 * t] = static_cast<int>(off[3 * t + 1]);
+            ir[2 * t + 1] = static_cast<int>(off[3 * t + 2]);
+        }
+        int rc = upload(P->stream, P->inst_rows, ir.data(), static_cast<int64_t>(ir.size()));
+        if (rc || (rc = sync(P))) return rc;
+    }
+    P->rsh = sh;
+    P->res_ok = true;
+    resident_cfg(P);
+    return GFORS_OK;
+}
+
+// The launch-per-step shapes whose sums the resident path reproduces.
+static void resident_cfg(gfors_problem *P) {
+    P->cfg.slices_dual = P->cfg.slices_primal = 1;
+    P->cfg.sell_dual = P->cfg.sell_primal = 0;
+    P->cfg.bits_dual = P->rsh.dense16 ? 4 : 0;
+    P->cfg.bits_primal = P->rsh.dense16 ? 5 : 0;
+    P->cfg.lpr_dual = std::min(P->cfg.lpr_dual, 64);
+    P->cfg.lpr_primal = std::min(P->cfg.lpr_primal, 64);
+    P->res_on = true;
+}
+
+// nsteps steps from the buffers of parity `a` on the resident path, into the
+// given state buffers; xbar_save (or null) receives xbar before the last step.
+static void launch_resident(gfors_problem *P, int lpr_d, int lpr_p, int nsteps, const float *x_in, const float *y_in,
+                            float *x_out, float *x_prev, float *y_out, float *y_prev, float *xbar, float *wy,
+                            float *xbar_save, DevCounters *ctr) {
+    ResidentArgs A;
+    A.m1 = static_cast<int>(P->m1);
+    A.m = static_cast<int>(P->m);
+    A.inst_var0 = P->d_inst_var0;
+    A.inst_nvar = P->d_inst_nvar;
+    A.inst_rows = P->inst_rows;
+    A.rp = P->rp;
+    A.ci = P->ci;
+    A.val = P->val;
+    A.rpT = P->rpT;
+    A.ciT = P->ciT;
+    A.valT = P->valT;
+    A.omega = P->omega;
+    A.rt = P->rt;
+    A.ct = P->ct;
+    A.tau1 = P->di.tau1;
+    A.tau2 = P->di.tau2;
+    A.rho = P->di.rho;
+    A.x_in = x_in;
+    A.y_in = y_in;
+    A.x_out = x_out;
+    A.x_prev = x_prev;
+    A.y_out = y_out;
+    A.y_prev = y_prev;
+    A.xbar_in = P->xbar;
+    A.xbar = xbar;
+    A.wy = wy;
+    A.xbar_save = xbar_save;
+    A.ctr = ctr;
+    A.blk_row0 = P->blk.row0;
+    A.blk_nrow = P->blk.nrow;
+    A.blk_rows = P->blk.rows;
+    A.pbase = P->blk.pbase;
+    A.pval = P->blk.pval;
+    launch_steps_resident(P->stream, A, P->T, P->rsh, nsteps, lpr_d, lpr_p);
 }
 
 // Relaxed set-partitioning rows [repair_row0, m1) (monotone relaxation,
@@ -1559,7 +1672,23 @@ static int autotune(gfors_problem *P, bool with_eval) {
     const int lprs[] = {1, 2, 4, 8, 16, 32, 64};
     P->cfg.bits_dual = P->cfg.bits_primal = 0;
     P->bx_fresh = P->by_fresh = false;
-    if (P->m > 0) {
+    if (P->res_ok) {
+        // lanes per row, then lanes per variable, of the resident steps
+        resident_cfg(P);
+        float *xo = P->xsave, *xp = reinterpret_cast<float *>(P->pv), *xb = reinterpret_cast<float *>(P->pu);
+        float *yo = reinterpret_cast<float *>(P->pw), *yp = yo + P->m, *wy = P->ybuf[1 - P->cur];
+        float best = 1e30f;
+        auto consider = [&](int ld, int lp) {
+            const float t = timeit([&] { launch_resident(P, ld, lp, 16, P->xbuf[P->cur], P->ybuf[P->cur], xo, xp, yo, yp,
+                                                         xb, wy, nullptr, P->ctr_scratch); });
+            if (t < best) { best = t; P->cfg.lpr_dual = ld; P->cfg.lpr_primal = lp; }
+        };
+        const int lp0 = P->cfg.lpr_primal;
+        for (int l : lprs)
+            if (!P->rsh.dense16 && l < 2 * P->rsh.len_r) consider(l, lp0);
+        for (int l : lprs)
+            if (!P->rsh.dense16 && l < 2 * P->rsh.len_c && l != lp0) consider(P->cfg.lpr_dual, l);
+    } else if (P->m > 0) {
         float best = 1e30f;
         auto consider = [&](int l, int sl, int se) {
             const float t = timeit([&] { launch_dual_cfg(P, l, sl, se, P->ybuf[P->cur], P->ybuf[1 - P->cur]); });
@@ -1595,7 +1724,7 @@ static int autotune(gfors_problem *P, bool with_eval) {
         }
         P->cfg.bits_dual = best_bits;
     }
-    {
+    if (!P->res_ok) {
         float best = 1e30f;
         float *xs = P->xsave, *xb = reinterpret_cast<float *>(P->pv);
         auto consider = [&](int l, int sl, int se) {
@@ -1662,6 +1791,24 @@ static int autotune(gfors_problem *P, bool with_eval) {
     return sync(P);
 }
 
+// FP64 residuals of the step from the buffers of parity a (xsave: xbar before it).
+static void enqueue_residuals(gfors_problem *P, int a) {
+    hipStream_t s = P->stream;
+    const int T = P->T, z = 1 - a;
+    launch_res_vars(s, P->vt, P->hasQ ? P->rpQ : nullptr, P->ciQ, P->valQ, P->xbuf[z], P->xbuf[a], P->di.rho,
+                    P->di.tau1d, P->di.two_sod, P->part);
+    launch_inst_sum(s, T, P->vt, P->part, 2, 0, P->res + 0, 4, true);
+    launch_inst_sum(s, T, P->vt, P->part, 2, 1, P->res + 3, 4, false);
+    if (P->m > 0) {
+        launch_res_rows(s, P->rtile, static_cast<int>(P->m1), P->rp, P->ci, P->unitK ? nullptr : P->val, P->omega64,
+                        P->rhs, P->xsave, P->xbuf[z], P->ybuf[a], P->ybuf[z], P->di.tau2d, P->part);
+        launch_inst_sum(s, T, P->rtile, P->part, 2, 0, P->res + 1, 4, true);
+        launch_inst_sum(s, T, P->rtile, P->part, 2, 1, P->res + 2, 4, true);
+    } else {
+        for (int t = 0; t < T; ++t) launch_fill64(s, P->res + 4 * t + 1, 0.0, 2);
+    }
+}
+
 static void enqueue_steps(gfors_problem *P, int nsteps, bool want_res, KTimer *tm = nullptr) {
     if (P->lu) {
         lu_enqueue_steps(P, nsteps, want_res, tm);
@@ -1670,6 +1817,16 @@ static void enqueue_steps(gfors_problem *P, int nsteps, bool want_res, KTimer *t
     hipStream_t s = P->stream;
     // a sequence never relies on bitmaps written before it
     P->bx_fresh = P->by_fresh = false;
+    // per-launch timing keeps a launch per step (the same sums in the same order)
+    if (P->res_on && !tm) {
+        const int a = P->cur, z = (P->cur + nsteps) & 1;
+        launch_resident(P, P->cfg.lpr_dual, P->cfg.lpr_primal, nsteps, P->xbuf[a], P->ybuf[a], P->xbuf[z],
+                        P->xbuf[1 - z], P->ybuf[z], P->ybuf[1 - z], P->xbar, P->wy, want_res ? P->xsave : nullptr,
+                        P->ctr);
+        if (want_res) enqueue_residuals(P, 1 - z);
+        P->cur = z;
+        return;
+    }
     for (int it = 0; it < nsteps; ++it) {
         const bool res = want_res && it == nsteps - 1;
         if (res) launch_copy_f32(s, P->xsave, P->xbar, P->n);
@@ -1683,24 +1840,7 @@ static void enqueue_steps(gfors_problem *P, int nsteps, bool want_res, KTimer *t
         launch_primal_cfg(P, P->cfg.lpr_primal, P->cfg.slices_primal, P->cfg.sell_primal,
                           P->xbuf[a], P->xbuf[bnext], P->xbar, P->ctr);
         TE(1);
-        if (res) {
-            const int T = P->T;
-            launch_res_vars(s, P->vt, P->hasQ ? P->rpQ : nullptr, P->ciQ, P->valQ, P->xbuf[bnext],
-                            P->xbuf[a], P->di.rho, P->di.tau1d, P->di.two_sod, P->part);
-            launch_inst_sum(s, T, P->vt, P->part, 2, 0, P->res + 0, 4, true);
-            launch_inst_sum(s, T, P->vt, P->part, 2, 1, P->res + 3, 4, false);
-            if (P->m > 0) {
-                launch_res_rows(s, P->rtile, static_cast<int>(P->m1), P->rp, P->ci,
-                                P->unitK ? nullptr : P->val, P->omega64, P->rhs, P->xsave,
-                                P->xbuf[bnext], P->ybuf[a], P->ybuf[bnext], P->di.tau2d, P->part);
-                launch_inst_sum(s, T, P->rtile, P->part, 2, 0, P->res + 1, 4, true);
-                launch_inst_sum(s, T, P->rtile, P->part, 2, 1, P->res + 2, 4, true);
-            } else {
-                for (int t = 0; t < T; ++t) {
-                    launch_fill64(s, P->res + 4 * t + 1, 0.0, 2);
-                }
-            }
-        }
+        if (res) enqueue_residuals(P, a);
         P->cur = bnext;
     }
 }
@@ -2145,6 +2285,7 @@ int gfors_set_launch_cfg(gfors_problem *P, const int32_t *cfg) {
     P->cfg.sell_primal = cfg[5] ? 1 : 0;
     P->cfg.bits_dual = cfg[6];
     P->cfg.bits_primal = cfg[7];
+    P->res_on = false;   // the caller asks for these launches
     P->graphs_clear();
     return GFORS_OK;
 }
