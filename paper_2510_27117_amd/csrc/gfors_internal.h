@@ -307,6 +307,8 @@ bool launch_primal_lds(hipStream_t s, int n, int m, int deg, int SL, const int *
 void launch_copy_f32(hipStream_t s, float *dst, const float *src, int64_t n);
 void launch_set_xbar(hipStream_t s, int64_t n, const float *x, const float *xp, float *xbar);
 void launch_fill_f32(hipStream_t s, float *dst, float v, int64_t n);
+// dst[i] = v for a pseudorandom `percent` of the entries, else 0 (stand-in iterates)
+void launch_fill_share(hipStream_t s, float *dst, float v, int percent, int64_t n);
 
 // ------------------------------------------------- FP64 (Preprocess, residuals)
 void launch_spmv64(hipStream_t s, int nrows, const int *rp, const int *ci, const int *val,

@@ -1654,6 +1654,11 @@ __global__ void k_fill_f32(float *__restrict__ d, float v, int64_t n) {
          i += (int64_t)gridDim.x * blockDim.x)
         d[i] = v;
 }
+__global__ void k_fill_share(float *__restrict__ d, float v, int percent, int64_t n) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x)
+        d[i] = ((static_cast<uint32_t>(i) * 2654435761u) >> 16) % 100u < static_cast<uint32_t>(percent) ? v : 0.f;
+}
 __global__ void k_set_xbar(int64_t n, const float *__restrict__ x, const float *__restrict__ xp,
                            float *__restrict__ xbar) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
@@ -1670,6 +1675,9 @@ void launch_copy_f32(hipStream_t s, float *dst, const float *src, int64_t n) {
 }
 void launch_fill_f32(hipStream_t s, float *dst, float v, int64_t n) {
     if (n > 0) k_fill_f32<<<grid_for(n), 256, 0, s>>>(dst, v, n);
+}
+void launch_fill_share(hipStream_t s, float *dst, float v, int percent, int64_t n) {
+    if (n > 0) k_fill_share<<<grid_for(n), 256, 0, s>>>(dst, v, percent, n);
 }
 void launch_set_xbar(hipStream_t s, int64_t n, const float *x, const float *xp, float *xbar) {
     if (n > 0) k_set_xbar<<<grid_for(n), 256, 0, s>>>(n, x, xp, xbar);
