@@ -47,6 +47,7 @@ constexpr int kQuadRows = 64;          // variables per Q tile (max): many tiles
 constexpr int kVarTile = 4096;        // variables per FP64 reduction tile
 constexpr int kRowNnz = 16384;        // nnz budget of a residual row tile
 constexpr int kRowRows = 2048;
+constexpr int kStepChunk = 32;         // steps per captured graph of gfors_pdhg_steps (even)
 constexpr int kMfmaRows = 32;          // rows per dense digit block (one 32 x 32 matrix-core tile)
 constexpr int kMfmaMaxSpan = 1 << 23;  // column span of a block: keeps int32 plane sums exact
 
