@@ -1937,10 +1937,12 @@ static void enqueue_eval(gfors_problem *P, int K, int threshold, KTimer *tm, int
                        P->hasQ ? 1 : 0, P->red_v, P->red_z, P->viol, P->z);
     TE(6);
     TB(7);
-    launch_argmin_update(s, P->T, K, W, P->viol, P->z, P->di, P->ctr, threshold ? 0 : (trigger ? 1 : 2));
+    const int advance = threshold ? 0 : (trigger ? 1 : 2);
+    launch_argmin_update(s, P->T, K, W, P->red_S, P->et, P->vpart, P->st, P->zpart, P->qt, P->zqpart,
+                         P->hasQ ? 1 : 0, P->viol, P->z, P->di, P->ctr, advance);
     TE(7);
     TB(8);
-    launch_extract_best(s, P->n, P->T, P->var_inst, P->X, P->di, P->xbest);
+    launch_extract_best(s, P->n, P->T, P->var_inst, P->X, P->di, P->xbest, P->ctr, advance);
     TE(8);
     P->lastK = K;
 }

@@ -491,10 +491,12 @@ void lu_enqueue_eval(gfors_problem *P, int K, int threshold, KTimer *tm, int tri
                        P->red_z, P->viol, P->z);
     TE(6);
     TB(7);
-    launch_argmin_update(s, 1, K, W, P->viol, P->z, P->di, P->ctr, threshold ? 0 : (trigger ? 1 : 2));
+    const int advance = threshold ? 0 : (trigger ? 1 : 2);
+    launch_argmin_update(s, 1, K, W, P->red_S, P->et, P->vpart, P->st, P->zpart, P->qt, P->zqpart, 1, P->viol, P->z,
+                         P->di, P->ctr, advance);
     TE(7);
     TB(8);
-    launch_extract_best(s, P->n, 1, P->var_inst, P->X, P->di, P->xbest);
+    launch_extract_best(s, P->n, 1, P->var_inst, P->X, P->di, P->xbest, P->ctr, advance);
     TE(8);
     P->lastK = K;
 }

@@ -215,82 +215,135 @@ __device__ __forceinline__ void wave_sync() {
 // (monotone for p > 0), an index-ordered compaction and a bitonic sort in
 // LDS; then the greedy conflict-free partial assignment (largest first).
 // part[i] / part[n + i] = j / k of i, or -1.
+//
+// Bound by the latency of its passes over p (n = 33: 35,937 entries by 1,024
+// lanes), so eight loads per lane are in flight, equal digits of a wavefront
+// are counted together (p in (0.5, 1) shares its top digit) and the digit
+// search and index arithmetic are spread over lanes.
 __global__ void __launch_bounds__(1024)
 k_a3_partial(const float *__restrict__ p, int64_t N, int n, int m, int *__restrict__ part) {
+    constexpr int U = 8;
     __shared__ uint32_t hist[256];
     __shared__ uint64_t sel[kA3MaxTop];
     __shared__ int J0[kA3MaxN], K0[kA3MaxN];
     __shared__ uint8_t uj[kA3MaxN], uk[kA3MaxN];
-    __shared__ uint32_t s_prefix, s_rank, s_npos, s_ngt, s_eqbase;
-    __shared__ uint32_t s_wcnt[16];
+    __shared__ uint32_t s_prefix, s_rank, s_meff, s_ngt, s_eqbase;
+    __shared__ uint32_t s_wcnt[U * 16];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int nw = blockDim.x >> 6;
-    if (tid == 0) { s_npos = 0; s_ngt = 0; s_eqbase = 0; s_prefix = 0; }
-    for (int i = tid; i < n; i += blockDim.x) { J0[i] = -1; K0[i] = -1; uj[i] = 0; uk[i] = 0; }
-    __syncthreads();
-    uint32_t cnt = 0;
-    for (int64_t v = tid; v < N; v += blockDim.x) cnt += p[v] > 0.f ? 1u : 0u;
-    atomicAdd(&s_npos, cnt);
-    __syncthreads();
-    const uint32_t meff = min(static_cast<uint32_t>(m), s_npos);
-    if (meff > 0) {
-        if (tid == 0) s_rank = meff;
-        for (int d = 3; d >= 0; --d) {
-            for (int b = tid; b < 256; b += blockDim.x) hist[b] = 0;
-            __syncthreads();
-            const uint32_t pre = s_prefix;
-            const int sh = 8 * d;
-            const uint32_t himask = d == 3 ? 0u : (0xFFFFFFFFu << (sh + 8));
-            for (int64_t v = tid; v < N; v += blockDim.x) {
-                const uint32_t key = a3_key(p[v]);
-                if (key != 0u && (key & himask) == (pre & himask)) atomicAdd(&hist[(key >> sh) & 255u], 1u);
-            }
-            __syncthreads();
-            if (tid == 0) {
-                uint32_t cum = 0;
-                const uint32_t r = s_rank;
-                int b = 255;
-                for (; b > 0; --b) {
-                    if (cum + hist[b] >= r) break;
-                    cum += hist[b];
+    const int bd = blockDim.x;                             // 1024
+    if (tid == 0) { s_ngt = 0; s_eqbase = 0; s_prefix = 0; }
+    for (int i = tid; i < n; i += bd) { J0[i] = -1; K0[i] = -1; uj[i] = 0; uk[i] = 0; }
+    auto load = [&](int64_t base, uint32_t *key) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t v = base + static_cast<int64_t>(u) * bd + tid;
+            key[u] = v < N ? a3_key(p[v]) : 0u;
+        }
+    };
+    for (int d = 3; d >= 0; --d) {
+        if (tid < 256) hist[tid] = 0;
+        __syncthreads();
+        const uint32_t pre = s_prefix;
+        const int sh = 8 * d;
+        const uint32_t himask = d == 3 ? 0u : (0xFFFFFFFFu << (sh + 8));
+        for (int64_t base = 0; base < N; base += static_cast<int64_t>(U) * bd) {
+            uint32_t key[U];
+            load(base, key);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t dg = (key[u] >> sh) & 255u;
+                bool on = key[u] != 0u && (key[u] & himask) == (pre & himask);
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {              // the first lane's digit, then the next one's
+                    const uint64_t left = __ballot(on);
+                    if (!left || (r && d < 3)) break;      // uniform
+                    const int lead = __builtin_ctzll(left);
+                    const uint32_t dl = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(dg), lead));
+                    const bool same = on && dg == dl;
+                    const uint64_t grp = __ballot(same);
+                    if (lane == lead) atomicAdd(&hist[dl], static_cast<uint32_t>(__popcll(grp)));
+                    on = on && !same;
                 }
-                s_prefix = pre | (static_cast<uint32_t>(b) << sh);
+                if (on) atomicAdd(&hist[dg], 1u);
+            }
+        }
+        __syncthreads();
+        if (wv == 0) {
+            // lane q: digits 255 - 4 q .. 252 - 4 q, counted from the largest down
+            uint32_t h[4], tot = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                h[k] = hist[255 - 4 * lane - k];
+                tot += h[k];
+            }
+            uint32_t inc = tot;
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t up = __shfl_up(inc, o, 64);
+                if (lane >= o) inc += up;
+            }
+            const uint32_t all = __shfl(inc, 63, 64);      // entries under the prefix; d = 3: #{p > 0}
+            const uint32_t r = d == 3 ? min(static_cast<uint32_t>(m), all) : s_rank;
+            const uint32_t before = inc - tot;
+            if (d == 3 && lane == 0) s_meff = r;
+            if (r > 0 && before < r && inc >= r) {
+                uint32_t cum = before;
+                int k = 0;
+                while (cum + h[k] < r) cum += h[k++];
+                s_prefix = pre | (static_cast<uint32_t>(255 - 4 * lane - k) << sh);
                 s_rank = r - cum;
             }
-            __syncthreads();
         }
+        __syncthreads();
+        if (s_meff == 0) break;                            // uniform: no positive entry, or none wanted
+    }
+    const uint32_t meff = s_meff;
+    if (meff > 0) {
         const uint32_t T = s_prefix, need_eq = s_rank, ngt_total = meff - need_eq;
-        for (int64_t base = 0; base < N; base += blockDim.x) {
-            const int64_t v = base + tid;
-            const uint32_t key = v < N ? a3_key(p[v]) : 0u;
-            const bool gt = key > T;
-            const bool eq = key != 0u && key == T;
-            if (gt) {
-                const uint32_t slot = atomicAdd(&s_ngt, 1u);
-                if (slot < ngt_total) sel[slot] = (static_cast<uint64_t>(~key) << 32) | static_cast<uint64_t>(v);
+        for (int64_t base = 0; base < N; base += static_cast<int64_t>(U) * bd) {
+            uint32_t key[U];
+            load(base, key);
+            uint64_t bal[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t v = base + static_cast<int64_t>(u) * bd + tid;
+                if (key[u] > T) {
+                    const uint32_t slot = atomicAdd(&s_ngt, 1u);
+                    if (slot < ngt_total) sel[slot] = (static_cast<uint64_t>(~key[u]) << 32) | static_cast<uint64_t>(v);
+                }
+                bal[u] = __ballot(key[u] != 0u && key[u] == T);
+                if (lane == 0) s_wcnt[16 * u + wv] = static_cast<uint32_t>(__popcll(bal[u]));
             }
-            const uint64_t bal = __ballot(eq);
-            if (lane == 0) s_wcnt[wv] = static_cast<uint32_t>(__popcll(bal));
             __syncthreads();
-            uint32_t off = s_eqbase;
-            for (int w = 0; w < wv; ++w) off += s_wcnt[w];
-            const uint32_t pos = off + static_cast<uint32_t>(__popcll(bal & ((1ull << lane) - 1ull)));
-            if (eq && pos < need_eq) sel[ngt_total + pos] = (static_cast<uint64_t>(~key) << 32) | static_cast<uint64_t>(v);
+            // exclusive offsets of the U x 16 wavefront counts, in index order
+            if (wv == 0) {
+                const uint32_t a = s_wcnt[2 * lane], b = s_wcnt[2 * lane + 1];
+                uint32_t inc = a + b;
+                for (int o = 1; o < 64; o <<= 1) {
+                    const uint32_t up = __shfl_up(inc, o, 64);
+                    if (lane >= o) inc += up;
+                }
+                const uint32_t at = s_eqbase + inc - a - b;
+                s_wcnt[2 * lane] = at;
+                s_wcnt[2 * lane + 1] = at + a;
+                if (lane == 63) s_eqbase = at + a + b;
+            }
             __syncthreads();
-            if (tid == 0) {
-                uint32_t tot = 0;
-                for (int w = 0; w < nw; ++w) tot += s_wcnt[w];
-                s_eqbase += tot;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t v = base + static_cast<int64_t>(u) * bd + tid;
+                const uint32_t pos = s_wcnt[16 * u + wv] + static_cast<uint32_t>(__popcll(bal[u] & ((1ull << lane) - 1ull)));
+                if (((bal[u] >> lane) & 1ull) && pos < need_eq)
+                    sel[ngt_total + pos] = (static_cast<uint64_t>(~key[u]) << 32) | static_cast<uint64_t>(v);
             }
             __syncthreads();
         }
         int M2 = 1;
         while (M2 < static_cast<int>(meff)) M2 <<= 1;
-        for (int i = static_cast<int>(meff) + tid; i < M2; i += blockDim.x) sel[i] = ~0ull;
+        for (int i = static_cast<int>(meff) + tid; i < M2; i += bd) sel[i] = ~0ull;
         __syncthreads();
         for (int k = 2; k <= M2; k <<= 1)
             for (int j = k >> 1; j > 0; j >>= 1) {
-                for (int i = tid; i < M2; i += blockDim.x) {
+                for (int i = tid; i < M2; i += bd) {
                     const int ixj = i ^ j;
                     if (ixj > i) {
                         const uint64_t a = sel[i], b = sel[ixj];
@@ -303,12 +356,19 @@ k_a3_partial(const float *__restrict__ p, int64_t N, int n, int m, int *__restri
                 }
                 __syncthreads();
             }
+        for (int t = tid; t < static_cast<int>(meff); t += bd) {   // index -> (i, j, k), 10 bits each
+            const uint32_t v = static_cast<uint32_t>(sel[t]);
+            const uint32_t ij = v / n, i = ij / n;
+            sel[t] = (i << 20) | ((ij - i * n) << 10) | (v - ij * n);
+        }
+        __syncthreads();
         if (tid == 0) {
-            const int64_t nn = static_cast<int64_t>(n) * n;
             for (uint32_t t = 0; t < meff; ++t) {
-                const int64_t v = static_cast<int64_t>(sel[t] & 0xFFFFFFFFull);
-                const int i = static_cast<int>(v / nn), j = static_cast<int>((v / n) % n), k = static_cast<int>(v % n);
-                if (J0[i] < 0 && !uj[j] && !uk[k]) {
+                const uint32_t v = static_cast<uint32_t>(sel[t]);
+                const int i = static_cast<int>(v >> 20), j = static_cast<int>((v >> 10) & 1023u), k = static_cast<int>(v & 1023u);
+                const int ji = J0[i];
+                const uint8_t fj = uj[j], fk = uk[k];
+                if (ji < 0 && !fj && !fk) {
                     J0[i] = j;
                     K0[i] = k;
                     uj[j] = 1;
@@ -318,7 +378,7 @@ k_a3_partial(const float *__restrict__ p, int64_t N, int n, int m, int *__restri
         }
         __syncthreads();
     }
-    for (int i = tid; i < n; i += blockDim.x) {
+    for (int i = tid; i < n; i += bd) {
         part[i] = J0[i];
         part[n + i] = K0[i];
     }
@@ -605,16 +665,33 @@ void launch_read_peak(hipStream_t s, int blocks, const void *p, int64_t n16, uin
 //                violated = the row's truth table over (x_p, x_q)
 // where one / two are the running "at least one / at least two set" masks.
 // A group of Wp (power of two >= W) lanes owns a row, lane w of the group word
-// w.  Each lane keeps per-candidate violation counts bit-sliced in 8 planes
-// (ripple-carry adds of 64-bit masks) and flushes them to LDS counters every
-// 255 rows.
+// w; on tiles of long rows S such groups share a row, each with every S-th
+// batch of entries.  Each lane keeps per-candidate violation counts bit-sliced
+// in 8 planes (ripple-carry adds of 64-bit masks) and flushes them to LDS
+// counters every 255 rows.
+//
+// What bounds it: gathers of 8 W bytes per entry, and on few or long rows the
+// chain index -> kind -> word.  One lane per (row, word) took 213 us for the 99
+// rows of 1,089 entries of a 33 x 33 x 33 assignment (K = 512).
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void flush_planes(uint64_t (&c)[8], int *cnt, int w) {
-    for (int b = 0; b < 64; ++b) {
-        int v = 0;
+// The counts of a lane's 64 candidates, from its `np` planes, into the
+// workgroup's counters (two 16-bit counts per word: a tile has at most 8,192
+// rows).  A nibble of a plane becomes four bytes with one multiply, so four
+// candidates' counts take 4 instructions per plane, and the words of a
+// candidate pair lie side by side over w (distinct banks).
+__device__ __forceinline__ void flush_planes(uint64_t (&c)[8], int np, uint32_t *cnt, int lgWp, int w) {
 #pragma unroll
-        for (int pl = 0; pl < 8; ++pl) v |= static_cast<int>((c[pl] >> b) & 1ull) << pl;
-        if (v) atomicAdd(&cnt[64 * w + b], v);
+    for (int k = 0; k < 16; ++k) {
+        uint32_t x = 0;
+#pragma unroll
+        for (int pl = 0; pl < 8; ++pl) {
+            if (pl >= np) break;   // uniform
+            const uint32_t half = static_cast<uint32_t>(k < 8 ? c[pl] : c[pl] >> 32);
+            x |= (__umul24((half >> (4 * (k & 7))) & 15u, 0x204081u) & 0x01010101u) << pl;
+        }
+        const uint32_t even = x & 0x00ff00ffu, odd = (x >> 8) & 0x00ff00ffu;
+        if (even) atomicAdd(&cnt[((2 * k) << lgWp) + w], even);
+        if (odd) atomicAdd(&cnt[((2 * k + 1) << lgWp) + w], odd);
     }
 #pragma unroll
     for (int pl = 0; pl < 8; ++pl) c[pl] = 0;
@@ -626,125 +703,145 @@ __device__ __forceinline__ void flush_planes(uint64_t (&c)[8], int *cnt, int w) 
 // candidate block.
 constexpr int kCoverBatch = 8;    // entries per load stage in the bitwise row evaluation (16 is slower)
 
-__device__ __forceinline__ uint64_t cand_word(const uint64_t *__restrict__ X,
-                                              const uint8_t *__restrict__ xkind, int c, int W,
-                                              int sub) {
-    const uint8_t k = xkind[c];
-    if (k == 1) return 0ull;
-    if (k == 2) return ~0ull;
-    return X[static_cast<int64_t>(c) * W + sub];
-}
-
+// Six wavefronts per SIMD for the long-row form (80 registers): the tiles of the
+// 2M x 200k set cover are then resident in one go (0.31 ms at four, 0.18 at six).
 template <int RU>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(RU == 1 ? 6 : 4)))
 k_eval_cover(const int *__restrict__ tile_ids, const int *__restrict__ tb0,
              const int *__restrict__ tb1, const int *__restrict__ rows,
              const uint8_t *__restrict__ rkind, const int *__restrict__ rp,
              const int *__restrict__ ci, const uint64_t *__restrict__ X,
              const uint8_t *__restrict__ xkind, int W, int lgWp, int *__restrict__ vpart, int K) {
-    __shared__ int cnt[4096];
+    __shared__ uint32_t cnt[32 * 64];
     const int tile = tile_ids[blockIdx.x];
     const int r0 = tb0[tile], r1 = tb1[tile];
-    for (int l = threadIdx.x; l < K; l += blockDim.x) cnt[l] = 0;
+    for (int l = threadIdx.x; l < (32 << lgWp); l += blockDim.x) cnt[l] = 0;
     __syncthreads();
+    // lanes per (row, word): as many as leave each at least four batches of
+    // entries (estimated from the tile's span), within a wavefront
+    int lgS = 0;
+    if (r1 > r0) {
+        const int avg = (rp[rows[r1 - 1] + 1] - rp[rows[r0]]) / (r1 - r0);
+        while (lgWp + lgS < 6 && avg >= (8 * kCoverBatch) << lgS) ++lgS;
+    }
     const int sub = threadIdx.x & ((1 << lgWp) - 1);
-    const int grp = threadIdx.x >> lgWp;
-    const int ngrp = blockDim.x >> lgWp;
+    const int part = (threadIdx.x >> lgWp) & ((1 << lgS) - 1);
+    const int grp = threadIdx.x >> (lgWp + lgS);
+    const int ngrp = blockDim.x >> (lgWp + lgS);
     uint64_t c[8];
 #pragma unroll
     for (int pl = 0; pl < 8; ++pl) c[pl] = 0;
     int since = 0;
+    auto count = [&](uint64_t viol) {
+        uint64_t carry = part == 0 ? viol : 0ull;   // one of the row's parts counts it
+#pragma unroll
+        for (int pl = 0; pl < 8; ++pl) {
+            const uint64_t t = c[pl] & carry;
+            c[pl] ^= carry;
+            carry = t;
+        }
+        ++since;
+    };
+    auto pair_viol = [](int k, uint64_t P, uint64_t Q) {
+        return ((k & 1) ? (~P & ~Q) : 0ull) | ((k & 2) ? (~P & Q) : 0ull) | ((k & 4) ? (P & ~Q) : 0ull) |
+               ((k & 8) ? (P & Q) : 0ull);
+    };
+    // "at least one / at least two set" do not depend on the order of the
+    // entries: kCoverBatch at a time, their column indices, kind bytes and
+    // words each loaded together
+    auto row_viol = [&](int j, int kd) {
+        const int e1 = rp[j + 1], step = kCoverBatch << lgS;
+        uint64_t one = 0, two = 0;
+        auto batch = [&](int e, auto whole) {
+            int cc[kCoverBatch];
+            uint8_t kk[kCoverBatch];
+            uint64_t xx[kCoverBatch];
+#pragma unroll
+            for (int v = 0; v < kCoverBatch; ++v) cc[v] = ci[whole ? e + v : min(e + v, e1 - 1)];
+#pragma unroll
+            for (int v = 0; v < kCoverBatch; ++v) kk[v] = xkind[cc[v]];
+#pragma unroll
+            for (int v = 0; v < kCoverBatch; ++v) {
+                if (!whole && e + v >= e1) kk[v] = 1;
+                xx[v] = kk[v] == 0 ? X[static_cast<int64_t>(cc[v]) * W + sub] : (kk[v] == 2 ? ~0ull : 0ull);
+            }
+#pragma unroll
+            for (int v = 0; v < kCoverBatch; ++v) {
+                two |= one & xx[v];
+                one |= xx[v];
+            }
+        };
+        int e = rp[j] + kCoverBatch * part;
+        for (; e + kCoverBatch <= e1; e += step) batch(e, std::true_type());
+        if (e < e1) batch(e, std::false_type());
+        for (int d = 1 << lgWp; d < 1 << (lgWp + lgS); d <<= 1) {   // the parts of the row
+            const uint64_t o1 = __shfl_xor(static_cast<unsigned long long>(one), d, 64);
+            const uint64_t o2 = __shfl_xor(static_cast<unsigned long long>(two), d, 64);
+            two |= o2 | (one & o1);
+            one |= o1;
+        }
+        const int kind = kd >> 4;
+        return kind == kEvalCover ? ~one : (kind == kEvalAtMostOne ? two : (~one | two));
+    };
     // RU rows per group and pass: their row data, and the two words of pair
     // rows, are loaded together (a row's count does not depend on the order
     // in which rows are added).  Four pay on pair rows (two entries, a chain
     // of dependent loads each); on long covering rows they cost occupancy.
     for (int rb = r0 + grp; rb < r1; rb += RU * ngrp) {
-        if (sub < W) {
-            int j[RU], kd[RU], e0[RU], e1[RU];
+        if (sub >= W) continue;
+        if (since > 255 - RU) {
+            flush_planes(c, 8, cnt, lgWp, sub);
+            since = 0;
+        }
+        int j[RU], kd[RU], c0[RU], c1[RU];
+        uint64_t P[RU], Q[RU];
 #pragma unroll
-            for (int u = 0; u < RU; ++u) j[u] = rb + u * ngrp < r1 ? rows[rb + u * ngrp] : -1;
+        for (int u = 0; u < RU; ++u) j[u] = rb + u * ngrp < r1 ? rows[rb + u * ngrp] : -1;
 #pragma unroll
-            for (int u = 0; u < RU; ++u) {
-                kd[u] = j[u] >= 0 ? rkind[j[u]] : 0;
-                e0[u] = j[u] >= 0 ? rp[j[u]] : 0;
-                e1[u] = j[u] >= 0 ? rp[j[u] + 1] : 0;
-            }
-            uint64_t P[RU], Q[RU];
-            {
-                int c0[RU], c1[RU];
-                uint8_t k0[RU], k1[RU];
+        for (int u = 0; u < RU; ++u) {
+            kd[u] = j[u] >= 0 ? rkind[j[u]] : 0;
+            c0[u] = j[u] >= 0 ? rp[j[u]] : 0;
+            c1[u] = j[u] >= 0 ? rp[j[u] + 1] - 1 : 0;
+        }
 #pragma unroll
-                for (int u = 0; u < RU; ++u) {
-                    const bool pr = j[u] >= 0 && (kd[u] >> 4) == kEvalPair;
-                    c0[u] = pr ? ci[e0[u]] : -1;
-                    c1[u] = pr ? ci[e1[u] - 1] : -1;
-                }
+        for (int u = 0; u < RU; ++u) {
+            const bool pr = j[u] >= 0 && (kd[u] >> 4) == kEvalPair;
+            c0[u] = pr ? ci[c0[u]] : -1;
+            c1[u] = pr ? ci[c1[u]] : -1;
+        }
+        uint8_t k0[RU], k1[RU];
 #pragma unroll
-                for (int u = 0; u < RU; ++u) {
-                    k0[u] = c0[u] >= 0 ? xkind[c0[u]] : 1;
-                    k1[u] = c1[u] >= 0 ? xkind[c1[u]] : 1;
-                }
+        for (int u = 0; u < RU; ++u) {
+            k0[u] = c0[u] >= 0 ? xkind[c0[u]] : 1;
+            k1[u] = c1[u] >= 0 ? xkind[c1[u]] : 1;
+        }
 #pragma unroll
-                for (int u = 0; u < RU; ++u) {
-                    P[u] = k0[u] == 0 ? X[static_cast<int64_t>(c0[u]) * W + sub] : (k0[u] == 2 ? ~0ull : 0ull);
-                    Q[u] = k1[u] == 0 ? X[static_cast<int64_t>(c1[u]) * W + sub] : (k1[u] == 2 ? ~0ull : 0ull);
-                }
-            }
+        for (int u = 0; u < RU; ++u) {
+            P[u] = k0[u] == 0 ? X[static_cast<int64_t>(c0[u]) * W + sub] : (k0[u] == 2 ? ~0ull : 0ull);
+            Q[u] = k1[u] == 0 ? X[static_cast<int64_t>(c1[u]) * W + sub] : (k1[u] == 2 ? ~0ull : 0ull);
+        }
+        uint32_t others = 0;   // rows of the pass that are not pairs
 #pragma unroll
-            for (int u = 0; u < RU; ++u) {
-                if (j[u] < 0) break;
-                const int kind = kd[u] >> 4;
-                uint64_t viol;
-                if (kind == kEvalPair) {
-                    const int k = kd[u];
-                    viol = ((k & 1) ? (~P[u] & ~Q[u]) : 0ull) | ((k & 2) ? (~P[u] & Q[u]) : 0ull) |
-                           ((k & 4) ? (P[u] & ~Q[u]) : 0ull) | ((k & 8) ? (P[u] & Q[u]) : 0ull);
-                } else {
-                    // "at least one / at least two set" do not depend on the
-                    // order of the entries: kCoverBatch at a time, their column
-                    // indices, kind bytes and words each loaded together
-                    uint64_t one = 0, two = 0;
-                    int e = e0[u];
-                    const int ee1 = e1[u];
-                    for (; e + kCoverBatch <= ee1; e += kCoverBatch) {
-                        int cc[kCoverBatch];
-                        uint8_t kk[kCoverBatch];
-                        uint64_t xx[kCoverBatch];
-#pragma unroll
-                        for (int v = 0; v < kCoverBatch; ++v) cc[v] = ci[e + v];
-#pragma unroll
-                        for (int v = 0; v < kCoverBatch; ++v) kk[v] = xkind[cc[v]];
-#pragma unroll
-                        for (int v = 0; v < kCoverBatch; ++v)
-                            xx[v] = kk[v] == 0 ? X[static_cast<int64_t>(cc[v]) * W + sub] : (kk[v] == 2 ? ~0ull : 0ull);
-#pragma unroll
-                        for (int v = 0; v < kCoverBatch; ++v) {
-                            two |= one & xx[v];
-                            one |= xx[v];
-                        }
-                    }
-                    for (; e < ee1; ++e) {
-                        const uint64_t x = cand_word(X, xkind, ci[e], W, sub);
-                        two |= one & x;
-                        one |= x;
-                    }
-                    viol = kind == kEvalCover ? ~one : (kind == kEvalAtMostOne ? two : (~one | two));
-                }
-                uint64_t carry = viol;
-#pragma unroll
-                for (int pl = 0; pl < 8; ++pl) {
-                    const uint64_t t = c[pl] & carry;
-                    c[pl] ^= carry;
-                    carry = t;
-                }
-                if (++since == 255) { flush_planes(c, cnt, sub); since = 0; }
-            }
+        for (int u = 0; u < RU; ++u) {
+            if (c0[u] >= 0) count(pair_viol(kd[u], P[u], Q[u]));
+            else if (j[u] >= 0) others |= 1u << u;
+        }
+        while (others) {
+            const int u = __builtin_ctz(others);
+            others &= others - 1;
+            const int jj = rows[rb + u * ngrp];
+            count(row_viol(jj, rkind[jj]));
         }
     }
-    if (sub < W && since) flush_planes(c, cnt, sub);
+    // planes in use: those of the most rows that a group of the workgroup can hold
+    const int most = min(255, (r1 - r0 + ngrp - 1) / max(ngrp, 1));
+    if (sub < W && since && part == 0) flush_planes(c, 32 - __clz(most), cnt, lgWp, sub);
     __syncthreads();
-    for (int l = threadIdx.x; l < K; l += blockDim.x)
-        vpart[static_cast<int64_t>(tile) * K + l] = cnt[l];
+    for (int l = threadIdx.x; l < K; l += blockDim.x) {
+        const int w = l >> 6, b = l & 63;
+        vpart[static_cast<int64_t>(tile) * K + l] =
+            static_cast<int>((cnt[((2 * (b >> 2) + (b & 1)) << lgWp) + w] >> (16 * ((b >> 1) & 1))) & 0xffffu);
+    }
 }
 
 void launch_eval_cover(hipStream_t s, int ntiles, const int *tile_ids, const Tiles &et,
@@ -753,10 +850,15 @@ void launch_eval_cover(hipStream_t s, int ntiles, const int *tile_ids, const Til
     if (!ntiles) return;
     int lg = 0;
     while ((1 << lg) < W) ++lg;
+    // few tiles: larger workgroups, so that more rows of a tile are in flight,
+    // up to what is resident at once (four wavefronts per SIMD; beyond that a
+    // second, nearly empty wave of workgroups trails)
+    int threads = 256;
+    while (threads < 1024 && static_cast<int64_t>(ntiles) * (2 * threads / 64) <= 4096) threads *= 2;
     if (pair_rows)
-        k_eval_cover<4><<<ntiles, 256, 0, s>>>(tile_ids, et.b0, et.b1, rows, rkind, rp, ci, X, xkind, W, lg, vpart, K);
+        k_eval_cover<4><<<ntiles, threads, 0, s>>>(tile_ids, et.b0, et.b1, rows, rkind, rp, ci, X, xkind, W, lg, vpart, K);
     else
-        k_eval_cover<1><<<ntiles, 256, 0, s>>>(tile_ids, et.b0, et.b1, rows, rkind, rp, ci, X, xkind, W, lg, vpart, K);
+        k_eval_cover<1><<<ntiles, threads, 0, s>>>(tile_ids, et.b0, et.b1, rows, rkind, rp, ci, X, xkind, W, lg, vpart, K);
 }
 
 // ---------------------------------------------------------------------------
@@ -1320,12 +1422,23 @@ void launch_reduce_cand(hipStream_t s, int T, int K, int S, const Tiles &et, con
                         const Tiles &st, const int64_t *zpart, const Tiles &qt,
                         const int64_t *zqpart, int has_q, int32_t *rv, int64_t *rz,
                         int32_t *viol, int64_t *z) {
+    if (S == 1) return;   // launch_argmin_update adds the few tiles itself
     dim3 g1(T, (K + 255) / 256, S);
     k_reduce_cand1<<<g1, 256, 0, s>>>(K, S, et.first, vpart, st.first, zpart,
                                        has_q ? qt.first : st.first, zqpart, has_q, rv, rz);
     dim3 g2(T, (K + 255) / 256);
     k_reduce_cand2<<<g2, 256, 0, s>>>(K, S, rv, rz, viol, z);
 }
+
+// Per candidate l of an instance: its violations and objective summed over the
+// instance's tiles.
+struct CandSums {
+    const int *efirst, *vpart, *sfirst;
+    const int64_t *zpart;
+    const int *qfirst;
+    const int64_t *zqpart;
+    int has_q;
+};
 
 // ---------------------------------------------------------------------------
 // EvalBest: l* = lowest index attaining min{z_l : viol_l = 0}; replace the
@@ -1334,19 +1447,39 @@ void launch_reduce_cand(hipStream_t s, int T, int K, int S, const Tiles &et, con
 //   rho_n = min(max(rho_min (1 + n/T)^p, rho_{n-1} + delta), rho_max).
 // advance: 0 = final rounding (no round consumed), 1 = sampling trigger (round
 // consumed, rho advances), 2 = extra round within a trigger (round consumed,
-// rho unchanged).  One block per instance.
+// rho unchanged).  One block per instance.  SUM: the per-tile partials are added
+// here first (instances of few tiles: one launch for what takes three, about
+// 4.5 us each).
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256)
-k_argmin_update(int K, int W, const int32_t *__restrict__ viol, const int64_t *__restrict__ z,
+template <bool SUM>
+__global__ void __launch_bounds__(1024)
+k_argmin_update(int K, int W, CandSums cs, int32_t *__restrict__ viol, int64_t *__restrict__ z,
                 DevInst di, DevCounters *__restrict__ ctr, int advance) {
-    __shared__ int64_t bz[256];
-    __shared__ int bl[256];
+    __shared__ int64_t bz[1024];
+    __shared__ int bl[1024];
     const int inst = blockIdx.x;
     int64_t best = INT64_MAX;
     int bi = 0x7fffffff;
-    for (int l = threadIdx.x; l < K; l += 256) {
-        const int64_t zl = z[static_cast<int64_t>(inst) * K + l];
-        if (viol[static_cast<int64_t>(inst) * K + l] == 0 && (zl < best || (zl == best && l < bi))) {
+    for (int l = threadIdx.x; l < K; l += blockDim.x) {
+        const int64_t o = static_cast<int64_t>(inst) * K + l;
+        int v = 0;
+        int64_t zl = 0;
+        if (SUM) {
+#pragma unroll 4
+            for (int t = cs.efirst[inst]; t < cs.efirst[inst + 1]; ++t) v += cs.vpart[static_cast<int64_t>(t) * K + l];
+#pragma unroll 4
+            for (int t = cs.sfirst[inst]; t < cs.sfirst[inst + 1]; ++t) zl += cs.zpart[static_cast<int64_t>(t) * K + l];
+            if (cs.has_q)
+#pragma unroll 4
+                for (int t = cs.qfirst[inst]; t < cs.qfirst[inst + 1]; ++t)
+                    zl += cs.zqpart[static_cast<int64_t>(t) * K + l];
+            viol[o] = v;
+            z[o] = zl;
+        } else {
+            v = viol[o];
+            zl = z[o];
+        }
+        if (v == 0 && (zl < best || (zl == best && l < bi))) {
             best = zl;
             bi = l;
         }
@@ -1354,7 +1487,7 @@ k_argmin_update(int K, int W, const int32_t *__restrict__ viol, const int64_t *_
     bz[threadIdx.x] = best;
     bl[threadIdx.x] = bi;
     __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
+    for (int o = blockDim.x / 2; o > 0; o >>= 1) {
         if (static_cast<int>(threadIdx.x) < o) {
             const int64_t z2 = bz[threadIdx.x + o];
             const int l2 = bl[threadIdx.x + o];
@@ -1390,18 +1523,21 @@ k_argmin_update(int K, int W, const int32_t *__restrict__ viol, const int64_t *_
     }
 }
 
-__global__ void k_round_bump(DevCounters *ctr) { ctr->round += 1; }
-
-void launch_argmin_update(hipStream_t s, int T, int K, int W, const int32_t *viol,
-                          const int64_t *z, DevInst di, DevCounters *ctr, int advance) {
-    k_argmin_update<<<T, 256, 0, s>>>(K, W, viol, z, di, ctr, advance);
-    if (advance) k_round_bump<<<1, 1, 0, s>>>(ctr);
+void launch_argmin_update(hipStream_t s, int T, int K, int W, int S, const Tiles &et, const int *vpart,
+                          const Tiles &st, const int64_t *zpart, const Tiles &qt, const int64_t *zqpart, int has_q,
+                          int32_t *viol, int64_t *z, DevInst di, DevCounters *ctr, int advance) {
+    const CandSums cs{et.first, vpart, st.first, zpart, has_q ? qt.first : st.first, zqpart, has_q};
+    const int threads = K >= 1024 ? 1024 : (K >= 512 ? 512 : 256);
+    if (S == 1) k_argmin_update<true><<<T, threads, 0, s>>>(K, W, cs, viol, z, di, ctr, advance);
+    else k_argmin_update<false><<<T, threads, 0, s>>>(K, W, cs, viol, z, di, ctr, advance);
 }
 
 // x_best of every instance whose incumbent just improved: byte per variable.
+// Also ends the round (round counter) when `advance` is set.
 __global__ void __launch_bounds__(256)
 k_extract_best(int64_t n, int T, const int *__restrict__ var_inst, const uint64_t *__restrict__ X,
-               DevInst di, uint8_t *__restrict__ xbest) {
+               DevInst di, uint8_t *__restrict__ xbest, DevCounters *__restrict__ ctr, int advance) {
+    if (advance && blockIdx.x == 0 && threadIdx.x == 0) ctr->round += 1;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
         const int t = T > 1 ? var_inst[i] : 0;
@@ -1414,11 +1550,11 @@ k_extract_best(int64_t n, int T, const int *__restrict__ var_inst, const uint64_
 }
 
 void launch_extract_best(hipStream_t s, int64_t n, int T, const int *var_inst, const uint64_t *X, DevInst di,
-                         uint8_t *xbest) {
+                         uint8_t *xbest, DevCounters *ctr, int advance) {
     int64_t b = (n + 255) / 256;
     if (b > 8192) b = 8192;
     if (b < 1) b = 1;
-    k_extract_best<<<static_cast<int>(b), 256, 0, s>>>(n, T, var_inst, X, di, xbest);
+    k_extract_best<<<static_cast<int>(b), 256, 0, s>>>(n, T, var_inst, X, di, xbest, ctr, advance);
 }
 
 }  // namespace gfors
