@@ -1855,6 +1855,23 @@ static void enqueue_steps(gfors_problem *P, int nsteps, bool want_res, KTimer *t
         P->cur = z;
         return;
     }
+    // dense int16 batches: a launch per step (the residual step and timed steps
+    // keep the two products apart; same sums in the same order).  The second
+    // buffer of tile sums lies in Preprocess's scratch.
+    const int joint = nsteps - (want_res ? 1 : 0);
+    if (joint > 0 && !tm && P->cfg.bits_dual == 4 && P->cfg.bits_primal == 5 && P->blk.pval &&
+        static_cast<int64_t>(P->blk.ntile) * 64 * 4 <= P->n * 8) {
+        float *pp[2] = {P->blk.pp, reinterpret_cast<float *>(P->pu)};
+        launch_dual_block_sums(s, P->blk, P->d_inst_var0, P->d_inst_nvar, P->xbar, pp[0]);
+        for (int it = 0; it < joint; ++it) {
+            const int a = P->cur, z = 1 - P->cur;
+            launch_step_block(s, P->blk, static_cast<int>(P->m1), P->d_inst_var0, P->d_inst_nvar, pp[it & 1],
+                              it + 1 < joint ? pp[1 - (it & 1)] : nullptr, P->omega, P->rt, P->di.tau2, P->ybuf[a],
+                              P->ybuf[z], P->wy, P->xbuf[a], P->xbuf[z], P->xbar, P->ct, P->di.tau1, P->di.rho, P->ctr);
+            P->cur = z;
+        }
+        nsteps -= joint;
+    }
     for (int it = 0; it < nsteps; ++it) {
         const bool res = want_res && it == nsteps - 1;
         if (res) launch_copy_f32(s, P->xsave, P->xbar, P->n);

@@ -270,6 +270,16 @@ struct BlockView {
     const int16_t *pval = nullptr;
     const int64_t *pbase = nullptr;
 };
+// A step of the padded int16 form in one launch: rows from the tile sums pp_in
+// (launch_dual_block_sums before the first step), the primal step, and the tile
+// sums of the next step into pp_out (null: the last step of a run).
+void launch_dual_block_sums(hipStream_t s, const BlockView &b, const int64_t *inst_var0, const int64_t *inst_nvar,
+                            const float *xbar, float *pp);
+void launch_step_block(hipStream_t s, const BlockView &b, int m1, const int64_t *inst_var0, const int64_t *inst_nvar,
+                       const float *pp_in, float *pp_out, const float *omega, const float *rt,
+                       const float *tau2_inst, const float *y_in, float *y_out, float *wy, const float *x_in,
+                       float *x_out, float *xbar, const float *ct, const float *tau1_inst, const double *rho,
+                       DevCounters *ctr);
 constexpr int kBlockCols = 2048;   // columns per tile of the dense-block SpMVs (256 threads x 8)
 void launch_dual_block(hipStream_t s, const BlockView &b, int m, int m1, const int *rp, const int *val,
                        const int16_t *val16, const int64_t *inst_var0, const int64_t *inst_nvar,

@@ -1607,6 +1607,183 @@ k_primal_block(const int *__restrict__ tile_inst, const int *__restrict__ tile_c
     }
 }
 
+// A whole step in one launch (padded int16 coefficients): the row updates from
+// the tile sums of the previous launch, the primal step of the tile, and the
+// tile's sums for the next step's rows from the xbar just made.  Same sums in
+// the same order as k_dual_block16 + k_dual_block_combine + k_primal_block16.
+//
+// Apart, the two products read every coefficient twice and the step takes three
+// launches; here a thread keeps its eight columns of the first H rows in
+// registers between the products (4 registers a row; further rows are read
+// again), all of them loaded before anything waits.  H = 36 leaves three
+// wavefronts per SIMD.  Every workgroup of an instance updates the instance's
+// rows for itself (row = lane; <= 64 rows x a few tiles of L2 reads), the first
+// one stores them.  pp_in / pp_out are two buffers: a workgroup may still read
+// the old sums while another writes new ones.
+// 128 knapsacks of 1,000 to 50,000 variables, 5 to 50 rows: dual 25.7 us +
+// combine 4.7 + primal 27.5 us per step before, 32 now (H = 24: 35, 44: 38,
+// 64: 51; the step moves 128 MB).
+constexpr int kBlkHold = 36;
+template <bool DUAL>
+__global__ void __launch_bounds__(256, 3)
+k_step_block16(const int *__restrict__ tile_inst, const int *__restrict__ tile_c0,
+               const int *__restrict__ blk_row0, const int *__restrict__ blk_nrow,
+               const int *__restrict__ blk_rows, const int64_t *__restrict__ pbase,
+               const int *__restrict__ inst_tile0, const int *__restrict__ inst_ntile,
+               const int64_t *__restrict__ inst_var0, const int64_t *__restrict__ inst_nvar,
+               const int16_t *__restrict__ pval, int m1, const float *__restrict__ pp_in,
+               float *__restrict__ pp_out, const float *__restrict__ omega, const float *__restrict__ rt,
+               const float *__restrict__ tau2_inst, const float *__restrict__ y_in, float *__restrict__ y_out,
+               float *__restrict__ wy, const float *__restrict__ x_in, float *__restrict__ x_out,
+               float *__restrict__ xbar, const float *__restrict__ ct, const float *__restrict__ tau1_inst,
+               const double *__restrict__ rho, DevCounters *__restrict__ ctr) {
+    __shared__ float red[4][64];
+    __shared__ float4 gs4[kBlkCols / 4];
+    constexpr int CPT = kBlkCols / 256, H = kBlkHold;
+    static_assert(CPT == 8, "one 16-byte load of a row per thread");
+    const int g = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    if (g == 0 && tid == 0) ctr->k += 1;
+    const int t = tile_inst[g];
+    const int v0 = static_cast<int>(inst_var0[t]);
+    const int c0 = tile_c0[g], c1 = min(c0 + kBlkCols, v0 + static_cast<int>(inst_nvar[t]));
+    const int nr = blk_nrow[t], r0 = blk_row0[t];
+    const int cb = c0 + CPT * tid, coff = cb - v0;
+    const bool in = cb < c1;
+    auto coef = [&](int r) -> int4 {
+        return *reinterpret_cast<const int4 *>(pval + pbase[r0 + r] + coff);
+    };
+    int4 q[H];
+#pragma unroll
+    for (int r = 0; r < H; ++r) q[r] = in && r < nr ? coef(r) : make_int4(0, 0, 0, 0);
+    // the rows' updates (k_dual_block_combine): row = lane, in every wavefront
+    float w = 0.f;
+    if (lane < nr) {
+        const int j = blk_rows[r0 + lane];
+        const int g0 = inst_tile0[t], ng = inst_ntile[t];
+        const float *pr = pp_in + static_cast<int64_t>(g0) * 64 + lane;
+        const float om = omega[j], rtj = rt[j], yj = y_in[j];
+        float s = 0.f;
+        int k = 0;
+        for (; k + 8 <= ng; k += 8) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = pr[static_cast<int64_t>(k + u) * 64];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += v[u];
+        }
+        for (; k < ng; ++k) s += pr[static_cast<int64_t>(k) * 64];
+        const float y = dual_update(s, om, rtj, tau2_inst[t], yj, j < m1);
+        w = om * y;
+        if (g == g0 && wv == 0) {
+            y_out[j] = y;
+            wy[j] = w;
+        }
+    }
+    auto w_of = [&](int r) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), r)); };
+    float acc[CPT];
+#pragma unroll
+    for (int k = 0; k < CPT; ++k) acc[k] = 0.f;
+#pragma unroll
+    for (int r = 0; r < H; r += 4)
+        if (r < nr) {                                       // uniform; rows past the last add 0 x 0
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float wr = w_of(r + u);
+                float a[8];
+                unpack8(q[r + u], a);
+#pragma unroll
+                for (int k = 0; k < CPT; ++k) acc[k] = fmaf(a[k], wr, acc[k]);
+            }
+        }
+#pragma unroll 4
+    for (int r = H; r < nr; ++r) {
+        const float wr = w_of(r);
+        float a[8];
+        unpack8(in ? coef(r) : make_int4(0, 0, 0, 0), a);
+#pragma unroll
+        for (int k = 0; k < CPT; ++k) acc[k] = fmaf(a[k], wr, acc[k]);
+    }
+    // through LDS, so that the update's loads and stores are coalesced; xbar
+    // comes back the same way for the thread's own eight columns
+#pragma unroll
+    for (int h = 0; h < CPT / 4; ++h)
+        gs4[(CPT / 4) * tid + h] = make_float4(acc[4 * h], acc[4 * h + 1], acc[4 * h + 2], acc[4 * h + 3]);
+    __syncthreads();
+    float *gs = reinterpret_cast<float *>(gs4);
+    const float rh = static_cast<float>(rho[t]);
+    const float ta = tau1_inst[t];
+#pragma unroll
+    for (int k = 0; k < CPT; ++k) {
+        const int c = c0 + 256 * k + tid;
+        float xb = 0.f;
+        if (c < c1) {
+            const float xi = x_in[c];
+            const float xn = primal_update(gs[256 * k + tid], ct[c], rh, ta, xi);
+            xb = 2.f * xn - xi;
+            x_out[c] = xn;
+            xbar[c] = xb;
+        }
+        if (DUAL) gs[256 * k + tid] = xb;
+    }
+    if (!DUAL) return;
+    __syncthreads();
+    // unpack again rather than keep both forms: 8 registers a row otherwise
+#pragma unroll
+    for (int r = 0; r < H; ++r) asm volatile("" : "+v"(q[r].x), "+v"(q[r].y), "+v"(q[r].z), "+v"(q[r].w));
+    float xv[CPT];
+#pragma unroll
+    for (int h = 0; h < CPT / 4; ++h) {
+        const float4 a = gs4[(CPT / 4) * tid + h];
+        xv[4 * h] = a.x; xv[4 * h + 1] = a.y; xv[4 * h + 2] = a.z; xv[4 * h + 3] = a.w;
+    }
+    auto four = [&](int r, const int4 (&qq)[4]) {
+        float s[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            float a[8];
+            unpack8(qq[u], a);
+            s[u] = 0.f;
+#pragma unroll
+            for (int k = 0; k < CPT; ++k) s[u] = fmaf(a[k], xv[k], s[u]);
+        }
+        const float v = wave_sum4(s[0], s[1], s[2], s[3]);
+        const int row = r + wave_sum4_of(lane);
+        if ((lane & 15) == 0 && row < nr) red[wv][row] = v;
+    };
+#pragma unroll
+    for (int r = 0; r < H; r += 4)
+        if (r < nr) {                                       // uniform
+            const int4 qq[4] = {q[r], q[r + 1], q[r + 2], q[r + 3]};
+            four(r, qq);
+        }
+    for (int r = H; r < nr; r += 4) {
+        int4 qq[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) qq[u] = in && r + u < nr ? coef(r + u) : make_int4(0, 0, 0, 0);
+        four(r, qq);
+    }
+    __syncthreads();
+    if (tid < nr)
+        pp_out[static_cast<int64_t>(g) * 64 + tid] = ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
+}
+
+void launch_dual_block_sums(hipStream_t s, const BlockView &b, const int64_t *inst_var0, const int64_t *inst_nvar,
+                            const float *xbar, float *pp) {
+    k_dual_block16<<<b.ntile, 256, 0, s>>>(b.ntile, b.tile_inst, b.tile_c0, b.row0, b.nrow, b.pbase, inst_var0,
+                                           inst_nvar, b.pval, xbar, pp);
+}
+void launch_step_block(hipStream_t s, const BlockView &b, int m1, const int64_t *inst_var0, const int64_t *inst_nvar,
+                       const float *pp_in, float *pp_out, const float *omega, const float *rt,
+                       const float *tau2_inst, const float *y_in, float *y_out, float *wy, const float *x_in,
+                       float *x_out, float *xbar, const float *ct, const float *tau1_inst, const double *rho,
+                       DevCounters *ctr) {
+#define GF_SB(D) k_step_block16<D><<<b.ntile, 256, 0, s>>>(b.tile_inst, b.tile_c0, b.row0, b.nrow, b.rows, b.pbase, \
+        b.inst_tile0, b.inst_ntile, inst_var0, inst_nvar, b.pval, m1, pp_in, pp_out, omega, rt, tau2_inst, y_in, y_out, \
+        wy, x_in, x_out, xbar, ct, tau1_inst, rho, ctr)
+    if (pp_out) GF_SB(true); else GF_SB(false);
+#undef GF_SB
+}
+
 void launch_dual_block(hipStream_t s, const BlockView &b, int m, int m1, const int *rp, const int *val,
                        const int16_t *val16, const int64_t *inst_var0, const int64_t *inst_nvar,
                        const float *xbar, const float *omega, const float *rt, const float *tau2_inst,
