@@ -2476,13 +2476,11 @@ int gnn_run(gfors_gnn *G, gfors_problem *P, const float *x, const float *y, cons
         const uint16_t *wfc = G->wf + static_cast<int64_t>(2 * l) * 128 * 64;
         const uint16_t *wfv = G->wf + static_cast<int64_t>(2 * l + 1) * 128 * 64;
         // constraint side: Hc = relu([Hc | E Hv] W + bc)
-        launch_gnn_spmm(s, true, true, 0, m, P->dual_order, P->gnn_rh, P->gnn_rm, P->rp, P->ci, val,
-                        P->rowinv32, a.Hv[l], a.Sc[l]);
-        launch_gnn_dense_fwd(s, m, a.Hc[l], a.Sc[l], wfc, lay + 2 * 4096, a.Hc[l + 1]);
+        launch_gnn_layer(s, true, m, P->dual_order, P->gnn_rh, P->gnn_rm, P->rp, P->ci, val, P->rowinv32, a.Hv[l],
+                         a.Hc[l], a.Sc[l], training, wfc, lay + 2 * 4096, a.Hc[l + 1]);
         // variable side: Hv = relu([Hv | E^T Hc] W + bv)
-        launch_gnn_spmm(s, false, true, 0, n, P->primal_order, P->gnn_ch, P->gnn_cm, P->rpT, P->ciT, valT,
-                        P->rowinv32, a.Hc[l + 1], a.Sv[l]);
-        launch_gnn_dense_fwd(s, n, a.Hv[l], a.Sv[l], wfv, lay + 8256 + 2 * 4096, a.Hv[l + 1]);
+        launch_gnn_layer(s, false, n, P->primal_order, P->gnn_ch, P->gnn_cm, P->rpT, P->ciT, valT, P->rowinv32,
+                         a.Hc[l + 1], a.Hv[l], a.Sv[l], training, wfv, lay + 8256 + 2 * 4096, a.Hv[l + 1]);
     }
     launch_gnn_out(s, n, a.Hv[kGnnL], G->theta, logit_out ? logit_out : a.logit, p_out ? p_out : a.p,
                    training ? target : nullptr, a.dHv, G->part, kGnnMaxParts, G->grad, G->loss);

@@ -40,8 +40,11 @@ void launch_gnn_embed(hipStream_t s, int64_t n, int64_t m, int m1, const float *
 void launch_gnn_spmm(hipStream_t s, bool rows, bool in_bf16, int out_mode, int64_t nrows,
                      const int *order, int nheavy, int nmedium, const int *rp, const int *ci,
                      const int *val, const float *rowinv, const void *in, void *out);
-void launch_gnn_dense_fwd(hipStream_t s, int64_t N, const uint16_t *A1, const uint16_t *A2,
-                          const uint16_t *BT, const float *bias, uint16_t *out);
+// out = relu([H | S] W + bias) with S = E in of the side's nodes; S receives the
+// messages of the nheavy + nmedium long nodes, and of all of them with store_s
+void launch_gnn_layer(hipStream_t s, bool rows, int64_t N, const int *order, int nheavy, int nmedium, const int *rp,
+                      const int *ci, const int *val, const float *rowinv, const uint16_t *in, const uint16_t *H,
+                      uint16_t *S, bool store_s, const uint16_t *BT, const float *bias, uint16_t *out);
 void launch_gnn_dense_bwd_in(hipStream_t s, int64_t N, const uint16_t *dZ, const uint16_t *Wrm,
                              float *dA1, float *dA2, int accumulate);
 void launch_gnn_wgrad(hipStream_t s, int64_t N, const uint16_t *A1, const uint16_t *A2,

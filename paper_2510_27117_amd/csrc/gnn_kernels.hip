@@ -430,24 +430,33 @@ k_gnn_gemm(int64_t N, const uint16_t *__restrict__ A1, const uint16_t *__restric
     }
 }
 
-// Forward dense layer out = relu([H | S] W + bias) over N rows (H, S: BF16
-// [N][64]; W as BT[64 out][128 in] in LDS; BF16 out).  A wavefront owns 16
-// rows at a time; lane (li, kq) loads 16 bytes of row li four times: H and S
-// columns 8 kq .. 8 kq + 7 and 32 + 8 kq .. 32 + 8 kq + 7 (each load fills
-// 64-byte segments of 16 rows), and the next 16 rows' loads are issued before
-// the current rows' MFMAs.  The contraction order is permuted alike in A and
-// B: in the MFMA step that uses half h of load q, lane (li, kq) supplies
-// the k indices kb(q) + 8 kq + 4 h + j (j = 0..3) of both operands, with
-// kb = 0, 32, 64, 96 for H low, H high, S low, S high.  The result tile goes
-// through LDS and is written with 16-byte stores.
+// A forward layer, out = relu([H | S] W + bias), with the messages S of the
+// short nodes computed on the way: S would otherwise be written and read back
+// (2 x 128 bytes a node of the 5 x 128 that the two kernels moved; 2M + 2M nodes
+// of mostly two entries: 222 + 150 us before, LAYER_US now).  Nodes come in
+// `order`; the first k2 (heavy and medium) find their S in the buffer, the others
+// gather E_e in[col_e] over their entries (at most kGnnShortLen), in entry order
+// in FP32, as k_gnn_spmm_short does; it is also stored where training needs it.
+//
+// A wavefront takes 16 nodes at a time; lane (li, kq) holds columns 8 kq .. 8 kq
+// + 7 and 32 + 8 kq .. 32 + 8 kq + 7 of node li's H and S (16-byte loads that fill
+// 64-byte segments).  The contraction order is permuted alike in A and B: in the
+// MFMA step that uses half h of part q, lane (li, kq) supplies the k indices
+// kb(q) + 8 kq + 4 h + j (j = 0..3) of both operands, kb = 0, 32, 64, 96 for H low,
+// H high, S low, S high.  W^T sits in LDS with its rows padded to 272 bytes (at
+// 256 the sixteen rows of a read share their banks); the result tile goes through
+// LDS and is written with 16-byte stores.
+template <bool ROWS>
 __global__ void __launch_bounds__(256)
-k_gnn_dense_fwd(int64_t N, const uint16_t *__restrict__ H, const uint16_t *__restrict__ S,
-                const uint16_t *__restrict__ BT, const float *__restrict__ bias,
-                uint16_t *__restrict__ out) {
-    __shared__ uint16_t sB[64 * 128];
-    __shared__ uint16_t sO[4][16 * 64];
+k_gnn_layer(int64_t N, int64_t k2, const int *__restrict__ order, const int *__restrict__ rp,
+            const int *__restrict__ ci, const int *__restrict__ val, const float *__restrict__ rowinv,
+            const uint16_t *__restrict__ in, const uint16_t *__restrict__ H, uint16_t *__restrict__ S, int store_s,
+            const uint16_t *__restrict__ BT, const float *__restrict__ bias, uint16_t *__restrict__ out) {
+    constexpr int LB = 136;   // row pitch of W^T in LDS
+    __shared__ __align__(16) uint16_t sB[64 * LB];
+    __shared__ __align__(16) uint16_t sO[4][16 * 64];
     for (int i = threadIdx.x; i < 64 * 128 / 4; i += blockDim.x)
-        reinterpret_cast<uint2 *>(sB)[i] = reinterpret_cast<const uint2 *>(BT)[i];
+        *reinterpret_cast<uint2 *>(&sB[(i >> 5) * LB + 4 * (i & 31)]) = reinterpret_cast<const uint2 *>(BT)[i];
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int li = lane & 15, kq = lane >> 4;
@@ -455,26 +464,78 @@ k_gnn_dense_fwd(int64_t N, const uint16_t *__restrict__ H, const uint16_t *__res
 #pragma unroll
     for (int t = 0; t < 4; ++t) bcol[t] = bias ? bias[t * 16 + li] : 0.f;
     const int64_t step = static_cast<int64_t>(gridDim.x) * 64;
-    auto load = [&](int64_t row0, uint4 *a) {
-        const int64_t ra = row0 + li;
-        if (ra < N) {
-            const uint4 *h = reinterpret_cast<const uint4 *>(H + ra * kGnnH);
-            const uint4 *sv = reinterpret_cast<const uint4 *>(S + ra * kGnnH);
-            a[0] = h[kq];
-            a[1] = h[4 + kq];
-            a[2] = sv[kq];
-            a[3] = sv[4 + kq];
-        } else {
+    for (int64_t row0 = (static_cast<int64_t>(blockIdx.x) * 4 + wave) * 16; row0 < N; row0 += step) {
+        const int64_t k = row0 + li;
+        const bool live = k < N, kept = live && k < k2;
+        const int64_t r = live ? order[k] : 0;
+        uint4 cur[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) a[q] = make_uint4(0u, 0u, 0u, 0u);
+        for (int q = 0; q < 4; ++q) cur[q] = make_uint4(0u, 0u, 0u, 0u);
+        int e = 0, e1 = 0;
+        if (live) {
+            const uint4 *h = reinterpret_cast<const uint4 *>(H + r * kGnnH);
+            cur[0] = h[kq];
+            cur[1] = h[4 + kq];
+            if (kept) {
+                const uint4 *sv = reinterpret_cast<const uint4 *>(S + r * kGnnH);
+                cur[2] = sv[kq];
+                cur[3] = sv[4 + kq];
+            } else {
+                e = rp[r];
+                e1 = rp[r + 1];
+            }
         }
-    };
-    int64_t row0 = (static_cast<int64_t>(blockIdx.x) * 4 + wave) * 16;
-    uint4 cur[4];
-    if (row0 < N) load(row0, cur);
-    for (; row0 < N; row0 += step) {
-        uint4 nxt[4];
-        if (row0 + step < N) load(row0 + step, nxt);
+        if (__any(live && !kept)) {
+            const float rs = ROWS && live ? rowinv[r] : 1.f;
+            float s[16];
+#pragma unroll
+            for (int t = 0; t < 16; ++t) s[t] = 0.f;
+            for (; __any(e < e1); e += 2) {
+                float a[2];
+                uint4 g[2][2];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    a[u] = 0.f;
+                    g[u][0] = g[u][1] = make_uint4(0u, 0u, 0u, 0u);
+                    if (e + u < e1) {
+                        const int c = ci[e + u];
+                        a[u] = val ? static_cast<float>(val[e + u]) : 1.f;
+                        a[u] *= ROWS ? rs : rowinv[c];
+                        const uint4 *f = reinterpret_cast<const uint4 *>(in + static_cast<int64_t>(c) * kGnnH);
+                        g[u][0] = f[kq];
+                        g[u][1] = f[4 + kq];
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) {
+                        const uint32_t w[4] = {g[u][p].x, g[u][p].y, g[u][p].z, g[u][p].w};
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) {
+                            float *d = s + 8 * p + 2 * t;
+                            d[0] = fmaf(a[u], __uint_as_float(w[t] << 16), d[0]);
+                            d[1] = fmaf(a[u], __uint_as_float(w[t] & 0xFFFF0000u), d[1]);
+                        }
+                    }
+            }
+            if (!kept) {
+#pragma unroll
+                for (int p = 0; p < 2; ++p) {
+                    uint32_t w[4];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        w[t] = static_cast<uint32_t>(f2bf(s[8 * p + 2 * t])) |
+                               (static_cast<uint32_t>(f2bf(s[8 * p + 2 * t + 1])) << 16);
+                    cur[2 + p] = make_uint4(w[0], w[1], w[2], w[3]);
+                }
+                if (store_s && live) {
+                    uint4 *sv = reinterpret_cast<uint4 *>(S + r * kGnnH);
+                    sv[kq] = cur[2];
+                    sv[4 + kq] = cur[3];
+                }
+            }
+        }
         f32x4 acc[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -492,7 +553,7 @@ k_gnn_dense_fwd(int64_t N, const uint16_t *__restrict__ H, const uint16_t *__res
                 const int kk = kb + 4 * hf;
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
-                    const bf16x4 b = *reinterpret_cast<const bf16x4 *>(&sB[(t * 16 + li) * 128 + kk]);
+                    const bf16x4 b = *reinterpret_cast<const bf16x4 *>(&sB[(t * 16 + li) * LB + kk]);
                     acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[t], 0, 0, 0);
                 }
             }
@@ -506,17 +567,15 @@ k_gnn_dense_fwd(int64_t N, const uint16_t *__restrict__ H, const uint16_t *__res
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
         const int rr = lane >> 2, cq = (lane & 3) * 16;
-        const int64_t r = row0 + rr;
-        if (r < N) {
+        const int64_t ro = __shfl(static_cast<int>(r), rr, 64);
+        if (row0 + rr < N) {
             const uint4 *src = reinterpret_cast<const uint4 *>(T + rr * 64 + cq);
-            uint4 *dst = reinterpret_cast<uint4 *>(out + r * kGnnH + cq);
+            uint4 *dst = reinterpret_cast<uint4 *>(out + ro * kGnnH + cq);
             dst[0] = src[0];
             dst[1] = src[1];
         }
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int q = 0; q < 4; ++q) cur[q] = nxt[q];
     }
 }
 
@@ -526,11 +585,20 @@ static int gemm_grid(int64_t N) {
     return static_cast<int>(b < 1 ? 1 : b);
 }
 
-// Forward dense layer: out = relu([A1|A2] W + bias), W given as BT[64][128].
-void launch_gnn_dense_fwd(hipStream_t s, int64_t N, const uint16_t *A1, const uint16_t *A2,
-                          const uint16_t *BT, const float *bias, uint16_t *out) {
+// Forward layer of one side: the messages of the long nodes into S, then the
+// dense layer with those of the short nodes on the way.
+void launch_gnn_layer(hipStream_t s, bool rows, int64_t N, const int *order, int nheavy, int nmedium, const int *rp,
+                      const int *ci, const int *val, const float *rowinv, const uint16_t *in, const uint16_t *H,
+                      uint16_t *S, bool store_s, const uint16_t *BT, const float *bias, uint16_t *out) {
     if (N <= 0) return;
-    k_gnn_dense_fwd<<<gemm_grid(N), 256, 0, s>>>(N, A1, A2, BT, bias, out);
+    const int64_t k2 = static_cast<int64_t>(nheavy) + nmedium;
+    launch_gnn_spmm(s, rows, true, 0, k2, order, nheavy, nmedium, rp, ci, val, rowinv, in, S);
+    // enough workgroups to fill the device; each stages W once
+    const int grid = std::min(gemm_grid(N), 2048);
+    if (rows)
+        k_gnn_layer<true><<<grid, 256, 0, s>>>(N, k2, order, rp, ci, val, rowinv, in, H, S, store_s ? 1 : 0, BT, bias, out);
+    else
+        k_gnn_layer<false><<<grid, 256, 0, s>>>(N, k2, order, rp, ci, val, rowinv, in, H, S, store_s ? 1 : 0, BT, bias, out);
 }
 
 // Backward through a dense layer: [dA1 | dA2] (+)= dZ W^T, with W^T given as
