@@ -21,6 +21,13 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
     return static_cast<uint16_t>(r >> 16);
 }
 
+// Two values rounded to BF16 (nearest even) in one word, the first in the low half.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t f2bf2(float lo, float hi) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){lo, hi}, bf16x2));
+}
+
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
 #pragma unroll
@@ -31,69 +38,57 @@ __device__ __forceinline__ T wave_sum(T v) {
 // ------------------------------------------------------------------ features
 // Hv0 = relu(Fv Uv + uv), Fv_i = [x_i, 4 x_i (1 - x_i), ct_i / ctmax, 1]
 // Hc0 = relu(Fc Uc + uc), Fc_j = [y_j / (1 + |y_j|), rt_j / rtmax, [j >= m1], 1]
-// 16 lanes per node (four hidden units each), four nodes per wavefront.
+// Eight lanes per node, lane f = hidden units 8f .. 8f + 7 (one 16-byte store, so
+// a wavefront writes 1 KiB in a row).  A workgroup embeds nodes of one side only:
+// choosing the weights per node took more instructions than the products
+// (2M + 2M nodes: 212 us, 134 now, at 512 MB written).
 __global__ void __launch_bounds__(256)
-k_gnn_embed(int64_t n, int64_t m, int m1, const float *__restrict__ x, const float *__restrict__ y,
+k_gnn_embed(int64_t n, int64_t m, int nbv, int m1, const float *__restrict__ x, const float *__restrict__ y,
             const float *__restrict__ ct, const float *__restrict__ rt, float ictmax, float irtmax,
             const float *__restrict__ theta, uint16_t *__restrict__ Hv, uint16_t *__restrict__ Hc) {
-    // 16 lanes per node, lane f = hidden units 4f..4f+3 (one 8-byte store)
-    const int f = threadIdx.x & 15;
-    float Wv[4][4], Wc[4][4], bv[4], bc[4];
+    const bool var = static_cast<int>(blockIdx.x) < nbv;
+    const int f = threadIdx.x & 7;
+    const float *U = theta + (var ? kGnnOffUv : kGnnOffUc), *b0 = theta + (var ? kGnnOffuv : kGnnOffuc);
+    float W[3][8], bias[8];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        bv[t] = theta[kGnnOffuv + 4 * f + t] + theta[kGnnOffUv + 3 * kGnnH + 4 * f + t];
-        bc[t] = theta[kGnnOffuc + 4 * f + t] + theta[kGnnOffUc + 3 * kGnnH + 4 * f + t];
+    for (int t = 0; t < 8; ++t) {
+        bias[t] = b0[8 * f + t] + U[3 * kGnnH + 8 * f + t];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            Wv[k][t] = theta[kGnnOffUv + k * kGnnH + 4 * f + t];
-            Wc[k][t] = theta[kGnnOffUc + k * kGnnH + 4 * f + t];
-        }
+        for (int k = 0; k < 3; ++k) W[k][t] = U[k * kGnnH + 8 * f + t];
     }
-    // four nodes per 16-lane group and pass: their inputs are loaded together,
-    // so a wavefront keeps 8-12 loads in flight instead of 2-3
+    // four nodes per 8-lane group and pass: their inputs are loaded together
     constexpr int NPG = 4;
-    const int64_t N = n + m;
-    const int64_t ng = (static_cast<int64_t>(gridDim.x) * blockDim.x) >> 4;
-    for (int64_t base = (blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x) >> 4; base < N;
-         base += NPG * ng) {
-        float f0[NPG], f1[NPG], f2[NPG];
+    const int64_t N = var ? n : m;
+    const int64_t ng = (static_cast<int64_t>(var ? nbv : gridDim.x - nbv) * blockDim.x) >> 3;
+    const int64_t first = ((static_cast<int64_t>(blockIdx.x) - (var ? 0 : nbv)) * blockDim.x + threadIdx.x) >> 3;
+    const float *p0 = var ? x : y, *p1 = var ? ct : rt;
+    uint16_t *out = var ? Hv : Hc;
+    for (int64_t base = first; base < N; base += NPG * ng) {
+        float u[NPG], v[NPG];
 #pragma unroll
         for (int q = 0; q < NPG; ++q) {
             const int64_t node = base + q * ng;
-            if (node < n) {
-                const float xi = x[node];
-                f0[q] = xi;
-                f1[q] = 4.f * xi * (1.f - xi);
-                f2[q] = ct[node] * ictmax;
-            } else if (node < N) {
-                const int64_t j2 = node - n;
-                const float yj = y[j2];
-                f0[q] = yj / (1.f + fabsf(yj));
-                f1[q] = rt[j2] * irtmax;
-                f2[q] = j2 >= m1 ? 1.f : 0.f;
-            } else {
-                f0[q] = f1[q] = f2[q] = 0.f;
-            }
+            u[q] = node < N ? p0[node] : 0.f;
+            v[q] = node < N ? p1[node] : 0.f;
         }
 #pragma unroll
         for (int q = 0; q < NPG; ++q) {
             const int64_t node = base + q * ng;
             if (node >= N) break;
-            const bool var = node < n;
-            float h[4];
+            const float f0 = var ? u[q] : u[q] / (1.f + fabsf(u[q]));
+            const float f1 = var ? 4.f * u[q] * (1.f - u[q]) : v[q] * irtmax;
+            const float f2 = var ? v[q] * ictmax : (node >= m1 ? 1.f : 0.f);
+            float h[8];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                float z = var ? bv[t] : bc[t];
-                z = fmaf(f0[q], var ? Wv[0][t] : Wc[0][t], z);
-                z = fmaf(f1[q], var ? Wv[1][t] : Wc[1][t], z);
-                z = fmaf(f2[q], var ? Wv[2][t] : Wc[2][t], z);
+            for (int t = 0; t < 8; ++t) {
+                float z = bias[t];
+                z = fmaf(f0, W[0][t], z);
+                z = fmaf(f1, W[1][t], z);
+                z = fmaf(f2, W[2][t], z);
                 h[t] = fmaxf(z, 0.f);
             }
-            uint2 w;
-            w.x = static_cast<uint32_t>(f2bf(h[0])) | (static_cast<uint32_t>(f2bf(h[1])) << 16);
-            w.y = static_cast<uint32_t>(f2bf(h[2])) | (static_cast<uint32_t>(f2bf(h[3])) << 16);
-            uint16_t *dst = var ? Hv + node * kGnnH : Hc + (node - n) * kGnnH;
-            reinterpret_cast<uint2 *>(dst)[f] = w;
+            reinterpret_cast<uint4 *>(out + node * kGnnH)[f] =
+                make_uint4(f2bf2(h[0], h[1]), f2bf2(h[2], h[3]), f2bf2(h[4], h[5]), f2bf2(h[6], h[7]));
         }
     }
 }
@@ -108,7 +103,8 @@ k_gnn_embed(int64_t n, int64_t m, int m1, const float *__restrict__ x, const flo
 // Nodes come in `order`, longest first, in three classes by entry count:
 //   heavy  (>= kGnnHeavy)  a workgroup of 8 wavefronts per node;
 //   medium (> kGnnShort)   one wavefront per node;
-//   short                  16 lanes per node (four nodes per wavefront).
+//   short                  16 lanes per node (four nodes per wavefront); forward
+//                          (BF16) messages of short nodes are k_gnn_layer's.
 // In the heavy and medium kernels a lane handles features 4f..4f+3 (f = lane
 // & 15) of entry slot q = lane >> 4, so one load instruction gathers four
 // neighbours' feature rows; eight such loads are issued before any is used.
@@ -140,8 +136,8 @@ template <int OUT>
 __device__ __forceinline__ void store_feat4(void *__restrict__ out, int64_t row, int f, const float *a) {
     if (OUT == 0) {
         uint2 w;
-        w.x = static_cast<uint32_t>(f2bf(a[0])) | (static_cast<uint32_t>(f2bf(a[1])) << 16);
-        w.y = static_cast<uint32_t>(f2bf(a[2])) | (static_cast<uint32_t>(f2bf(a[3])) << 16);
+        w.x = f2bf2(a[0], a[1]);
+        w.y = f2bf2(a[2], a[3]);
         reinterpret_cast<uint2 *>(static_cast<uint16_t *>(out) + row * kGnnH)[f] = w;
     } else {
         float4 *o = reinterpret_cast<float4 *>(static_cast<float *>(out) + row * kGnnH) + f;
@@ -251,7 +247,7 @@ k_gnn_spmm_medium(int k0, int k1, const int *__restrict__ order, const int *__re
     }
 }
 
-template <bool ROWS, bool IN_BF16, int OUT>
+template <bool ROWS, int OUT>
 __global__ void __launch_bounds__(256)
 k_gnn_spmm_short(int k0, int k1, const int *__restrict__ order, const int *__restrict__ rp,
                  const int *__restrict__ ci, const int *__restrict__ val,
@@ -299,7 +295,7 @@ k_gnn_spmm_short(int k0, int k1, const int *__restrict__ order, const int *__res
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     a[q][u] *= ROWS ? rs[q] : rowinv[c[q][u]];
-                    h[q][u] = load_feat4<IN_BF16>(in, c[q][u], f);
+                    h[q][u] = load_feat4<false>(in, c[q][u], f);
                 }
 #pragma unroll
             for (int q = 0; q < NPG; ++q)
@@ -328,7 +324,7 @@ void launch_gnn_spmm(hipStream_t s, bool rows, bool in_bf16, int out_mode, int64
     do {                                                                                                         \
         if (bh > 0) k_gnn_spmm_heavy<R, IB, O><<<bh, 512, 0, s>>>(k1, order, rp, ci, val, rowinv, in, out);      \
         if (bm > 0) k_gnn_spmm_medium<R, IB, O><<<static_cast<int>(bm), 256, 0, s>>>(k1, k2, order, rp, ci, val, rowinv, in, out); \
-        if (bs > 0) k_gnn_spmm_short<R, IB, O><<<static_cast<int>(bs), 256, 0, s>>>(k2, k3, order, rp, ci, val, rowinv, in, out); \
+        if (!IB && bs > 0) k_gnn_spmm_short<R, O><<<static_cast<int>(bs), 256, 0, s>>>(k2, k3, order, rp, ci, val, rowinv, in, out); \
     } while (0)
 #define GF_SP2(R, IB) if (out_mode == 0) GF_SP(R, IB, 0); else if (out_mode == 1) GF_SP(R, IB, 1); else GF_SP(R, IB, 2)
     if (rows) { if (in_bf16) { GF_SP2(true, true); } else { GF_SP2(true, false); } }
@@ -433,7 +429,7 @@ k_gnn_gemm(int64_t N, const uint16_t *__restrict__ A1, const uint16_t *__restric
 // A forward layer, out = relu([H | S] W + bias), with the messages S of the
 // short nodes computed on the way: S would otherwise be written and read back
 // (2 x 128 bytes a node of the 5 x 128 that the two kernels moved; 2M + 2M nodes
-// of mostly two entries: 222 + 150 us before, LAYER_US now).  Nodes come in
+// of mostly two entries: 222 + 150 us before, 193 now).  Nodes come in
 // `order`; the first k2 (heavy and medium) find their S in the buffer, the others
 // gather E_e in[col_e] over their entries (at most kGnnShortLen), in entry order
 // in FP32, as k_gnn_spmm_short does; it is also stored where training needs it.
@@ -524,9 +520,7 @@ k_gnn_layer(int64_t N, int64_t k2, const int *__restrict__ order, const int *__r
                 for (int p = 0; p < 2; ++p) {
                     uint32_t w[4];
 #pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                        w[t] = static_cast<uint32_t>(f2bf(s[8 * p + 2 * t])) |
-                               (static_cast<uint32_t>(f2bf(s[8 * p + 2 * t + 1])) << 16);
+                    for (int t = 0; t < 4; ++t) w[t] = f2bf2(s[8 * p + 2 * t], s[8 * p + 2 * t + 1]);
                     cur[2 + p] = make_uint4(w[0], w[1], w[2], w[3]);
                 }
                 if (store_s && live) {
@@ -562,8 +556,11 @@ k_gnn_layer(int64_t N, int64_t k2, const int *__restrict__ order, const int *__r
 #pragma unroll
         for (int t = 0; t < 4; ++t)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                T[(4 * kq + j) * 64 + t * 16 + li] = f2bf(fmaxf(acc[t][j] + bcol[t], 0.f));
+            for (int j = 0; j < 4; j += 2) {
+                const uint32_t w = f2bf2(fmaxf(acc[t][j] + bcol[t], 0.f), fmaxf(acc[t][j + 1] + bcol[t], 0.f));
+                T[(4 * kq + j) * 64 + t * 16 + li] = static_cast<uint16_t>(w);
+                T[(4 * kq + j + 1) * 64 + t * 16 + li] = static_cast<uint16_t>(w >> 16);
+            }
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
         const int rr = lane >> 2, cq = (lane & 3) * 16;
@@ -914,10 +911,11 @@ void launch_gnn_embed_bwd(hipStream_t s, int64_t N, int is_var, int m1, const fl
 void launch_gnn_embed(hipStream_t s, int64_t n, int64_t m, int m1, const float *x, const float *y,
                       const float *ct, const float *rt, float ictmax, float irtmax,
                       const float *theta, uint16_t *Hv, uint16_t *Hc) {
-    int64_t blocks = ((n + m) * 16 + 255) / 256;
-    if (blocks > 16384) blocks = 16384;
-    if (blocks > 0)
-        k_gnn_embed<<<static_cast<int>(blocks), 256, 0, s>>>(n, m, m1, x, y, ct, rt, ictmax, irtmax, theta, Hv, Hc);
+    // workgroups shared out by the nodes of each side
+    auto blocks = [](int64_t nodes) { return static_cast<int>(std::min<int64_t>((nodes * 8 + 255) / 256, 8192)); };
+    const int bv = blocks(n), bc = blocks(m);
+    if (bv + bc > 0)
+        k_gnn_embed<<<bv + bc, 256, 0, s>>>(n, m, bv, m1, x, y, ct, rt, ictmax, irtmax, theta, Hv, Hc);
 }
 
 // ---------------------------------------------------------------------------
