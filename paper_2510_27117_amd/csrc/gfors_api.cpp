@@ -1462,6 +1462,41 @@ static int device_norms(gfors_problem *P) {
 // zero-skipping variants read the nonzero bitmap of the vector they gather;
 // it is rebuilt (k_nzbits) unless the kernel that last wrote the vector, in
 // the same enqueued sequence, already wrote the bitmap with it.
+static DualLongArgs dual_long_args(gfors_problem *P, int count, const float *y_in, float *y_out) {
+    DualLongArgs A;
+    A.count = count;
+    A.m1 = static_cast<int>(P->m1);
+    A.order = P->dual_order;
+    A.rp = P->rp;
+    A.rowc0 = P->rowc0;
+    A.ci = P->ci;
+    A.val = P->val;
+    A.val16 = P->use16 ? P->val16 : nullptr;
+    A.rowunit = P->rowunit;
+    A.omega = P->omega;
+    A.rt = P->rt;
+    A.xbar = P->xbar;
+    A.y_in = y_in;
+    A.y_out = y_out;
+    A.wy = P->wy;
+    return A;
+}
+static PrimalLongArgs primal_long_args(gfors_problem *P, const float *x_in, float *x_out, float *xbar) {
+    PrimalLongArgs A;
+    A.count = P->heavy_cols;
+    A.order = P->primal_order;
+    A.rpT = P->rpT;
+    A.ciT = P->ciT;
+    A.valT = P->valT;
+    A.wy = P->wy;
+    A.x_in = x_in;
+    A.x_out = x_out;
+    A.xbar = xbar;
+    A.ct = P->ct;
+    A.rho = P->di.rho;
+    return A;
+}
+
 static void launch_dual_cfg(gfors_problem *P, int lpr, int slices, int sell, const float *y_in,
                             float *y_out) {
     hipStream_t s = P->stream;
@@ -1483,11 +1518,8 @@ static void launch_dual_cfg(gfors_problem *P, int lpr, int slices, int sell, con
                           P->d_inst_nvar, P->xbar, P->omega, P->rt, P->di.tau2, P->row_inst, y_in, y_out, P->wy);
     } else if (P->cfg.bits_dual == 5 && P->lgt_dd > 0 && !sell && slices == 1) {
         // heavy rows a workgroup each, the light range a lane per row with signed indices
-        launch_dual_long(s, P->unitK, false, P->heavy_rows, m1, P->dual_order, P->rp, P->rowc0, P->ci, P->val,
-                         P->use16 ? P->val16 : nullptr, P->rowunit, P->omega, P->rt, P->xbar, y_in, y_out, P->wy, tau2,
-                         P->di.tau2, P->row_inst);
-        launch_dual_light(s, P->lgt_dd, P->lgt_d0, P->lgt_dn, m1, P->lgt_d, P->omega, P->rt, P->xbar, y_in, y_out,
-                          P->wy, tau2);
+        launch_dual_light(s, P->unitK, P->lgt_dd, dual_long_args(P, P->heavy_rows, y_in, y_out), P->lgt_d0, P->lgt_dn,
+                          P->lgt_d, tau2);
     } else if (sell && P->cfg.bits_dual >= 2) {
         const int nc = P->cfg.bits_dual == 3 ? 4 : 2;
         need_bx();
@@ -1528,10 +1560,7 @@ static void launch_dual_cfg(gfors_problem *P, int lpr, int slices, int sell, con
         // a workgroup per row for all rows (256) or for the heavy rows only,
         // the others with lpr - 256 lanes each
         const bool all = lpr == kLprBlock;
-        launch_dual_long(s, P->unitK, batched, all ? m : P->heavy_rows, m1, P->dual_order, P->rp,
-                         P->rowc0, P->ci, P->val, P->use16 ? P->val16 : nullptr, P->rowunit, P->omega, P->rt,
-                         P->xbar,
-                         y_in, y_out, P->wy, tau2,
+        launch_dual_long(s, P->unitK, batched, dual_long_args(P, all ? m : P->heavy_rows, y_in, y_out), tau2,
                          P->di.tau2, P->row_inst);
         if (!all)
             launch_dual(s, lpr - kLprBlock, P->unitK, batched, m, m1, P->rp, P->ci, P->val,
@@ -1562,16 +1591,24 @@ static void launch_primal_cfg(gfors_problem *P, int lpr, int slices, int sell, c
     if ((P->cfg.bits_primal == 6 || P->cfg.bits_primal == 7) && P->lgt_pd > 0 && !sell && slices == 1) {
         // heavy variables a workgroup each (6) or in shift groups (7), the
         // light range a lane per variable with signed indices
-        if (P->cfg.bits_primal == 7)
-            launch_primal_hgroup(s, P->unitK, P->hg_nslot, P->hg_ngroup, P->hg_ord, P->hg_chg, P->hg_chb, P->hg_che,
-                                 P->hg_var0, P->hg_w, P->hg_e0, P->hg_c0, P->ciT, P->valT, P->wy, P->hg_part,
-                                 x_in, x_out, xbar, P->ct, tau1, P->di.rho);
-        else
-            launch_primal_long(s, P->unitK, false, P->heavy_cols, P->primal_order, P->rpT, P->ciT, P->valT,
-                               P->wy, x_in, x_out, xbar, P->ct, tau1, P->di.tau1, P->di.rho, P->var_inst);
         uint64_t *xb_out = (P->lgt_p0 == 0 && P->lgt_pn == P->n && P->heavy_cols == 0) ? xbits : nullptr;
-        launch_primal_light(s, P->lgt_pd, P->lgt_p0, P->lgt_pn, P->lgt_p, P->wy, x_in, x_out, xbar, P->ct, tau1,
-                            P->di.rho, ctr, xb_out);
+        HgroupArgs G;
+        G.nslot = P->hg_nslot;
+        G.ngroup = P->hg_ngroup;
+        G.ord = P->hg_ord;
+        G.ch_g = P->hg_chg;
+        G.ch_b = P->hg_chb;
+        G.ch_e = P->hg_che;
+        G.var0 = P->hg_var0;
+        G.w = P->hg_w;
+        G.e0 = P->hg_e0;
+        G.c0 = P->hg_c0;
+        G.ciT = P->ciT;
+        G.valT = P->valT;
+        G.wy = P->wy;
+        G.part = P->hg_part;
+        launch_primal_light(s, P->unitK, P->lgt_pd, primal_long_args(P, x_in, x_out, xbar),
+                            P->cfg.bits_primal == 7 ? &G : nullptr, P->lgt_p0, P->lgt_pn, P->lgt_p, tau1, ctr, xb_out);
         xbar_bits = xb_out != nullptr;
     } else if (P->cfg.bits_primal == 5 && P->dense_block && !sell && slices == 1) {
         launch_primal_block(s, P->blk, P->rp, P->val, P->use16 ? P->val16 : nullptr, P->d_inst_var0, P->d_inst_nvar,
@@ -1607,9 +1644,7 @@ static void launch_primal_cfg(gfors_problem *P, int lpr, int slices, int sell, c
         xbar_bits = xbits != nullptr;
     } else if (lpr > kLprBlock) {
         // heavy variables a workgroup each, the others lpr - 256 lanes (no Q)
-        launch_primal_long(s, P->unitK, batched, P->heavy_cols, P->primal_order, P->rpT, P->ciT,
-                           P->valT, P->wy, x_in, x_out, xbar, P->ct, tau1, P->di.tau1, P->di.rho,
-                           P->var_inst);
+        launch_primal_long(s, P->unitK, batched, primal_long_args(P, x_in, x_out, xbar), tau1, P->di.tau1, P->var_inst);
         launch_primal(s, lpr - kLprBlock, kmode, false, batched, static_cast<int>(P->n), P->rpT,
                       P->dense_cols ? P->colT0 : nullptr, P->ciT, P->valT, P->wy, P->rpQ, P->ciQ, P->valQ,
                       x_in, x_out, xbar, P->ct, tau1, 0.f, P->di.tau1, P->di.two_so, P->di.rho,

@@ -209,10 +209,35 @@ void launch_primal(hipStream_t s, int lpr, int kmode, bool hasq, bool batched, i
                    float *x_out, float *xbar, const float *ct, float tau1, float two_so,
                    const float *tau1_inst, const float *two_so_inst, const double *rho,
                    const int *var_inst, DevCounters *ctr, int skip_len);
-void launch_primal_long(hipStream_t s, bool unit, bool batched, int count, const int *order,
-                        const int *rpT, const int *ciT, const int *valT, const float *wy,
-                        const float *x_in, float *x_out, float *xbar, const float *ct, float tau1,
-                        const float *tau1_inst, const double *rho, const int *var_inst);
+// Heavy rows / variables, a workgroup each, taken in `order` (longest first).
+// rowc0: first column of a dense row, else -1; val16: the coefficients as int16
+// when all fit (else null); rowunit: rows whose coefficients are all 1 (or null).
+struct DualLongArgs {
+    int count = 0, m1 = 0;
+    const int *order = nullptr, *rp = nullptr, *rowc0 = nullptr, *ci = nullptr, *val = nullptr;
+    const int16_t *val16 = nullptr;
+    const uint8_t *rowunit = nullptr;
+    const float *omega = nullptr, *rt = nullptr, *xbar = nullptr, *y_in = nullptr;
+    float *y_out = nullptr, *wy = nullptr;
+};
+struct PrimalLongArgs {
+    int count = 0;
+    const int *order = nullptr, *rpT = nullptr, *ciT = nullptr, *valT = nullptr;
+    const float *wy = nullptr, *x_in = nullptr;
+    float *x_out = nullptr, *xbar = nullptr;
+    const float *ct = nullptr;
+    const double *rho = nullptr;
+};
+// Heavy variables in shift groups (k_primal_light): launch slots, chunks, groups.
+struct HgroupArgs {
+    int nslot = 0, ngroup = 0;
+    const int *ord = nullptr, *ch_g = nullptr, *ch_b = nullptr, *ch_e = nullptr;
+    const int *var0 = nullptr, *w = nullptr, *e0 = nullptr, *c0 = nullptr, *ciT = nullptr, *valT = nullptr;
+    const float *wy = nullptr;
+    float *part = nullptr;
+};
+void launch_primal_long(hipStream_t s, bool unit, bool batched, const PrimalLongArgs &A, float tau1,
+                        const float *tau1_inst, const int *var_inst);
 
 void launch_spmv_part(hipStream_t s, int lpr, bool unit, int nrows, int P, const int *rpP,
                       const int *ci, const int *val, const float *v, float *part);
@@ -233,11 +258,8 @@ void launch_sell(hipStream_t s, const SellView &sv, int mode, bool unit, bool ba
                  const int *var_inst, DevCounters *ctr);
 
 void launch_nzbits(hipStream_t s, const float *v, int64_t n, int64_t nwords64, uint64_t *bits);
-void launch_dual_long(hipStream_t s, bool unit, bool batched, int m, int m1, const int *order,
-                      const int *rp, const int *rowc0, const int *ci, const int *val,
-                      const int16_t *val16, const uint8_t *rowunit, const float *omega,
-                      const float *rt, const float *xbar, const float *y_in, float *y_out,
-                      float *wy, float tau2, const float *tau2_inst, const int *row_inst);
+void launch_dual_long(hipStream_t s, bool unit, bool batched, const DualLongArgs &A, float tau2,
+                      const float *tau2_inst, const int *row_inst);
 void launch_sell_bits(hipStream_t s, const SellView &sv, int mode, bool unit, bool batched,
                       int ncols, const float *v, const uint32_t *bits, float *part, int m1,
                       const float *omega, const float *rt, const float *y_in, float *y_out,
@@ -297,19 +319,11 @@ int primal_lds_slice(size_t lds_limit);
 // Light rows / variables [i0, i0 + L) of D <= 8 entries each, indices entry-major
 // with the coefficient's sign (|a| = 1) in bit 31; one instance, no Q.  xbits:
 // nonzero bitmap of xbar (only when the range is every variable), or null.
-void launch_dual_light(hipStream_t s, int D, int i0, int L, int m1, const int *sidx, const float *omega,
-                       const float *rt, const float *xbar, const float *y_in, float *y_out, float *wy,
+// The heavy items of A (or of the shift groups G) ride in the same launch.
+void launch_dual_light(hipStream_t s, bool unit, int D, const DualLongArgs &A, int i0, int L, const int *sidx,
                        float tau2);
-void launch_primal_light(hipStream_t s, int D, int i0, int L, const int *sidx, const float *wy,
-                         const float *x_in, float *x_out, float *xbar, const float *ct, float tau1,
-                         const double *rho, DevCounters *ctr, uint64_t *xbits);
-// Heavy variables in groups of <= kHgWidth whose rows are unit shifts of the first
-// one's (one instance, no Q): chunk partials, then the per-variable update.
-void launch_primal_hgroup(hipStream_t s, bool unit, int nslot, int ngroup, const int *ord, const int *ch_g,
-                          const int *ch_b, const int *ch_e, const int *hg_var0, const int *hg_w, const int *hg_e0,
-                          const int *hg_c0, const int *ciT, const int *valT, const float *wy, float *part,
-                          const float *x_in, float *x_out, float *xbar, const float *ct, float tau1,
-                          const double *rho);
+void launch_primal_light(hipStream_t s, bool unit, int D, const PrimalLongArgs &A, const HgroupArgs *G, int i0, int L,
+                         const int *sidx, float tau1, DevCounters *ctr, uint64_t *xbits);
 bool launch_primal_lds(hipStream_t s, int n, int m, int deg, int SL, const int *ell, const float *wy,
                        const float *x_in, float *x_out, float *xbar, const float *ct, float tau1,
                        const double *rho, DevCounters *ctr, uint64_t *xbits);

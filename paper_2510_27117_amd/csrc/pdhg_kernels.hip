@@ -115,54 +115,52 @@ __device__ __forceinline__ float long_row_sum(int e0, int e1, int c0, const int 
 }
 
 template <bool UNIT, bool BATCH>
-__global__ void __launch_bounds__(256)
-k_dual_long(int count, int m1, const int *__restrict__ order, const int *__restrict__ rp,
-            const int *__restrict__ rowc0, const int *__restrict__ ci, const int *__restrict__ val,
-            const int16_t *__restrict__ val16, const uint8_t *__restrict__ rowunit,
-            const float *__restrict__ omega, const float *__restrict__ rt,
-            const float *__restrict__ xbar, const float *__restrict__ y_in,
-            float *__restrict__ y_out, float *__restrict__ wy, float tau2,
-            const float *__restrict__ tau2_inst, const int *__restrict__ row_inst) {
+__device__ __forceinline__ void dual_long_item(int block, const DualLongArgs &A, float tau2,
+                                               const float *__restrict__ tau2_inst, const int *__restrict__ row_inst) {
     __shared__ float ws[4];
-    const int slot = xcd_grouped_slot(blockIdx.x);
-    if (slot >= count) return;                          // uniform per workgroup
-    const int row = order[slot];
-    const int e0 = rp[row], e1 = rp[row + 1];
-    const int c0 = rowc0[row];                          // first column of a dense row, else -1
+    const int slot = xcd_grouped_slot(block);
+    if (slot >= A.count) return;                        // uniform per workgroup
+    const int row = A.order[slot];
+    const int e0 = A.rp[row], e1 = A.rp[row + 1];
+    const int c0 = A.rowc0[row];                        // first column of a dense row, else -1
     // val16: the same coefficients as int16 (all fit), half the stream
     float s;
-    if (!UNIT && rowunit && rowunit[row])   // every coefficient of the row is 1: no coefficient stream
-        s = c0 >= 0 ? long_row_sum<true, true>(e0, e1, c0, ci, val, xbar)
-                    : long_row_sum<true, false>(e0, e1, c0, ci, val, xbar);
-    else if (!UNIT && val16)
-        s = c0 >= 0 ? long_row_sum<UNIT, true>(e0, e1, c0, ci, val16, xbar)
-                    : long_row_sum<UNIT, false>(e0, e1, c0, ci, val16, xbar);
+    if (!UNIT && A.rowunit && A.rowunit[row])   // every coefficient of the row is 1: no coefficient stream
+        s = c0 >= 0 ? long_row_sum<true, true>(e0, e1, c0, A.ci, A.val, A.xbar)
+                    : long_row_sum<true, false>(e0, e1, c0, A.ci, A.val, A.xbar);
+    else if (!UNIT && A.val16)
+        s = c0 >= 0 ? long_row_sum<UNIT, true>(e0, e1, c0, A.ci, A.val16, A.xbar)
+                    : long_row_sum<UNIT, false>(e0, e1, c0, A.ci, A.val16, A.xbar);
     else
-        s = c0 >= 0 ? long_row_sum<UNIT, true>(e0, e1, c0, ci, val, xbar)
-                    : long_row_sum<UNIT, false>(e0, e1, c0, ci, val, xbar);
+        s = c0 >= 0 ? long_row_sum<UNIT, true>(e0, e1, c0, A.ci, A.val, A.xbar)
+                    : long_row_sum<UNIT, false>(e0, e1, c0, A.ci, A.val, A.xbar);
     s = group_sum<64>(s);
     if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = s;
     __syncthreads();
     if (threadIdx.x == 0) {
         const float tot = ((ws[0] + ws[1]) + ws[2]) + ws[3];
-        const float om = omega[row];
-        const float t = rt[row] - om * tot;
+        const float om = A.omega[row];
+        const float t = A.rt[row] - om * tot;
         const float ta = BATCH ? tau2_inst[row_inst[row]] : tau2;
-        float y = y_in[row] + ta * t;
-        if (row < m1) y = fmaxf(y, 0.f);
-        y_out[row] = y;
-        wy[row] = om * y;
+        float y = A.y_in[row] + ta * t;
+        if (row < A.m1) y = fmaxf(y, 0.f);
+        A.y_out[row] = y;
+        A.wy[row] = om * y;
     }
 }
 
-void launch_dual_long(hipStream_t s, bool unit, bool batched, int m, int m1, const int *order,
-                      const int *rp, const int *rowc0, const int *ci, const int *val, const int16_t *val16,
-                      const uint8_t *rowunit, const float *omega,
-                      const float *rt, const float *xbar, const float *y_in, float *y_out,
-                      float *wy, float tau2, const float *tau2_inst, const int *row_inst) {
-    if (m <= 0) return;
-    const int grid = ((m + 127) / 128) * 128;
-#define GF_DL(U, B) k_dual_long<U, B><<<grid, 256, 0, s>>>(m, m1, order, rp, rowc0, ci, val, val16, rowunit, omega, rt, xbar, y_in, y_out, wy, tau2, tau2_inst, row_inst)
+template <bool UNIT, bool BATCH>
+__global__ void __launch_bounds__(256)
+k_dual_long(DualLongArgs A, float tau2, const float *__restrict__ tau2_inst, const int *__restrict__ row_inst) {
+    dual_long_item<UNIT, BATCH>(blockIdx.x, A, tau2, tau2_inst, row_inst);
+}
+
+static int long_grid(int count) { return ((count + 127) / 128) * 128; }   // whole groups of xcd_grouped_slot
+
+void launch_dual_long(hipStream_t s, bool unit, bool batched, const DualLongArgs &A, float tau2,
+                      const float *tau2_inst, const int *row_inst) {
+    if (A.count <= 0) return;
+#define GF_DL(U, B) k_dual_long<U, B><<<long_grid(A.count), 256, 0, s>>>(A, tau2, tau2_inst, row_inst)
     if (unit) { if (batched) GF_DL(true, true); else GF_DL(true, false); }
     else { if (batched) GF_DL(false, true); else GF_DL(false, false); }
 #undef GF_DL
@@ -172,18 +170,13 @@ void launch_dual_long(hipStream_t s, bool unit, bool batched, int m, int m1, con
 // taken from `order` (most rows first), same summation structure as
 // k_dual_long.  The iteration counter is advanced by the companion kernel.
 template <bool UNIT, bool BATCH>
-__global__ void __launch_bounds__(256)
-k_primal_long(int count, const int *__restrict__ order, const int *__restrict__ rpT,
-              const int *__restrict__ ciT, const int *__restrict__ valT,
-              const float *__restrict__ wy, const float *__restrict__ x_in,
-              float *__restrict__ x_out, float *__restrict__ xbar, const float *__restrict__ ct,
-              float tau1, const float *__restrict__ tau1_inst, const double *__restrict__ rho,
-              const int *__restrict__ var_inst) {
+__device__ __forceinline__ void primal_long_item(int block, const PrimalLongArgs &A, float tau1,
+                                                 const float *__restrict__ tau1_inst, const int *__restrict__ var_inst) {
     __shared__ float ws[4];
-    const int slot = xcd_grouped_slot(blockIdx.x);
-    if (slot >= count) return;                          // uniform per workgroup
-    const int i = order[slot];
-    const int e0 = rpT[i], e1 = rpT[i + 1];
+    const int slot = xcd_grouped_slot(block);
+    if (slot >= A.count) return;                        // uniform per workgroup
+    const int i = A.order[slot];
+    const int e0 = A.rpT[i], e1 = A.rpT[i + 1];
     float s = 0.f;
     for (int eb = e0 + static_cast<int>(threadIdx.x); eb < e1; eb += kLongUnroll * 256) {
         float w[kLongUnroll];
@@ -191,10 +184,10 @@ k_primal_long(int count, const int *__restrict__ order, const int *__restrict__ 
 #pragma unroll
         for (int u = 0; u < kLongUnroll; ++u) {
             const int e = min(eb + 256 * u, e1 - 1);
-            const float v = wy[ciT[e]];
+            const float v = A.wy[A.ciT[e]];
             const bool in = eb + 256 * u < e1;
             w[u] = in ? v : 0.f;
-            a[u] = UNIT ? 1 : (in ? valT[e] : 0);
+            a[u] = UNIT ? 1 : (in ? A.valT[e] : 0);
         }
 #pragma unroll
         for (int u = 0; u < kLongUnroll; ++u) {
@@ -208,23 +201,26 @@ k_primal_long(int count, const int *__restrict__ order, const int *__restrict__ 
     if (threadIdx.x == 0) {
         const float tot = ((ws[0] + ws[1]) + ws[2]) + ws[3];
         const int t = BATCH ? var_inst[i] : 0;
-        const float xi = x_in[i];
-        const float rh = static_cast<float>(rho[t]);
+        const float xi = A.x_in[i];
+        const float rh = static_cast<float>(A.rho[t]);
         const float ta = BATCH ? tau1_inst[t] : tau1;
-        const float g = ct[i] + rh - tot - 2.f * rh * xi;
+        const float g = A.ct[i] + rh - tot - 2.f * rh * xi;
         const float xn = fminf(fmaxf(xi - ta * g, 0.f), 1.f);
-        x_out[i] = xn;
-        xbar[i] = 2.f * xn - xi;
+        A.x_out[i] = xn;
+        A.xbar[i] = 2.f * xn - xi;
     }
 }
 
-void launch_primal_long(hipStream_t s, bool unit, bool batched, int count, const int *order,
-                        const int *rpT, const int *ciT, const int *valT, const float *wy,
-                        const float *x_in, float *x_out, float *xbar, const float *ct, float tau1,
-                        const float *tau1_inst, const double *rho, const int *var_inst) {
-    if (count <= 0) return;
-    const int grid = ((count + 127) / 128) * 128;
-#define GF_PL(U, B) k_primal_long<U, B><<<grid, 256, 0, s>>>(count, order, rpT, ciT, valT, wy, x_in, x_out, xbar, ct, tau1, tau1_inst, rho, var_inst)
+template <bool UNIT, bool BATCH>
+__global__ void __launch_bounds__(256)
+k_primal_long(PrimalLongArgs A, float tau1, const float *__restrict__ tau1_inst, const int *__restrict__ var_inst) {
+    primal_long_item<UNIT, BATCH>(blockIdx.x, A, tau1, tau1_inst, var_inst);
+}
+
+void launch_primal_long(hipStream_t s, bool unit, bool batched, const PrimalLongArgs &A, float tau1,
+                        const float *tau1_inst, const int *var_inst) {
+    if (A.count <= 0) return;
+#define GF_PL(U, B) k_primal_long<U, B><<<long_grid(A.count), 256, 0, s>>>(A, tau1, tau1_inst, var_inst)
     if (unit) { if (batched) GF_PL(true, true); else GF_PL(true, false); }
     else { if (batched) GF_PL(false, true); else GF_PL(false, false); }
 #undef GF_PL
@@ -1142,16 +1138,15 @@ bool launch_primal_lds(hipStream_t s, int n, int m, int deg, int SL, const int *
 // workgroup-per-item kernels.
 // ---------------------------------------------------------------------------
 template <int D>
-__global__ void __launch_bounds__(256)
-k_dual_light(int i0, int L, int m1, const int *__restrict__ sidx, const float *__restrict__ omega,
-             const float *__restrict__ rt, const float *__restrict__ xbar, const float *__restrict__ y_in,
-             float *__restrict__ y_out, float *__restrict__ wy, float tau2) {
-    const int k = blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void dual_light_item(int k, int i0, int L, int m1, const int *__restrict__ sidx,
+                                                const float *__restrict__ omega, const float *__restrict__ rt,
+                                                const float *__restrict__ xbar, const float *__restrict__ y_in,
+                                                float *__restrict__ y_out, float *__restrict__ wy, float tau2) {
     if (k >= L) return;
     int c[D];
 #pragma unroll
     for (int u = 0; u < D; ++u) c[u] = sidx[static_cast<int64_t>(u) * L + k];
-    if (c[0] == kLightHole) return;   // a heavy row: its workgroup kernel updates it
+    if (c[0] == kLightHole) return;   // a heavy row: its workgroup updates it
     float g[D];
 #pragma unroll
     for (int u = 0; u < D; ++u) g[u] = xbar[c[u] & 0x7fffffff];
@@ -1160,22 +1155,34 @@ k_dual_light(int i0, int L, int m1, const int *__restrict__ sidx, const float *_
     for (int u = 0; u < D; ++u) sum += c[u] < 0 ? -g[u] : g[u];
     const int row = i0 + k;
     const float om = omega[row];
-    const float t = rt[row] - om * sum;
-    float y = y_in[row] + tau2 * t;
-    if (row < m1) y = fmaxf(y, 0.f);
+    const float y = dual_update(sum, om, rt[row], tau2, y_in[row], row < m1);
     y_out[row] = y;
     wy[row] = om * y;
+}
+
+// The whole dual step: workgroups [0, hblocks) take a heavy row each, the others
+// 256 light rows.  One launch, so that the heavy rows' latency hides behind the
+// light rows' streams (400 x 4,000 facility location: 5.0 + 9.4 us apart,
+// 11.7 together).
+template <int D, bool UNIT>
+__global__ void __launch_bounds__(256)
+k_dual_light(int hblocks, DualLongArgs A, int i0, int L, const int *__restrict__ sidx, float tau2) {
+    if (static_cast<int>(blockIdx.x) < hblocks)
+        dual_long_item<UNIT, false>(blockIdx.x, A, tau2, nullptr, nullptr);
+    else
+        dual_light_item<D>((blockIdx.x - hblocks) * 256 + threadIdx.x, i0, L, A.m1, sidx, A.omega, A.rt, A.xbar, A.y_in,
+                           A.y_out, A.wy, tau2);
 }
 
 // xbits (optional, only when the light range is every variable): the nonzero
 // bitmap of the new xbar for the zero-skipping dual, one word per wavefront.
 template <int D>
-__global__ void __launch_bounds__(256)
-k_primal_light(int i0, int L, const int *__restrict__ sidx, const float *__restrict__ wy,
-               const float *__restrict__ x_in, float *__restrict__ x_out, float *__restrict__ xbar,
-               const float *__restrict__ ct, float tau1, const double *__restrict__ rho,
-               DevCounters *__restrict__ ctr, uint64_t *__restrict__ xbits) {
-    const int k = blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void primal_light_item(int k, int i0, int L, const int *__restrict__ sidx,
+                                                  const float *__restrict__ wy, const float *__restrict__ x_in,
+                                                  float *__restrict__ x_out, float *__restrict__ xbar,
+                                                  const float *__restrict__ ct, float tau1,
+                                                  const double *__restrict__ rho, DevCounters *__restrict__ ctr,
+                                                  uint64_t *__restrict__ xbits) {
     if (k == 0) ctr->k += 1;
     float xb = 0.f;
     const bool live = k < L && sidx[k] != kLightHole;   // holes: heavy variables, updated elsewhere
@@ -1191,11 +1198,7 @@ k_primal_light(int i0, int L, const int *__restrict__ sidx, const float *__restr
         float sum = 0.f;
 #pragma unroll
         for (int u = 0; u < D; ++u) sum += c[u] < 0 ? -g[u] : g[u];
-        const float rh = static_cast<float>(rho[0]);
-        float gr = cti + rh;
-        gr -= sum;
-        gr -= 2.f * rh * xi;
-        const float xn = fminf(fmaxf(xi - tau1 * gr, 0.f), 1.f);
+        const float xn = primal_update(sum, cti, static_cast<float>(rho[0]), tau1, xi);
         x_out[i] = xn;
         xb = 2.f * xn - xi;
         xbar[i] = xb;
@@ -1221,32 +1224,28 @@ k_primal_light(int i0, int L, const int *__restrict__ sidx, const float *__restr
 // apart, so that both run on one XCD (workgroup b runs on XCD b % 8) at about
 // the same time and fetch each line into one L2 once.
 template <bool UNIT>
-__global__ void __launch_bounds__(256)
-k_primal_hgroup(const int *__restrict__ ord, const int *__restrict__ ch_g, const int *__restrict__ ch_b,
-                const int *__restrict__ ch_e, const int *__restrict__ hg_w, const int *__restrict__ hg_e0,
-                const int *__restrict__ ciT, const int *__restrict__ valT, const float *__restrict__ wy,
-                float *__restrict__ part) {
+__device__ __forceinline__ void hgroup_item(int block, const HgroupArgs &A) {
     constexpr int NS = 256 / kHgWidth;   // entry slots
     __shared__ float red[NS][kHgWidth + 1];
-    const int c = ord[blockIdx.x];
+    const int c = A.ord[block];
     if (c < 0) return;                   // padding slot (whole workgroup, before any barrier)
-    const int g = ch_g[c];
+    const int g = A.ch_g[c];
     const int d = threadIdx.x % kHgWidth, q = threadIdx.x / kHgWidth;
-    const int w = hg_w[g], base = hg_e0[g];
-    const int b1 = ch_e[c];
+    const int w = A.w[g], base = A.e0[g];
+    const int b1 = A.ch_e[c];
     float acc = 0.f;
-    for (int e = ch_b[c] + q; e < b1; e += NS * kLongUnroll) {
+    for (int e = A.ch_b[c] + q; e < b1; e += NS * kLongUnroll) {
         int r[kLongUnroll], a[kLongUnroll];
 #pragma unroll
         for (int u = 0; u < kLongUnroll; ++u) {
             const int ee = e + NS * u;
             const bool in = ee < b1;
-            r[u] = in ? ciT[base + ee] : 0;
-            a[u] = UNIT ? (in ? 1 : 0) : (in ? valT[base + ee] : 0);
+            r[u] = in ? A.ciT[base + ee] : 0;
+            a[u] = UNIT ? (in ? 1 : 0) : (in ? A.valT[base + ee] : 0);
         }
         float v[kLongUnroll];
 #pragma unroll
-        for (int u = 0; u < kLongUnroll; ++u) v[u] = (a[u] != 0 && d < w) ? wy[r[u] + d] : 0.f;
+        for (int u = 0; u < kLongUnroll; ++u) v[u] = (a[u] != 0 && d < w) ? A.wy[r[u] + d] : 0.f;
 #pragma unroll
         for (int u = 0; u < kLongUnroll; ++u) acc = fmaf(static_cast<float>(a[u]), v[u], acc);
     }
@@ -1256,7 +1255,25 @@ k_primal_hgroup(const int *__restrict__ ord, const int *__restrict__ ch_g, const
         float sum = 0.f;
 #pragma unroll
         for (int k = 0; k < NS; ++k) sum += red[k][threadIdx.x];
-        part[static_cast<int64_t>(c) * kHgWidth + threadIdx.x] = sum;
+        A.part[static_cast<int64_t>(c) * kHgWidth + threadIdx.x] = sum;
+    }
+}
+
+// The primal step of the light variables with, in the first hblocks workgroups,
+// the heavy ones: HV 0 a workgroup per variable, 1 a chunk of a shift group
+// (k_primal_hgroup_fin then ends those).  One launch for the same reason as in
+// k_dual_light (400 x 4,000 facility location: 13.7 + 9.1 us apart, 16.6
+// together).
+template <int D, bool UNIT, int HV>
+__global__ void __launch_bounds__(256)
+k_primal_light(int hblocks, PrimalLongArgs A, HgroupArgs G, int i0, int L, const int *__restrict__ sidx, float tau1,
+               DevCounters *__restrict__ ctr, uint64_t *__restrict__ xbits) {
+    if (static_cast<int>(blockIdx.x) < hblocks) {
+        if (HV == 0) primal_long_item<UNIT, false>(blockIdx.x, A, tau1, nullptr, nullptr);
+        else hgroup_item<UNIT>(blockIdx.x, G);
+    } else {
+        primal_light_item<D>((blockIdx.x - hblocks) * 256 + threadIdx.x, i0, L, sidx, A.wy, A.x_in, A.x_out, A.xbar,
+                             A.ct, tau1, A.rho, ctr, xbits);
     }
 }
 
@@ -1289,42 +1306,42 @@ k_primal_hgroup_fin(int ngroup, const int *__restrict__ hg_var0, const int *__re
     xbar[i] = 2.f * xn - xi;
 }
 
-void launch_primal_hgroup(hipStream_t s, bool unit, int nslot, int ngroup, const int *ord, const int *ch_g,
-                          const int *ch_b, const int *ch_e, const int *hg_var0, const int *hg_w, const int *hg_e0,
-                          const int *hg_c0, const int *ciT, const int *valT, const float *wy, float *part,
-                          const float *x_in, float *x_out, float *xbar, const float *ct, float tau1,
-                          const double *rho) {
-    if (nslot <= 0 || ngroup <= 0) return;
-    if (unit) k_primal_hgroup<true><<<nslot, 256, 0, s>>>(ord, ch_g, ch_b, ch_e, hg_w, hg_e0, ciT, valT, wy, part);
-    else k_primal_hgroup<false><<<nslot, 256, 0, s>>>(ord, ch_g, ch_b, ch_e, hg_w, hg_e0, ciT, valT, wy, part);
-    k_primal_hgroup_fin<<<(ngroup * kHgWidth + 255) / 256, 256, 0, s>>>(ngroup, hg_var0, hg_w, hg_c0, part, x_in, x_out,
-                                                                   xbar, ct, tau1, rho);
-}
-
-void launch_dual_light(hipStream_t s, int D, int i0, int L, int m1, const int *sidx, const float *omega,
-                       const float *rt, const float *xbar, const float *y_in, float *y_out, float *wy,
+void launch_dual_light(hipStream_t s, bool unit, int D, const DualLongArgs &A, int i0, int L, const int *sidx,
                        float tau2) {
-    const int blocks = (L + 255) / 256;
+    const int hb = A.count > 0 ? long_grid(A.count) : 0, blocks = hb + (L + 255) / 256;
     if (blocks == 0) return;
+#define GF_DL(DD)                                                                                           \
+    case DD:                                                                                                \
+        if (unit) k_dual_light<DD, true><<<blocks, 256, 0, s>>>(hb, A, i0, L, sidx, tau2);                  \
+        else k_dual_light<DD, false><<<blocks, 256, 0, s>>>(hb, A, i0, L, sidx, tau2);                      \
+        break;
     switch (D) {
-#define GF_DL(DD) case DD: k_dual_light<DD><<<blocks, 256, 0, s>>>(i0, L, m1, sidx, omega, rt, xbar, y_in, y_out, wy, tau2); break;
         GF_DL(1) GF_DL(2) GF_DL(3) GF_DL(4) GF_DL(5) GF_DL(6) GF_DL(7) GF_DL(8)
-#undef GF_DL
         default: break;
     }
+#undef GF_DL
 }
 
-void launch_primal_light(hipStream_t s, int D, int i0, int L, const int *sidx, const float *wy,
-                         const float *x_in, float *x_out, float *xbar, const float *ct, float tau1,
-                         const double *rho, DevCounters *ctr, uint64_t *xbits) {
-    const int blocks = (L + 255) / 256;
+void launch_primal_light(hipStream_t s, bool unit, int D, const PrimalLongArgs &A, const HgroupArgs *G, int i0, int L,
+                         const int *sidx, float tau1, DevCounters *ctr, uint64_t *xbits) {
+    const int hb = G ? G->nslot : (A.count > 0 ? long_grid(A.count) : 0), blocks = hb + (L + 255) / 256;
     if (blocks == 0) return;
+    const HgroupArgs g = G ? *G : HgroupArgs();
+#define GF_PLK(DD, U, HV) k_primal_light<DD, U, HV><<<blocks, 256, 0, s>>>(hb, A, g, i0, L, sidx, tau1, ctr, xbits)
+#define GF_PLG(DD)                                                                     \
+    case DD:                                                                           \
+        if (unit) { if (G) GF_PLK(DD, true, 1); else GF_PLK(DD, true, 0); }            \
+        else { if (G) GF_PLK(DD, false, 1); else GF_PLK(DD, false, 0); }               \
+        break;
     switch (D) {
-#define GF_PLG(DD) case DD: k_primal_light<DD><<<blocks, 256, 0, s>>>(i0, L, sidx, wy, x_in, x_out, xbar, ct, tau1, rho, ctr, xbits); break;
         GF_PLG(1) GF_PLG(2) GF_PLG(3) GF_PLG(4) GF_PLG(5) GF_PLG(6) GF_PLG(7) GF_PLG(8)
-#undef GF_PLG
         default: break;
     }
+#undef GF_PLG
+#undef GF_PLK
+    if (G)
+        k_primal_hgroup_fin<<<(g.ngroup * kHgWidth + 255) / 256, 256, 0, s>>>(g.ngroup, g.var0, g.w, g.c0, g.part, A.x_in,
+                                                                              A.x_out, A.xbar, A.ct, tau1, A.rho);
 }
 
 // ---------------------------------------------------------------------------
