@@ -134,6 +134,39 @@ __device__ __forceinline__ float wave_sum4(float a, float b, float c, float d) {
     v = xor_sum<2>(v);
     return xor_sum<1>(v);
 }
+// The same of a double, its two halves moved as above.
+template <int D>
+__device__ __forceinline__ double xor_sum(double v) {
+    const int lo = __double2loint(v), hi = __double2hiint(v);
+    if constexpr (D >= 16) {
+        auto swap = [](int w) {
+            if constexpr (D == 32) return __builtin_amdgcn_permlane32_swap(w, w, false, false);
+            else return __builtin_amdgcn_permlane16_swap(w, w, false, false);
+        };
+        const auto l = swap(lo), h = swap(hi);
+        return __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+    } else {
+        auto partner = [](int w) {
+            const float f = __int_as_float(w);
+            if constexpr (D == 8) return __float_as_int(dpp_move<0x128>(f, f));
+            else if constexpr (D == 4) return __float_as_int(dpp_move<0x114, 0xa>(dpp_move<0x104, 0x5>(f, f), f));
+            else if constexpr (D == 2) return __float_as_int(dpp_move<0x4e>(f, f));
+            else return __float_as_int(dpp_move<0xb1>(f, f));
+        };
+        return v + __hiloint2double(partner(hi), partner(lo));
+    }
+}
+// Sum over groups of L lanes (a power of two <= 64), widest distance first.
+template <typename T>
+__device__ __forceinline__ T lane_group_sum(T v, int L) {
+    if (L >= 64) v = xor_sum<32>(v);
+    if (L >= 32) v = xor_sum<16>(v);
+    if (L >= 16) v = xor_sum<8>(v);
+    if (L >= 8) v = xor_sum<4>(v);
+    if (L >= 4) v = xor_sum<2>(v);
+    if (L >= 2) v = xor_sum<1>(v);
+    return v;
+}
 // Which of wave_sum4's operands (0..3) a lane's quarter holds.
 __device__ __forceinline__ int wave_sum4_of(int lane) {
     const int q = lane >> 4;
@@ -422,28 +455,57 @@ struct LuSolve {
     // host copies: first position of each level, first entry of each level's first position
     const int *hlvl = nullptr, *hptr_at_lvl = nullptr;
 };
-// LDS that a one-workgroup run may stage the solved vector in.
-constexpr size_t kLuLdsBytes = 64 * 1024;
+// LDS that a one-workgroup run may stage the solved vector in (of the 160 KB).
+constexpr size_t kLuLdsBytes = 128 * 1024;
 
-// In-place solve; with xbar given, xbar[k] = 2 x[k] - xold[k] afterwards.
-template <typename T>
-void launch_lu_trsv(hipStream_t s, const LuSolve &sv, T *x, const T *xold = nullptr, T *xbar = nullptr);
+// In-place solve; with x32 given also x32 = x rounded, and with xbar given
+// xbar[k] = 2 x32[k] - xold[k].
+void launch_lu_trsv(hipStream_t s, const LuSolve &sv, double *x, float *x32 = nullptr, const float *xold = nullptr,
+                    float *xbar = nullptr);
 void launch_lu_mv_f32(hipStream_t s, int lpr, int nrows, const int *rp, const int *ci, const int *val,
-                      const float *x, float *y, float sgn);
+                      const float *x, double *y, double sgn);
 void launch_lu_mv_f64(hipStream_t s, int lpr, int nrows, const int *rp, const int *ci, const int *val,
                       const double *x, double *y, double sgn, bool accumulate);
 void launch_lu_tail_grad(hipStream_t s, int lpr, bool hasq, int r, int nk, const int *rpT, const int *ciT,
                          const int *valT, const float *wy, const int *rpQ, const int *ciQ, const int *valQ,
-                         const float *x, const float *two_so, float *v);
+                         const float *x, const float *two_so, double *v);
 void launch_lu_primal(hipStream_t s, int lpr, bool hasq, int nk, const int *rpT, const int *ciT,
                       const int *valT, const float *wy, const int *rpQ, const int *ciQ, const int *valQ,
-                      const int *rpB, const int *ciB, const int *valB, const float *u, const float *x_in,
+                      const int *rpB, const int *ciB, const int *valB, const double *u, const float *x_in,
                       float *x_out, float *xbar, const float *ct, const float *tau1, const float *two_so,
                       const double *rho, DevCounters *ctr);
-void launch_lu_dual_heavy(hipStream_t s, int nchunk, int nheavy, int m1, const int *ch_row, const int *ch_e0,
-                          const int *ch_e1, const int *first, const int *order, const int *rowc0, const int *rp,
-                          const int *ci, const int *val, const float *xbar, float *part, const float *omega,
-                          const float *rt, float tau2, const float *y_in, float *y_out, float *wy);
+// The dual step's row sums: chunks of the heavy rows into part, the other rows
+// (lpr lanes each) updated; launch_lu_dual_heavy then ends the heavy rows.
+struct LuDualArgs {
+    int m = 0, m1 = 0, nchunk = 0, skip_len = 0;
+    bool rows = true;                    // some row is not heavy
+    const int *ch_row = nullptr, *ch_e0 = nullptr, *ch_e1 = nullptr, *rowc0 = nullptr, *rp = nullptr, *ci = nullptr,
+              *val = nullptr;
+    const float *xbar = nullptr, *omega = nullptr, *rt = nullptr, *y_in = nullptr;
+    double *part = nullptr;
+    float *y_out = nullptr, *wy = nullptr;
+    float tau2 = 0.f;
+};
+struct LuHeavyArgs {
+    int nheavy = 0, m1 = 0;
+    const int *first = nullptr, *order = nullptr;
+    const double *part = nullptr;
+    const float *omega = nullptr, *rt = nullptr, *y_in = nullptr;
+    float *y_out = nullptr, *wy = nullptr;
+    float tau2 = 0.f;
+};
+void launch_lu_dual(hipStream_t s, int lpr, const LuDualArgs &A);
+void launch_lu_dual_heavy(hipStream_t s, const LuHeavyArgs &A);
+// One workgroup for what lies between the row sums and the primal step: the
+// heavy rows' updates, the pivot gradient and both transposed solves; and for
+// the lift's two solves.  lu_fits: whether a pair of solves qualifies.
+constexpr int kLuOneMax = 1024;   // pivots of the one-workgroup form (a thread each)
+bool lu_fits(const LuSolve &a, const LuSolve &b);
+void launch_lu_mid(hipStream_t s, const LuHeavyArgs &H, int lpr, bool hasq, int r, int nk, const int *rpT,
+                   const int *ciT, const int *valT, const float *wy, const int *rpQ, const int *ciQ, const int *valQ,
+                   const float *x, const float *two_so, const LuSolve &a, const LuSolve &b, double *v);
+void launch_lu_lift(hipStream_t s, int r, const LuSolve &a, const LuSolve &b, const double *t, float *x32,
+                    const float *xold, float *xbar);
 void launch_lu_xbar_tail(hipStream_t s, int r, int nk, const float *x_new, const float *x_old, float *xbar);
 void launch_lu_diff64(hipStream_t s, int n, const float *a, const float *b, double *d);
 void launch_lu_res_rows(hipStream_t s, const Tiles &rt, int m1, const int *rp, const int *ci, const int *val,

@@ -50,7 +50,7 @@ struct LuForm {
     int *BJTrp = nullptr, *BJTci = nullptr, *BJTval = nullptr;
     int64_t *dJ = nullptr;
     LuDevSolve Lf, Ub, Utf, Ltb;
-    float *v32 = nullptr;                          // pivot part of the gradient (r)
+    double *v64 = nullptr, *t64 = nullptr;         // pivot part of the gradient, lift under way (r each)
     double *w64a = nullptr, *w64b = nullptr, *w64c = nullptr;   // FP64 lifted work vectors (nfull)
     int *XI = nullptr;                             // candidates' pivot values, r x K
     int64_t *rhs_orig = nullptr;
@@ -68,7 +68,7 @@ struct LuForm {
     // their chunks of kLuRowChunk entries (a workgroup each) and chunk sums
     int nhch = 0;
     int *hch_row = nullptr, *hch_e0 = nullptr, *hch_e1 = nullptr, *hch_first = nullptr;
-    float *hpart = nullptr;
+    double *hpart = nullptr;
     std::vector<int> h_hch_row, h_hch_e0, h_hch_e1, h_hch_first;
     // host copies
     std::vector<int> h_ch_row, h_ch_e0, h_ch_e1, h_ch_slot, h_slot_row, h_qch_row, h_qch_e0, h_qch_e1;
@@ -167,7 +167,8 @@ size_t lu_carve(gfors_problem *P, Carver &cv, const gftu::TuFactored &F, const g
         ds[q]->ent = cv.take<int>(static_cast<int64_t>(hs[q]->ent.size()));
         ds[q]->lvl = cv.take<int>(static_cast<int64_t>(hs[q]->lvl.size()));
     }
-    L.v32 = cv.take<float>(r);
+    L.v64 = cv.take<double>(r);
+    L.t64 = cv.take<double>(r);
     L.w64a = cv.take<double>(nfull);
     L.w64b = cv.take<double>(nfull);
     L.w64c = cv.take<double>(nfull);
@@ -187,7 +188,7 @@ size_t lu_carve(gfors_problem *P, Carver &cv, const gftu::TuFactored &F, const g
     L.hch_e0 = cv.take<int>(L.nhch);
     L.hch_e1 = cv.take<int>(L.nhch);
     L.hch_first = cv.take<int>(L.heavy_rows + 1);
-    L.hpart = cv.take<float>(L.nhch);
+    L.hpart = cv.take<double>(L.nhch);
     return cv.off;
 }
 
@@ -256,24 +257,24 @@ void lift64(gfors_problem *P, double *x) {
     LuForm &L = *P->lu;
     hipStream_t s = P->stream;
     launch_lu_mv_f64(s, L.lpr_bj, static_cast<int>(L.r), L.BJrp, L.BJci, L.BJval, x, x + L.nk, -1.0, false);
-    launch_lu_trsv<double>(s, L.Lf.view(), x + L.nk);
-    launch_lu_trsv<double>(s, L.Ub.view(), x + L.nk);
+    launch_lu_trsv(s, L.Lf.view(), x + L.nk);
+    launch_lu_trsv(s, L.Ub.view(), x + L.nk);
 }
 // x (nfull, FP64): x[0..nk) += S^T x[nk..) = -B_JIbar^T M^{-T} x[nk..) (the tail is overwritten)
 void project64(gfors_problem *P, double *x) {
     LuForm &L = *P->lu;
     hipStream_t s = P->stream;
-    launch_lu_trsv<double>(s, L.Utf.view(), x + L.nk);
-    launch_lu_trsv<double>(s, L.Ltb.view(), x + L.nk);
+    launch_lu_trsv(s, L.Utf.view(), x + L.nk);
+    launch_lu_trsv(s, L.Ltb.view(), x + L.nk);
     launch_lu_mv_f64(s, L.lpr_bjt, static_cast<int>(L.nk), L.BJTrp, L.BJTci, L.BJTval, x + L.nk, x, -1.0, true);
 }
 // FP32 lift of an iterate in place (x[nk..) = S x[0..nk)).
 void lift32(gfors_problem *P, float *x) {
     LuForm &L = *P->lu;
     hipStream_t s = P->stream;
-    launch_lu_mv_f32(s, L.lpr_bj, static_cast<int>(L.r), L.BJrp, L.BJci, L.BJval, x, x + L.nk, -1.f);
-    launch_lu_trsv<float>(s, L.Lf.view(), x + L.nk);
-    launch_lu_trsv<float>(s, L.Ub.view(), x + L.nk);
+    launch_lu_mv_f32(s, L.lpr_bj, static_cast<int>(L.r), L.BJrp, L.BJci, L.BJval, x, L.t64, -1.0);
+    launch_lu_trsv(s, L.Lf.view(), L.t64);
+    launch_lu_trsv(s, L.Ub.view(), L.t64, x + L.nk);
 }
 
 // Preprocess norms (Sec. 3) of the reformulated data by FP64 power iteration
@@ -331,24 +332,53 @@ int lu_device_norms(gfors_problem *P) {
     return GFORS_OK;
 }
 
+// Milliseconds per call of f (launches on s, no synchronisation): one untimed
+// and five timed calls between events.  Calls of less than 15 us are then timed
+// as a replayed graph of sixteen: launched one by one they cost the host more
+// than the device, and every shape looks the same (the lift product of the
+// 90,000-variable quadratic assignment came out at 4 lanes per row and 12.6 us
+// instead of 64 and 4.7).  A stream that cannot be captured keeps the first figure.
+static float time_launches(hipStream_t s, hipEvent_t e0, hipEvent_t e1, const std::function<void()> &f) {
+    auto between = [&](const std::function<void()> &g) {
+        float ms = 0.f;
+        (void)hipEventRecord(e0, s);
+        g();
+        (void)hipEventRecord(e1, s);
+        (void)hipEventSynchronize(e1);
+        (void)hipEventElapsedTime(&ms, e0, e1);
+        return ms;
+    };
+    f();
+    float per = between([&] { for (int q = 0; q < 5; ++q) f(); }) / 5.f;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (per >= 0.015f || !s || s == hipStreamPerThread || s == hipStreamLegacy ||
+        hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone)
+        return per;
+    constexpr int kReps = 16;
+    hipGraph_t g = nullptr;
+    hipGraphExec_t ge = nullptr;
+    if (hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) == hipSuccess) {
+        for (int q = 0; q < kReps; ++q) f();
+        if (hipStreamEndCapture(s, &g) == hipSuccess && g && hipGraphInstantiate(&ge, g, nullptr, nullptr, 0) == hipSuccess) {
+            (void)hipGraphLaunch(ge, s);
+            per = between([&] { (void)hipGraphLaunch(ge, s); (void)hipGraphLaunch(ge, s); }) / (2.f * kReps);
+        }
+    }
+    if (ge) (void)hipGraphExecDestroy(ge);
+    if (g) (void)hipGraphDestroy(g);
+    (void)hipGetLastError();
+    return per;
+}
+
 // Lanes per row of the SpMV-like kernels of a step, timed on the problem
-// (HIP events, 5 launches each after one untimed); the state is reset after.
+// (time_launches); the state is reset after.
 int lu_autotune(gfors_problem *P) {
     LuForm &L = *P->lu;
     hipStream_t s = P->stream;
     hipEvent_t e0, e1;
     HIP_TRY(hipEventCreate(&e0));
     HIP_TRY(hipEventCreate(&e1));
-    auto timeit = [&](const std::function<void()> &f) -> float {
-        f();
-        (void)hipEventRecord(e0, s);
-        for (int q = 0; q < 5; ++q) f();
-        (void)hipEventRecord(e1, s);
-        (void)hipEventSynchronize(e1);
-        float ms = 0.f;
-        (void)hipEventElapsedTime(&ms, e0, e1);
-        return ms;
-    };
+    auto timeit = [&](const std::function<void()> &f) { return time_launches(s, e0, e1, f); };
     const int nk = static_cast<int>(L.nk), r = static_cast<int>(L.r), m = static_cast<int>(P->m);
     const int m1 = static_cast<int>(P->m1);
     const float tau2 = static_cast<float>(P->tau2[0]);
@@ -368,16 +398,20 @@ int lu_autotune(gfors_problem *P) {
         });
     if (r > 0) {
         best_of({1, 4, 16, 64}, L.lpr_tail, [&](int l) {
-            launch_lu_tail_grad(s, l, L.hasQ, r, nk, P->rpT, P->ciT, P->valT, P->wy, P->rpQ, P->ciQ, P->valQ,
-                                P->xbuf[0], P->di.two_so, L.v32);
+            if (lu_fits(L.Utf.view(), L.Ltb.view()))
+                launch_lu_mid(s, LuHeavyArgs(), l, L.hasQ, r, nk, P->rpT, P->ciT, P->valT, P->wy, P->rpQ, P->ciQ, P->valQ,
+                              P->xbuf[0], P->di.two_so, L.Utf.view(), L.Ltb.view(), L.v64);
+            else
+                launch_lu_tail_grad(s, l, L.hasQ, r, nk, P->rpT, P->ciT, P->valT, P->wy, P->rpQ, P->ciQ, P->valQ,
+                                    P->xbuf[0], P->di.two_so, L.v64);
         });
         best_of({1, 4, 16, 64}, L.lpr_bj, [&](int l) {
-            launch_lu_mv_f32(s, l, r, L.BJrp, L.BJci, L.BJval, P->xbuf[0], P->xbuf[1] + nk, -1.f);
+            launch_lu_mv_f32(s, l, r, L.BJrp, L.BJci, L.BJval, P->xbuf[0], L.t64, -1.0);
         });
     }
     best_of({1, 4, 16, 64}, L.lpr_primal, [&](int l) {
         launch_lu_primal(s, l, L.hasQ, nk, P->rpT, P->ciT, P->valT, P->wy, P->rpQ, P->ciQ, P->valQ, L.BJTrp,
-                         L.BJTci, L.BJTval, L.v32, P->xbuf[0], P->xbuf[1], P->xbar, P->ct, P->di.tau1,
+                         L.BJTci, L.BJTval, L.v64, P->xbuf[0], P->xbuf[1], P->xbar, P->ct, P->di.tau1,
                          P->di.two_so, P->di.rho, P->ctr_scratch);
     });
     HIP_TRY(hipGetLastError());
@@ -412,29 +446,61 @@ void lu_enqueue_steps(gfors_problem *P, int nsteps, bool want_res, KTimer *tm) {
         if (res) launch_copy_f32(s, P->xsave, P->xbar, nfull);
         const int a = P->cur, bn = 1 - P->cur;
         TB(0);
+        LuHeavyArgs H;
         if (m > 0) {
-            if (L.heavy_rows > 0)
-                launch_lu_dual_heavy(s, L.nhch, L.heavy_rows, m1, L.hch_row, L.hch_e0, L.hch_e1, L.hch_first,
-                                     P->dual_order, P->rowc0, P->rp, P->ci, P->val, P->xbar, L.hpart, P->omega,
-                                     P->rt, tau2, P->ybuf[a], P->ybuf[bn], P->wy);
-            if (L.heavy_rows < m)
-                launch_dual(s, L.lpr_dual, false, false, m, m1, P->rp, P->ci, P->val, nullptr, P->omega, P->rt,
-                            P->xbar, P->ybuf[a], P->ybuf[bn], P->wy, tau2, P->di.tau2, P->row_inst,
-                            L.heavy_rows > 0 ? kHeavyLen : 0);
+            LuDualArgs A;
+            A.m = m;
+            A.m1 = H.m1 = m1;
+            A.nchunk = L.heavy_rows > 0 ? L.nhch : 0;
+            A.skip_len = L.heavy_rows > 0 ? kHeavyLen : 0;
+            A.rows = L.heavy_rows < m;
+            A.ch_row = L.hch_row;
+            A.ch_e0 = L.hch_e0;
+            A.ch_e1 = L.hch_e1;
+            A.rowc0 = P->rowc0;
+            A.rp = P->rp;
+            A.ci = P->ci;
+            A.val = P->val;
+            A.xbar = P->xbar;
+            A.omega = H.omega = P->omega;
+            A.rt = H.rt = P->rt;
+            A.y_in = H.y_in = P->ybuf[a];
+            A.part = L.hpart;
+            A.y_out = H.y_out = P->ybuf[bn];
+            A.wy = H.wy = P->wy;
+            A.tau2 = H.tau2 = tau2;
+            launch_lu_dual(s, L.lpr_dual, A);
+            H.nheavy = L.heavy_rows;
+            H.first = L.hch_first;
+            H.order = P->dual_order;
+            H.part = L.hpart;
         }
         TE(0);
         TB(1);
-        launch_lu_tail_grad(s, L.lpr_tail, L.hasQ, r, nk, P->rpT, P->ciT, P->valT, P->wy, P->rpQ, P->ciQ,
-                            P->valQ, P->xbuf[a], P->di.two_so, L.v32);
-        launch_lu_trsv<float>(s, L.Utf.view(), L.v32);
-        launch_lu_trsv<float>(s, L.Ltb.view(), L.v32);
+        // one workgroup takes the heavy rows' updates, the pivot gradient and the
+        // transposed solves while the pivots fit its threads
+        const bool mid = lu_fits(L.Utf.view(), L.Ltb.view());
+        if (mid) {
+            launch_lu_mid(s, H, L.lpr_tail, L.hasQ, r, nk, P->rpT, P->ciT, P->valT, P->wy, P->rpQ, P->ciQ, P->valQ,
+                          P->xbuf[a], P->di.two_so, L.Utf.view(), L.Ltb.view(), L.v64);
+        } else {
+            launch_lu_dual_heavy(s, H);
+            launch_lu_tail_grad(s, L.lpr_tail, L.hasQ, r, nk, P->rpT, P->ciT, P->valT, P->wy, P->rpQ, P->ciQ,
+                                P->valQ, P->xbuf[a], P->di.two_so, L.v64);
+            launch_lu_trsv(s, L.Utf.view(), L.v64);
+            launch_lu_trsv(s, L.Ltb.view(), L.v64);
+        }
         launch_lu_primal(s, L.lpr_primal, L.hasQ, nk, P->rpT, P->ciT, P->valT, P->wy, P->rpQ, P->ciQ, P->valQ,
-                         L.BJTrp, L.BJTci, L.BJTval, L.v32, P->xbuf[a], P->xbuf[bn], P->xbar, P->ct,
+                         L.BJTrp, L.BJTci, L.BJTval, L.v64, P->xbuf[a], P->xbuf[bn], P->xbar, P->ct,
                          P->di.tau1, P->di.two_so, P->di.rho, P->ctr);
-        // lift of x_k; the last run also writes xbar's lifted part 2 t(x_k) - t(x_{k-1})
-        launch_lu_mv_f32(s, L.lpr_bj, r, L.BJrp, L.BJci, L.BJval, P->xbuf[bn], P->xbuf[bn] + nk, -1.f);
-        launch_lu_trsv<float>(s, L.Lf.view(), P->xbuf[bn] + nk);
-        launch_lu_trsv<float>(s, L.Ub.view(), P->xbuf[bn] + nk, P->xbuf[a] + nk, P->xbar + nk);
+        // lift of x_k in FP64, rounded once; the last run also writes xbar's lifted part
+        launch_lu_mv_f32(s, L.lpr_bj, r, L.BJrp, L.BJci, L.BJval, P->xbuf[bn], L.t64, -1.0);
+        if (lu_fits(L.Lf.view(), L.Ub.view())) {
+            launch_lu_lift(s, r, L.Lf.view(), L.Ub.view(), L.t64, P->xbuf[bn] + nk, P->xbuf[a] + nk, P->xbar + nk);
+        } else {
+            launch_lu_trsv(s, L.Lf.view(), L.t64);
+            launch_lu_trsv(s, L.Ub.view(), L.t64, P->xbuf[bn] + nk, P->xbuf[a] + nk, P->xbar + nk);
+        }
         TE(1);
         if (res) {
             // s^y and the primal gap on lift(xbar_{k-1} - x_k), lift(x_k)

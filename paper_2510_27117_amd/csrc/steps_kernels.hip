@@ -28,17 +28,6 @@ namespace gfors {
 
 namespace {
 
-// Sum over groups of L lanes (a power of two <= 64), widest distance first.
-__device__ __forceinline__ float lane_group_sum(float v, int L) {
-    if (L >= 64) v = xor_sum<32>(v);
-    if (L >= 32) v = xor_sum<16>(v);
-    if (L >= 16) v = xor_sum<8>(v);
-    if (L >= 8) v = xor_sum<4>(v);
-    if (L >= 4) v = xor_sum<2>(v);
-    if (L >= 2) v = xor_sum<1>(v);
-    return v;
-}
-
 template <int VB>
 struct Coef {
     using type = int;
