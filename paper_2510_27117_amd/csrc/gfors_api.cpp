@@ -82,6 +82,8 @@ static size_t carve(gfors_problem *P, Carver &cv, int64_t n, int64_t m1, int64_t
     P->ciQ = cv.take<int>(nnzQ);
     P->valQ = cv.take<int>(nnzQ);
     P->rowQ = cv.take<int>(nnzQ);
+    P->packQ = cv.take<int>(nnzQ);
+    for (uint4 *&q : P->qcode) q = cv.take<uint4>(nnzQ && m == 0 ? (n + 63) / 64 : 0);
     P->rpU = cv.take<int>(nnzQ ? n + 1 : 1);
     P->ciU = cv.take<int>(nnzQ);
     P->valU = cv.take<int>(nnzQ);
@@ -680,6 +682,13 @@ int gfors_create_problem(const gfors_csr *A, const int64_t *b, const gfors_csr *
         for (int64_t i = 0; i < n; ++i)
             for (int e = rpQ[i]; e < rpQ[i + 1]; ++e) rowQ[e] = static_cast<int>(i);
         if ((rc = upload(s, P->rowQ, rowQ.data(), P->nnzQ))) return rc;
+        P->qpacked = n <= (int64_t{1} << 24) &&
+                     std::all_of(valQ.begin(), valQ.end(), [](int v) { return v >= -128 && v <= 127; });
+        std::vector<int> packQ(P->qpacked ? P->nnzQ : 0);
+        for (size_t e = 0; e < packQ.size(); ++e)
+            packQ[e] = static_cast<int>(static_cast<uint32_t>(ciQ[e]) | static_cast<uint32_t>(valQ[e]) << 24);
+        P->qcode_ok = P->qpacked && P->T == 1 && P->m == 0 && n <= kMaxCodes;
+        if (P->qpacked && (rc = upload(s, P->packQ, packQ.data(), P->nnzQ))) return rc;
         if ((rc = sync(P))) return rc;
         if (P->qsym) {
             const int64_t nu = static_cast<int64_t>(ciU.size());
@@ -1248,6 +1257,7 @@ int gfors_create_problem(const gfors_csr *A, const int64_t *b, const gfors_csr *
     };
     P->cfg.lpr_dual = pick(m ? static_cast<double>(P->nnzK) / m : 1.0);
     P->cfg.lpr_primal = pick(static_cast<double>(P->nnzK + P->nnzQ) / n);
+    P->qcode_on = P->qcode_ok && P->cfg.lpr_primal <= 16;
     if (P->slicedK) {
         P->cfg.slices_dual = kXcdSlices;
         P->cfg.lpr_dual = pick(static_cast<double>(P->nnzK) / m / kXcdSlices);
@@ -1575,6 +1585,9 @@ static void launch_dual_cfg(gfors_problem *P, int lpr, int slices, int sell, con
     P->by_fresh = wy_bits;
 }
 
+// 2 / s_o of a single instance
+static float two_so32(const gfors_problem *P) { return static_cast<float>(P->s_o[0] > 0 ? 2.0 / P->s_o[0] : 2.0); }
+
 static void launch_primal_cfg(gfors_problem *P, int lpr, int slices, int sell, const float *x_in,
                               float *x_out, float *xbar, DevCounters *ctr) {
     hipStream_t s = P->stream;
@@ -1645,16 +1658,16 @@ static void launch_primal_cfg(gfors_problem *P, int lpr, int slices, int sell, c
     } else if (lpr > kLprBlock) {
         // heavy variables a workgroup each, the others lpr - 256 lanes (no Q)
         launch_primal_long(s, P->unitK, batched, primal_long_args(P, x_in, x_out, xbar), tau1, P->di.tau1, P->var_inst);
-        launch_primal(s, lpr - kLprBlock, kmode, false, batched, static_cast<int>(P->n), P->rpT,
+        launch_primal(s, lpr - kLprBlock, kmode, 0, batched, static_cast<int>(P->n), P->rpT,
                       P->dense_cols ? P->colT0 : nullptr, P->ciT, P->valT, P->wy, P->rpQ, P->ciQ, P->valQ,
                       x_in, x_out, xbar, P->ct, tau1, 0.f, P->di.tau1, P->di.two_so, P->di.rho,
                       P->var_inst, ctr, kHeavyLen);
     } else {
-        launch_primal(s, lpr, kmode, P->hasQ, batched, static_cast<int>(P->n), P->rpT,
-                      P->dense_cols ? P->colT0 : nullptr, P->ciT,
-                      P->valT, P->wy, P->rpQ, P->ciQ, P->valQ, x_in, x_out, xbar, P->ct, tau1,
-                      static_cast<float>(P->s_o[0] > 0 ? 2.0 / P->s_o[0] : 2.0), P->di.tau1,
-                      P->di.two_so, P->di.rho, P->var_inst, ctr, 0);
+        // values of 8 bits and indices of 24 travel in one word (half the bytes)
+        launch_primal(s, lpr, kmode, !P->hasQ ? 0 : P->qpacked ? kQPacked : kQInt32, batched,
+                      static_cast<int>(P->n), P->rpT, P->dense_cols ? P->colT0 : nullptr, P->ciT,
+                      P->valT, P->wy, P->rpQ, P->qpacked ? P->packQ : P->ciQ, P->valQ, x_in, x_out, xbar, P->ct, tau1,
+                      two_so32(P), P->di.tau1, P->di.two_so, P->di.rho, P->var_inst, ctr, 0);
     }
     // the problem's xbar changed: its bitmap is current only if written with it
     if (xbar == P->xbar) P->bx_fresh = xbar_bits;
@@ -1684,6 +1697,14 @@ static int bits_ok_primal(gfors_problem *P, int slices, int sell, int bits) {
     if (bits == 7) return (!sell && P->lgt_pd > 0 && P->hg_ngroup > 0) ? 1 : 0;   // + heavy shift groups
     if (bits != 2 && bits != 3) return 0;
     return (sell && P->sellT.ptr && P->sellT.ns / 8 <= kMaxLdsBitmapBytes) ? 1 : 0;
+}
+
+// A primal step from the codes of x_in (qcode[from]), leaving those of x_out.
+static void launch_codes(gfors_problem *P, int lpr, int from, const float *x_in, float *x_out, float *xbar,
+                         DevCounters *ctr) {
+    launch_primal_codes(P->stream, lpr, static_cast<int>(P->n), P->rpQ, P->packQ, x_in, P->qcode[from],
+                        P->qcode[1 - from], x_out, xbar, P->ct, static_cast<float>(P->tau1[0]), two_so32(P),
+                        P->di.rho, ctr);
 }
 
 // Autotuner: time every candidate launch shape of the dual and primal SpMV on
@@ -1772,6 +1793,9 @@ static int autotune(gfors_problem *P, bool with_eval) {
         float best = 1e30f;
         float *xs = P->xsave, *xb = reinterpret_cast<float *>(P->pv);
         if (with_eval) launch_fill_share(s, P->wy, 0.5f, 56, P->m);
+        // a quadratic over the box: 45 % of x neither 0 nor 1 (max cut's 50th step)
+        if (with_eval && P->qcode_ok) launch_fill_share(s, P->xbuf[P->cur], 0.5f, 45, P->n);
+        P->qcode_on = false;
         // the dual in use reads the bitmap of xbar / leaves the bitmap of wy
         const bool dual_reads = P->cfg.sell_dual && P->cfg.bits_dual >= 1 && P->cfg.bits_dual <= 3;
         const bool dual_leaves = P->m > 0 && P->cfg.slices_dual > 1;
@@ -1812,6 +1836,13 @@ static int autotune(gfors_problem *P, bool with_eval) {
             P->cfg.bits_primal = b;
             const float t = primal_time(1, 1, 1);
             if (t < best) { best = t; best_bits = b; P->cfg.lpr_primal = 1; P->cfg.slices_primal = 1; P->cfg.sell_primal = 1; }
+        }
+        if (P->qcode_ok) {
+            launch_q_codes(s, static_cast<int>(P->n), P->xbuf[P->cur], P->qcode[0]);
+            for (int l : {1, 2, 4, 8, 16}) {
+                const float t = timeit([&] { launch_codes(P, l, 0, P->xbuf[P->cur], xs, xb, P->ctr_scratch); });
+                if (t < best) { best = t; P->qcode_on = true; P->cfg.lpr_primal = l; }
+            }
         }
         for (int b : {4, 5, 6, 7}) {
             if (!bits_ok_primal(P, 1, 0, b)) continue;
@@ -1907,6 +1938,9 @@ static void enqueue_steps(gfors_problem *P, int nsteps, bool want_res, KTimer *t
         }
         nsteps -= joint;
     }
+    // codes of x from step to step (timed steps keep k_primal: the same sums)
+    const bool codes = P->qcode_on && !tm;
+    if (codes && nsteps > 0) launch_q_codes(s, static_cast<int>(P->n), P->xbuf[P->cur], P->qcode[0]);
     for (int it = 0; it < nsteps; ++it) {
         const bool res = want_res && it == nsteps - 1;
         if (res) launch_copy_f32(s, P->xsave, P->xbar, P->n);
@@ -1917,8 +1951,11 @@ static void enqueue_steps(gfors_problem *P, int nsteps, bool want_res, KTimer *t
                             P->ybuf[bnext]);
         TE(0);
         TB(1);
-        launch_primal_cfg(P, P->cfg.lpr_primal, P->cfg.slices_primal, P->cfg.sell_primal,
-                          P->xbuf[a], P->xbuf[bnext], P->xbar, P->ctr);
+        if (codes)
+            launch_codes(P, P->cfg.lpr_primal, it & 1, P->xbuf[a], P->xbuf[bnext], P->xbar, P->ctr);
+        else
+            launch_primal_cfg(P, P->cfg.lpr_primal, P->cfg.slices_primal, P->cfg.sell_primal,
+                              P->xbuf[a], P->xbuf[bnext], P->xbar, P->ctr);
         TE(1);
         if (res) enqueue_residuals(P, a);
         P->cur = bnext;
@@ -2406,7 +2443,7 @@ int gfors_set_launch_cfg(gfors_problem *P, const int32_t *cfg) {
     P->cfg.sell_primal = cfg[5] ? 1 : 0;
     P->cfg.bits_dual = cfg[6];
     P->cfg.bits_primal = cfg[7];
-    P->res_on = false;   // the caller asks for these launches
+    P->res_on = P->qcode_on = false;   // the caller asks for these launches
     P->graphs_clear();
     return GFORS_OK;
 }

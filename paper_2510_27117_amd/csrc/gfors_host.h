@@ -119,6 +119,12 @@ struct gfors_problem {
     int *rpT = nullptr, *ciT = nullptr, *valT = nullptr;
     int *rpQ = nullptr, *ciQ = nullptr, *valQ = nullptr;
     int *rowQ = nullptr;   // row of each Q entry (quadratic objective)
+    int *packQ = nullptr;  // qpacked: column (24 bits) and value (8) of each Q entry
+    bool qpacked = false;
+    // one instance without rows, Q packed: codes of x (two bits per variable), the
+    // step kernel that uses them applies (qcode_ok), is chosen (qcode_on)
+    uint4 *qcode[2] = {nullptr, nullptr};
+    bool qcode_ok = false, qcode_on = false;
     // the objective's evaluation over the upper triangle of a symmetric Q:
     // entries (i, k) with k > i doubled, the diagonal once
     bool qsym = false;

@@ -236,7 +236,23 @@ void launch_dual(hipStream_t s, int lpr, bool unit, bool batched, int m, int m1,
                  float *wy, float tau2, const float *tau2_inst, const int *row_inst,
                  int skip_len);
 
-void launch_primal(hipStream_t s, int lpr, int kmode, bool hasq, bool batched, int n,
+// The update of a variable without rows, s2 = (Q x)_i.
+__device__ __forceinline__ float primal_update_q(float s2, float ct, float rh, float two_so, float tau1, float xi) {
+    float g = ct + rh;
+    g = fmaf(two_so, s2, g);
+    g -= 2.f * rh * xi;
+    return fminf(fmaxf(xi - tau1 * g, 0.f), 1.f);
+}
+// The step over codes (two bits per variable) of x: n <= kMaxCodes, lpr <= 16.
+constexpr int64_t kMaxCodes = 128 * 1024 * 4;
+void launch_q_codes(hipStream_t s, int n, const float *x, uint4 *codes);
+void launch_primal_codes(hipStream_t s, int lpr, int n, const int *rpQ, const int *packQ, const float *x_in,
+                         const uint4 *codes_in, uint4 *codes_out, float *x_out, float *xbar, const float *ct, float tau1,
+                         float two_so, const double *rho, DevCounters *ctr);
+// How k_primal reads Q: not at all, an index and an int32 value per entry, or both
+// in a word (24 + 8 bits, ciQ points at the words).
+constexpr int kQInt32 = 1, kQPacked = 2;
+void launch_primal(hipStream_t s, int lpr, int kmode, int qmode, bool batched, int n,
                    const int *rpT, const int *colT0, const int *ciT, const int *valT, const float *wy,
                    const int *rpQ, const int *ciQ, const int *valQ, const float *x_in,
                    float *x_out, float *xbar, const float *ct, float tau1, float two_so,

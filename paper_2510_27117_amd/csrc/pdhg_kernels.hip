@@ -234,7 +234,7 @@ void launch_primal_long(hipStream_t s, bool unit, bool batched, const PrimalLong
 // read from x_in while x_out receives x_k (double buffer).
 // KMODE: 0 = no constraint rows, 1 = unit coefficients, 2 = int32 values.
 // ---------------------------------------------------------------------------
-template <int LPR, int KMODE, bool HASQ, bool BATCH>
+template <int LPR, int KMODE, int QMODE, bool BATCH>
 __global__ void __launch_bounds__(256)
 k_primal(int n, const int *__restrict__ rpT, const int *__restrict__ colT0, const int *__restrict__ ciT,
          const int *__restrict__ valT, const float *__restrict__ wy,
@@ -275,20 +275,44 @@ k_primal(int n, const int *__restrict__ rpT, const int *__restrict__ colT0, cons
                 else s1 = fmaf(static_cast<float>(valT[e]), w, s1);
             }
         }
-        if (HASQ) {
+        if (QMODE != 0) {
+            // a batch's entries are loaded together, then their operands: a row
+            // costs three latencies (bounds, entries, operands) and not two more
+            // for every LPR entries
+            constexpr int U = LPR <= 2 ? 8 : 4;
             const int e1 = rpQ[i + 1];
-            for (int e = rpQ[i] + sub; e < e1; e += LPR)
-                s2 = fmaf(static_cast<float>(valQ[e]), x_in[ciQ[e]], s2);
+            for (int e = rpQ[i] + sub; e < e1; e += U * LPR) {
+                int c[U], a[U];
+                float v[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const bool in = e + u * LPR < e1;
+                    const int w = in ? ciQ[e + u * LPR] : 0;
+                    c[u] = QMODE == kQPacked ? w & 0xffffff : w;
+                    a[u] = QMODE == kQPacked ? w >> 24 : (in ? valQ[e + u * LPR] : 0);
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) v[u] = e + u * LPR < e1 ? x_in[c[u]] : 0.f;
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (e + u * LPR < e1) s2 = fmaf(static_cast<float>(a[u]), v[u], s2);
+            }
         }
     }
     if (KMODE != 0) s1 = group_sum<LPR>(s1);
-    if (HASQ) s2 = group_sum<LPR>(s2);
-    if (own && sub == 0) {
+    if (QMODE != 0) s2 = group_sum<LPR>(s2);
+    if (KMODE == 0 && QMODE != 0 && !BATCH) {
+        if (own && sub == 0) {
+            const float xn = primal_update_q(s2, cti, static_cast<float>(rho[0]), two_so, tau1, xi);
+            x_out[i] = xn;
+            xbar[i] = 2.f * xn - xi;
+        }
+    } else if (own && sub == 0) {
         const float rh = static_cast<float>(rho[t]);
         const float ta = BATCH ? tau1_inst[t] : tau1;
         float g = cti + rh;
         if (KMODE != 0) g -= s1;
-        if (HASQ) g = fmaf(BATCH ? two_so_inst[t] : two_so, s2, g);
+        if (QMODE != 0) g = fmaf(BATCH ? two_so_inst[t] : two_so, s2, g);
         g -= 2.f * rh * xi;
         const float xn = fminf(fmaxf(xi - ta * g, 0.f), 1.f);
         x_out[i] = xn;
@@ -326,7 +350,7 @@ void launch_dual(hipStream_t s, int lpr, bool unit, bool batched, int m, int m1,
     }
 }
 
-template <int LPR, int KMODE, bool HASQ>
+template <int LPR, int KMODE, int QMODE>
 static void primal_k(hipStream_t s, bool batched, int n, const int *rpT, const int *colT0, const int *ciT,
                      const int *valT, const float *wy, const int *rpQ, const int *ciQ,
                      const int *valQ, const float *x_in, float *x_out, float *xbar,
@@ -337,36 +361,158 @@ static void primal_k(hipStream_t s, bool batched, int n, const int *rpT, const i
     const int blocks = static_cast<int>((threads + 255) / 256);
     if (blocks == 0) return;
     if (batched)
-        k_primal<LPR, KMODE, HASQ, true><<<blocks, 256, 0, s>>>(n, rpT, colT0, ciT, valT, wy, rpQ, ciQ, valQ, x_in, x_out, xbar, ct, tau1, two_so, tau1_inst, two_so_inst, rho, var_inst, ctr, skip_len);
+        k_primal<LPR, KMODE, QMODE, true><<<blocks, 256, 0, s>>>(n, rpT, colT0, ciT, valT, wy, rpQ, ciQ, valQ, x_in, x_out, xbar, ct, tau1, two_so, tau1_inst, two_so_inst, rho, var_inst, ctr, skip_len);
     else
-        k_primal<LPR, KMODE, HASQ, false><<<blocks, 256, 0, s>>>(n, rpT, colT0, ciT, valT, wy, rpQ, ciQ, valQ, x_in, x_out, xbar, ct, tau1, two_so, tau1_inst, two_so_inst, rho, var_inst, ctr, skip_len);
+        k_primal<LPR, KMODE, QMODE, false><<<blocks, 256, 0, s>>>(n, rpT, colT0, ciT, valT, wy, rpQ, ciQ, valQ, x_in, x_out, xbar, ct, tau1, two_so, tau1_inst, two_so_inst, rho, var_inst, ctr, skip_len);
 }
 
 template <int LPR>
-static void primal_lpr(hipStream_t s, int kmode, bool hasq, bool batched, int n,
+static void primal_lpr(hipStream_t s, int kmode, int qmode, bool batched, int n,
                        const int *rpT, const int *colT0, const int *ciT, const int *valT, const float *wy,
                        const int *rpQ, const int *ciQ, const int *valQ, const float *x_in,
                        float *x_out, float *xbar, const float *ct, float tau1, float two_so,
                        const float *tau1_inst, const float *two_so_inst, const double *rho,
                        const int *var_inst, DevCounters *ctr, int skip_len) {
 #define GF_P(KM, HQ) primal_k<LPR, KM, HQ>(s, batched, n, rpT, colT0, ciT, valT, wy, rpQ, ciQ, valQ, x_in, x_out, xbar, ct, tau1, two_so, tau1_inst, two_so_inst, rho, var_inst, ctr, skip_len)
-    if (hasq) {
-        if (kmode == 0) GF_P(0, true); else if (kmode == 1) GF_P(1, true); else GF_P(2, true);
+    if (qmode == kQPacked) {
+        if (kmode == 0) GF_P(0, kQPacked); else if (kmode == 1) GF_P(1, kQPacked); else GF_P(2, kQPacked);
+    } else if (qmode == kQInt32) {
+        if (kmode == 0) GF_P(0, kQInt32); else if (kmode == 1) GF_P(1, kQInt32); else GF_P(2, kQInt32);
     } else {
-        if (kmode == 0) GF_P(0, false); else if (kmode == 1) GF_P(1, false); else GF_P(2, false);
+        if (kmode == 0) GF_P(0, 0); else if (kmode == 1) GF_P(1, 0); else GF_P(2, 0);
     }
 #undef GF_P
 }
 
-void launch_primal(hipStream_t s, int lpr, int kmode, bool hasq, bool batched, int n,
+void launch_primal(hipStream_t s, int lpr, int kmode, int qmode, bool batched, int n,
                    const int *rpT, const int *colT0, const int *ciT, const int *valT, const float *wy,
                    const int *rpQ, const int *ciQ, const int *valQ, const float *x_in,
                    float *x_out, float *xbar, const float *ct, float tau1, float two_so,
                    const float *tau1_inst, const float *two_so_inst, const double *rho,
                    const int *var_inst, DevCounters *ctr, int skip_len) {
     switch (lpr) {
-#define GF_CASE(L) case L: primal_lpr<L>(s, kmode, hasq, batched, n, rpT, colT0, ciT, valT, wy, rpQ, ciQ, valQ, x_in, x_out, xbar, ct, tau1, two_so, tau1_inst, two_so_inst, rho, var_inst, ctr, skip_len); break;
+#define GF_CASE(L) case L: primal_lpr<L>(s, kmode, qmode, batched, n, rpT, colT0, ciT, valT, wy, rpQ, ciQ, valQ, x_in, x_out, xbar, ct, tau1, two_so, tau1_inst, two_so_inst, rho, var_inst, ctr, skip_len); break;
         GF_CASE(1) GF_CASE(2) GF_CASE(4) GF_CASE(8) GF_CASE(16) GF_CASE(32) GF_CASE(64)
+#undef GF_CASE
+        default: break;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Primal step without rows (a quadratic over the box: max cut) with the operands'
+// codes in LDS.  k_primal is bound by its gathers: 2 M operands cost 2 M L2 lines
+// (11 us at 200,000 variables, 10 entries each, for 11 MB of compulsory traffic).
+// But x is mostly 0 or 1 (55 % at step 50, 75 % at step 500 there): every workgroup
+// stages two bits per variable (x == 1, x neither 0 nor 1; 16 bytes per 64
+// variables), and only the others are gathered.  A wavefront owns 64 rows, LPR
+// lanes add up LPR consecutive rows one after the other with all rows' first
+// entries in flight together, and then a lane per row updates it and the
+// wavefront writes the new codes.  The sums are k_primal's, in its order.
+// A step in a replayed run, 200,000 variables: 12.4 us by k_primal with an index
+// and a value per entry loaded one after the other, 10.7 packed and in batches,
+// 6.6 here.  1 to 16 lanes per row are within 5 % of each other.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ void put_codes(uint4 *codes, int blk, bool own, float x) {
+    const uint64_t one = __ballot(own && x == 1.f), mid = __ballot(own && x != 0.f && x != 1.f);
+    if ((threadIdx.x & 63) == 0)
+        codes[blk] = make_uint4(static_cast<uint32_t>(one), static_cast<uint32_t>(mid), static_cast<uint32_t>(one >> 32),
+                                static_cast<uint32_t>(mid >> 32));
+}
+__global__ void __launch_bounds__(256)
+k_q_codes(int n, const float *__restrict__ x, uint4 *__restrict__ codes) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if ((i & ~63) >= n) return;   // a whole wavefront
+    put_codes(codes, i >> 6, i < n, i < n ? x[i] : 0.f);
+}
+
+template <int LPR>
+__global__ void __launch_bounds__(1024)
+k_primal_codes(int n, const int *__restrict__ rpQ, const int *__restrict__ packQ, const float *__restrict__ x_in,
+               const uint4 *__restrict__ codes_in, uint4 *__restrict__ codes_out, float *__restrict__ x_out,
+               float *__restrict__ xbar, const float *__restrict__ ct, float tau1, float two_so,
+               const double *__restrict__ rho, DevCounters *__restrict__ ctr) {
+    extern __shared__ uint4 qcodes[];
+    constexpr int U = LPR >= 16 ? 1 : 16 / LPR;   // entries of a row in flight per lane
+    const int lane = threadIdx.x & 63, sub = lane & (LPR - 1);
+    const int nblk = (n + 63) >> 6;
+    const int blk = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    const int row = blk * 64 + lane;
+    const bool own = row < n;
+    const int r0 = rpQ[min(row, n)], r1 = rpQ[min(row + 1, n)];
+    const float xi = own ? x_in[row] : 0.f, cti = own ? ct[row] : 0.f;
+    const float rh = static_cast<float>(rho[0]);
+    int w[LPR][U];
+    int e0[LPR], e1[LPR];
+#pragma unroll
+    for (int p = 0; p < LPR; ++p) {
+        const int src = (lane & ~(LPR - 1)) + p;
+        e0[p] = __shfl(r0, src, 64) + sub;
+        e1[p] = __shfl(r1, src, 64);
+#pragma unroll
+        for (int u = 0; u < U; ++u) w[p][u] = e0[p] + u * LPR < e1[p] ? packQ[e0[p] + u * LPR] : 0;
+    }
+    for (int t0 = threadIdx.x; t0 < nblk; t0 += 4 * blockDim.x) {
+        uint4 q[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) q[u] = codes_in[min(t0 + u * static_cast<int>(blockDim.x), nblk - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (t0 + u * static_cast<int>(blockDim.x) < nblk) qcodes[t0 + u * blockDim.x] = q[u];
+    }
+    __syncthreads();
+    if (blk >= nblk) return;
+    const uint2 *half = reinterpret_cast<const uint2 *>(qcodes);
+    auto operand = [&](int word, bool in) {
+        const int c = word & 0xffffff;
+        const uint2 q = half[c >> 5];
+        float v = (q.x >> (c & 31)) & 1u ? 1.f : 0.f;
+        if (in && ((q.y >> (c & 31)) & 1u)) v = x_in[c];
+        return v;
+    };
+    float v[LPR][U];
+#pragma unroll
+    for (int p = 0; p < LPR; ++p)
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[p][u] = operand(w[p][u], e0[p] + u * LPR < e1[p]);
+    float mine = 0.f;
+#pragma unroll
+    for (int p = 0; p < LPR; ++p) {
+        float s2 = 0.f;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (e0[p] + u * LPR < e1[p]) s2 = fmaf(static_cast<float>(w[p][u] >> 24), v[p][u], s2);
+        for (int e = e0[p] + U * LPR; e < e1[p]; e += LPR) {
+            const int word = packQ[e];
+            s2 = fmaf(static_cast<float>(word >> 24), operand(word, true), s2);
+        }
+        s2 = group_sum<LPR>(s2);
+        if (sub == p) mine = s2;
+    }
+    float xn = 0.f;
+    if (own) {
+        xn = primal_update_q(mine, cti, rh, two_so, tau1, xi);
+        x_out[row] = xn;
+        xbar[row] = 2.f * xn - xi;
+    }
+    put_codes(codes_out, blk, own, xn);
+    if (blockIdx.x == 0 && threadIdx.x == 0) ctr->k += 1;
+}
+
+void launch_q_codes(hipStream_t s, int n, const float *x, uint4 *codes) {
+    k_q_codes<<<(n + 255) / 256, 256, 0, s>>>(n, x, codes);
+}
+void launch_primal_codes(hipStream_t s, int lpr, int n, const int *rpQ, const int *packQ, const float *x_in,
+                         const uint4 *codes_in, uint4 *codes_out, float *x_out, float *xbar, const float *ct, float tau1,
+                         float two_so, const double *rho, DevCounters *ctr) {
+    // one workgroup per CU as soon as there are 64 rows for each: the table is
+    // staged once per workgroup
+    const int nblk = (n + 63) / 64;
+    const int waves = std::max(1, std::min(16, (nblk + 255) / 256));
+    const int blocks = (nblk + waves - 1) / waves;
+    const size_t lds = static_cast<size_t>(nblk) * sizeof(uint4);
+    switch (lpr) {
+#define GF_CASE(L) case L: k_primal_codes<L><<<blocks, 64 * waves, lds, s>>>(n, rpQ, packQ, x_in, codes_in, codes_out, x_out, xbar, ct, tau1, two_so, rho, ctr); break;
+        GF_CASE(1) GF_CASE(2) GF_CASE(4) GF_CASE(8) GF_CASE(16)
 #undef GF_CASE
         default: break;
     }

@@ -1,0 +1,80 @@
+"""Steps of a quadratic over the box.  The kernel that reads codes of x against the
+one that gathers every operand: the sums run over the same lanes in the same order,
+so every bit must agree.  Both forms of Q (a word per entry, index and int32 value)
+against the step in FP64: rows of some 50 entries add up 50 rounded products, so 1e-5
+of the largest gradient term bounds an FP32 step."""
+import numpy as np
+import pytest
+
+from paper_2510_27117_amd import instances as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def G():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2510_27117_amd import gfors
+    return gfors
+
+
+def _box(n, degree, vmax, seed, star=0):
+    """Random symmetric Q (about `degree` entries a row, the extremes of [-vmax, vmax - 1] among
+    them), `star` neighbours of variable 0, no rows."""
+    rng = np.random.default_rng(seed)
+    k = max(1, int(n * degree / 2)) if n > 1 else 0
+    i, j = rng.integers(0, n, k), rng.integers(0, n, k)
+    if star:
+        i, j = np.concatenate([i, np.zeros(star, int)]), np.concatenate([j, rng.integers(1, n, star)])
+    key = np.unique((np.minimum(i, j) * n + np.maximum(i, j))[i != j])
+    i, j = key // n, key % n
+    v = rng.integers(-vmax, vmax, key.size)
+    v[v == 0] = 1
+    if key.size:
+        v[0], v[-1] = vmax - 1, -vmax
+    P = I.from_dense(rng.integers(-9, 10, n)) if n <= 64 else I.max_cut_er(n, 0.0, seed)
+    P.c = rng.integers(-9, 10, n).astype(P.c.dtype)
+    P.Q = I.csr_from_coo(n, n, np.concatenate([i, j]), np.concatenate([j, i]), np.concatenate([v, v]))
+    return P
+
+
+CASES = {"two": (2, 1, 128, 0), "63": (63, 4, 5, 0), "64": (64, 9, 128, 0), "65": (65, 20, 1, 0),
+         "lanes1": (3000, 1.2, 3, 0), "lanes2": (4097, 3, 3, 0), "lanes4": (5000, 6, 128, 0), "lanes8": (16385, 11, 1, 0),
+         "lanes16": (7000, 30, 7, 0), "lanes32": (2000, 50, 7, 0), "star": (6000, 5, 4, 5000),
+         "int32": (5000, 6, 129, 0), "int32_long": (3000, 30, 100000, 0), "largest": (1 << 19, 4, 2, 0),
+         "beyond": ((1 << 19) + 1, 4, 2, 0)}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_codes_equal_gathers_and_the_exact_step(G, name):
+    n, degree, vmax, star = CASES[name]
+    P = _box(n, degree, vmax, 3, star)
+    prm = G.default_params(k_int=7, K_max=64, autotune=0, power_iters=20)
+    a, b = G.Problem(P, prm), G.Problem(P, prm)
+    b.set_launch_cfg(**b.launch_cfg())                  # a launch of k_primal per step from here on
+    rng = np.random.default_rng(5)
+    sc = a.scales()
+    rho, so, tau1 = float(sc["rho_min"][0]), float(sc["obj_scale"][0]), float(sc["tau1"][0])
+    x = np.clip(rng.random(n) * 3 - 1, 0, 1).astype(np.float32)     # a third each: 0, between, 1
+    xp = rng.random(n).astype(np.float32)
+    for steps in (1, 2, 7, 70):                         # 70: replayed runs of 32 and the rest
+        for p in (a, b):
+            p.set_state(x, xp, np.zeros(0), rho, k=3)
+            p.pdhg_steps(steps, want_residuals=steps == 7)
+        sa, sb = a.get_state(), b.get_state()
+        for key in ("x", "x_prev"):
+            assert np.array_equal(sa[key], sb[key]), (steps, key)
+        if steps == 7:
+            assert np.array_equal(a.residuals(), b.residuals())
+        if steps == 1:
+            x64, Q = x.astype(np.float64), P.Q
+            rows = np.repeat(np.arange(n), np.diff(Q.row_ptr))
+            prod = Q.val * x64[Q.col]
+            qx, mag = np.bincount(rows, prod, n), np.bincount(rows, np.abs(prod), n)
+            g = P.c / so + rho + 2 / so * qx - 2 * rho * x64
+            bar = 1e-5 * (1 + tau1 * (np.abs(P.c) / so + rho * 3 + 2 / so * mag))
+            assert np.all(np.abs(sa["x"] - np.clip(x64 - tau1 * g, 0, 1)) <= bar)
+    a.close()
+    b.close()
