@@ -82,7 +82,7 @@ static size_t carve(gfors_problem *P, Carver &cv, int64_t n, int64_t m1, int64_t
     P->ciQ = cv.take<int>(nnzQ);
     P->valQ = cv.take<int>(nnzQ);
     P->rowQ = cv.take<int>(nnzQ);
-    P->packQ = cv.take<int>(nnzQ);
+    P->packQ = cv.take<int>(nnzQ ? nnzQ + 1 : 0);
     for (uint4 *&q : P->qcode) q = cv.take<uint4>(nnzQ && m == 0 ? (n + 63) / 64 : 0);
     P->rpU = cv.take<int>(nnzQ ? n + 1 : 1);
     P->ciU = cv.take<int>(nnzQ);
@@ -494,6 +494,15 @@ int gfors_create_problem(const gfors_csr *A, const int64_t *b, const gfors_csr *
         const std::vector<int> &ve = P->qsym ? valU : valQ;
         for (int v : ve)
             if (std::llabs(static_cast<int64_t>(v)) >= (1LL << 21)) P->q24 = false;
+        // one magnitude: counted bitwise (294 us weighted, 23 counted, for a
+        // million entries and 2048 candidates), unless a row alone passes the counters
+        const std::vector<int> &re = P->qsym ? rpU : rpQ;
+        int64_t longest = 0;
+        for (int64_t i = 0; i < n; ++i) longest = std::max<int64_t>(longest, re[i + 1] - re[i]);
+        P->qmag = ve.empty() || ve[0] == INT32_MIN ? 0 : std::abs(ve[0]);
+        for (int v : ve)
+            if (v != P->qmag && v != -P->qmag) P->qmag = 0;
+        if (longest + kQuadNnz > kQuadBitsMax) P->qmag = 0;
     }
     // objective accumulation width in the sampler
     int64_t cmax = 0;
@@ -609,7 +618,7 @@ int gfors_create_problem(const gfors_csr *A, const int64_t *b, const gfors_csr *
             const int64_t v0 = P->inst_var0[t];
             const std::vector<int> &rpE = P->qsym ? rpU : rpQ;   // the evaluated entries
             std::function<int64_t(int64_t)> wq = [&](int64_t q) -> int64_t { return rpE[v0 + q + 1] - rpE[v0 + q]; };
-            build_tiles_items(hq, t, P->inst_nvar[t], &wq, kQuadNnz, kQuadRows, v0);
+            build_tiles_items(hq, t, P->inst_nvar[t], &wq, kQuadNnz, P->qmag ? kQuadBitsRows : kQuadRows, v0);
         }
         build_tiles_items(hv, t, P->inst_nvar[t], nullptr, kVarTile, kVarTile, P->inst_var0[t]);
         for (int part = 0; part < 2; ++part) {
@@ -684,11 +693,12 @@ int gfors_create_problem(const gfors_csr *A, const int64_t *b, const gfors_csr *
         if ((rc = upload(s, P->rowQ, rowQ.data(), P->nnzQ))) return rc;
         P->qpacked = n <= (int64_t{1} << 24) &&
                      std::all_of(valQ.begin(), valQ.end(), [](int v) { return v >= -128 && v <= 127; });
-        std::vector<int> packQ(P->qpacked ? P->nnzQ : 0);
-        for (size_t e = 0; e < packQ.size(); ++e)
+        // one more for the code kernel's padding: value 0 at the first index past the variables' blocks
+        std::vector<int> packQ(P->qpacked ? P->nnzQ + 1 : 0, static_cast<int>(64 * ceil_div(n, 64)));
+        for (int64_t e = 0; e + 1 < static_cast<int64_t>(packQ.size()); ++e)
             packQ[e] = static_cast<int>(static_cast<uint32_t>(ciQ[e]) | static_cast<uint32_t>(valQ[e]) << 24);
-        P->qcode_ok = P->qpacked && P->T == 1 && P->m == 0 && n <= kMaxCodes;
-        if (P->qpacked && (rc = upload(s, P->packQ, packQ.data(), P->nnzQ))) return rc;
+        P->qcode_ok = P->qpacked && P->T == 1 && P->m == 0 && n >= kMinCodes && n <= kMaxCodes;
+        if (P->qpacked && (rc = upload(s, P->packQ, packQ.data(), P->nnzQ + 1))) return rc;
         if ((rc = sync(P))) return rc;
         if (P->qsym) {
             const int64_t nu = static_cast<int64_t>(ciU.size());
@@ -1257,7 +1267,8 @@ int gfors_create_problem(const gfors_csr *A, const int64_t *b, const gfors_csr *
     };
     P->cfg.lpr_dual = pick(m ? static_cast<double>(P->nnzK) / m : 1.0);
     P->cfg.lpr_primal = pick(static_cast<double>(P->nnzK + P->nnzQ) / n);
-    P->qcode_on = P->qcode_ok && P->cfg.lpr_primal <= 16;
+    P->qcode_on = P->qcode_ok && P->nnzQ <= kCodesPerRow * n;
+    if (P->qcode_on) P->cfg.lpr_primal = std::min(P->cfg.lpr_primal, kCodesLanes);
     if (P->slicedK) {
         P->cfg.slices_dual = kXcdSlices;
         P->cfg.lpr_dual = pick(static_cast<double>(P->nnzK) / m / kXcdSlices);
@@ -1789,13 +1800,10 @@ static int autotune(gfors_problem *P, bool with_eval) {
         }
         P->cfg.bits_dual = best_bits;
     }
-    if (!P->res_ok) {
+    if (!P->res_ok && !P->qcode_on) {
         float best = 1e30f;
         float *xs = P->xsave, *xb = reinterpret_cast<float *>(P->pv);
         if (with_eval) launch_fill_share(s, P->wy, 0.5f, 56, P->m);
-        // a quadratic over the box: 45 % of x neither 0 nor 1 (max cut's 50th step)
-        if (with_eval && P->qcode_ok) launch_fill_share(s, P->xbuf[P->cur], 0.5f, 45, P->n);
-        P->qcode_on = false;
         // the dual in use reads the bitmap of xbar / leaves the bitmap of wy
         const bool dual_reads = P->cfg.sell_dual && P->cfg.bits_dual >= 1 && P->cfg.bits_dual <= 3;
         const bool dual_leaves = P->m > 0 && P->cfg.slices_dual > 1;
@@ -1836,13 +1844,6 @@ static int autotune(gfors_problem *P, bool with_eval) {
             P->cfg.bits_primal = b;
             const float t = primal_time(1, 1, 1);
             if (t < best) { best = t; best_bits = b; P->cfg.lpr_primal = 1; P->cfg.slices_primal = 1; P->cfg.sell_primal = 1; }
-        }
-        if (P->qcode_ok) {
-            launch_q_codes(s, static_cast<int>(P->n), P->xbuf[P->cur], P->qcode[0]);
-            for (int l : {1, 2, 4, 8, 16}) {
-                const float t = timeit([&] { launch_codes(P, l, 0, P->xbuf[P->cur], xs, xb, P->ctr_scratch); });
-                if (t < best) { best = t; P->qcode_on = true; P->cfg.lpr_primal = l; }
-            }
         }
         for (int b : {4, 5, 6, 7}) {
             if (!bits_ok_primal(P, 1, 0, b)) continue;
@@ -2016,7 +2017,11 @@ static void enqueue_eval(gfors_problem *P, int K, int threshold, KTimer *tm, int
     launch_eval_general_rows(P, K);
     TE(4);
     TB(5);
-    if (P->hasQ)
+    if (P->hasQ && P->qmag)
+        launch_eval_quad_bits(s, P->qt, P->qsym ? P->rpU : P->rpQ, P->qsym ? P->rowU : P->rowQ,
+                              P->qsym ? P->ciU : P->ciQ, P->qsym ? P->valU : P->valQ, P->X, P->xkind, W, P->qmag,
+                              P->zqpart, K);
+    else if (P->hasQ)
         launch_eval_quad(s, P->qt, P->qsym ? P->rpU : P->rpQ, P->qsym ? P->rowU : P->rowQ,
                          P->qsym ? P->ciU : P->ciQ, P->qsym ? P->valU : P->valQ, P->X, W, P->zqpart, K,
                          P->q24);

@@ -43,6 +43,7 @@ constexpr int kCoverRows = 8192;      // rows per bitwise-evaluated tile (max)
 constexpr int kBitwiseNnz = 8192;     // nnz budget of a bitwise-evaluated tile
 constexpr int kGeneralRows = 4096;    // rows per general tile (max)
 constexpr int kQuadNnz = 4096;        // nnz budget of a Q tile
+constexpr int kQuadBitsRows = 256;     // variables per Q tile (max) when it is evaluated bitwise
 constexpr int kQuadRows = 64;          // variables per Q tile (max): many tiles keep enough wavefronts in flight
 constexpr int kVarTile = 4096;        // variables per FP64 reduction tile
 constexpr int kRowNnz = 16384;        // nnz budget of a residual row tile
@@ -121,6 +122,7 @@ struct gfors_problem {
     int *rowQ = nullptr;   // row of each Q entry (quadratic objective)
     int *packQ = nullptr;  // qpacked: column (24 bits) and value (8) of each Q entry
     bool qpacked = false;
+    int qmag = 0;          // the magnitude that every evaluated Q entry has (0: they differ)
     // one instance without rows, Q packed: codes of x (two bits per variable), the
     // step kernel that uses them applies (qcode_ok), is chosen (qcode_on)
     uint4 *qcode[2] = {nullptr, nullptr};

@@ -243,8 +243,13 @@ __device__ __forceinline__ float primal_update_q(float s2, float ct, float rh, f
     g -= 2.f * rh * xi;
     return fminf(fmaxf(xi - tau1 * g, 0.f), 1.f);
 }
-// The step over codes (two bits per variable) of x: n <= kMaxCodes, lpr <= 16.
-constexpr int64_t kMaxCodes = 128 * 1024 * 4;
+// The step over codes (two bits per variable) of x, up to kCodesLanes lanes per
+// row.  A table that fits in LDS bounds n above; below, its latency does (us a step,
+// this kernel against k_primal, ten entries a row: 5.8 : 4.3 at 50,000 variables,
+// 6.3 : 6.6 at 100,000, 7.7 : 11.3 at 200,000, 17.6 : 25.5 at 500,000).  Longer rows
+// narrow the lead (40 entries: 28 : 36) and leave less to gain from 4 lanes.
+constexpr int64_t kMinCodes = 1 << 17, kMaxCodes = 128 * 1024 * 4, kCodesPerRow = 64;
+constexpr int kCodesLanes = 4;
 void launch_q_codes(hipStream_t s, int n, const float *x, uint4 *codes);
 void launch_primal_codes(hipStream_t s, int lpr, int n, const int *rpQ, const int *packQ, const float *x_in,
                          const uint4 *codes_in, uint4 *codes_out, float *x_out, float *xbar, const float *ct, float tau1,
@@ -438,6 +443,11 @@ void launch_eval_mfma(hipStream_t s, int ntiles, const int *tile_ids, const Tile
                       const int *rows, const int64_t *mf_off, const int *mf_c0, const int *mf_span,
                       const int8_t *dig, const int64_t *rhs, int m1, const uint64_t *X, int W,
                       int *vpart, int K);
+// Entries of one magnitude; at most kQuadBitsMax of them in a tile (16-bit counts).
+constexpr int64_t kQuadBitsMax = 65535;
+void launch_eval_quad_bits(hipStream_t s, const Tiles &qt, const int *rpQ, const int *rowQ, const int *ciQ,
+                           const int *valQ, const uint64_t *X, const uint8_t *xkind, int W, int mag, int64_t *zqpart,
+                           int K);
 void launch_eval_quad(hipStream_t s, const Tiles &qt, const int *rpQ, const int *rowQ,
                       const int *ciQ, const int *valQ, const uint64_t *X, int W, int64_t *zqpart,
                       int K, bool q24);

@@ -410,7 +410,7 @@ void launch_primal(hipStream_t s, int lpr, int kmode, int qmode, bool batched, i
 // wavefront writes the new codes.  The sums are k_primal's, in its order.
 // A step in a replayed run, 200,000 variables: 12.4 us by k_primal with an index
 // and a value per entry loaded one after the other, 10.7 packed and in batches,
-// 6.6 here.  1 to 16 lanes per row are within 5 % of each other.
+// 7.0 here (at 1, 2, 4, 8, 16 lanes per row 9.1, 8.5, 7.7, 8.1, 9.2 late in a run).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void put_codes(uint4 *codes, int blk, bool own, float x) {
     const uint64_t one = __ballot(own && x == 1.f), mid = __ballot(own && x != 0.f && x != 1.f);
@@ -432,7 +432,7 @@ k_primal_codes(int n, const int *__restrict__ rpQ, const int *__restrict__ packQ
                float *__restrict__ xbar, const float *__restrict__ ct, float tau1, float two_so,
                const double *__restrict__ rho, DevCounters *__restrict__ ctr) {
     extern __shared__ uint4 qcodes[];
-    constexpr int U = LPR >= 16 ? 1 : 16 / LPR;   // entries of a row in flight per lane
+    constexpr int U = 16 / LPR;   // entries of a row in flight per lane
     const int lane = threadIdx.x & 63, sub = lane & (LPR - 1);
     const int nblk = (n + 63) >> 6;
     const int blk = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
@@ -443,13 +443,14 @@ k_primal_codes(int n, const int *__restrict__ rpQ, const int *__restrict__ packQ
     const float rh = static_cast<float>(rho[0]);
     int w[LPR][U];
     int e0[LPR], e1[LPR];
+    const int pad = rpQ[n];   // the entry after the last one: value 0 at a variable whose code is 0
 #pragma unroll
     for (int p = 0; p < LPR; ++p) {
         const int src = (lane & ~(LPR - 1)) + p;
         e0[p] = __shfl(r0, src, 64) + sub;
         e1[p] = __shfl(r1, src, 64);
 #pragma unroll
-        for (int u = 0; u < U; ++u) w[p][u] = e0[p] + u * LPR < e1[p] ? packQ[e0[p] + u * LPR] : 0;
+        for (int u = 0; u < U; ++u) w[p][u] = packQ[e0[p] + u * LPR < e1[p] ? e0[p] + u * LPR : pad];
     }
     for (int t0 = threadIdx.x; t0 < nblk; t0 += 4 * blockDim.x) {
         uint4 q[4];
@@ -459,31 +460,34 @@ k_primal_codes(int n, const int *__restrict__ rpQ, const int *__restrict__ packQ
         for (int u = 0; u < 4; ++u)
             if (t0 + u * static_cast<int>(blockDim.x) < nblk) qcodes[t0 + u * blockDim.x] = q[u];
     }
+    if (threadIdx.x == 0) qcodes[nblk] = make_uint4(0, 0, 0, 0);
     __syncthreads();
     if (blk >= nblk) return;
+    // the code's value, or x itself through a buffer load whose offset lies past
+    // the buffer for the others (such a lane makes no request and reads 0)
     const uint2 *half = reinterpret_cast<const uint2 *>(qcodes);
-    auto operand = [&](int word, bool in) {
-        const int c = word & 0xffffff;
+    const auto xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(x_in), 0, n * 4, 0x00027000);
+    auto operand = [&](int word) {
+        const uint32_t c = static_cast<uint32_t>(word) & 0xffffffu;
         const uint2 q = half[c >> 5];
-        float v = (q.x >> (c & 31)) & 1u ? 1.f : 0.f;
-        if (in && ((q.y >> (c & 31)) & 1u)) v = x_in[c];
-        return v;
+        const bool mid = __builtin_amdgcn_ubfe(q.y, c, 1u) != 0;
+        const float g = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xr, mid ? c * 4 : ~3u, 0, 0));
+        return mid ? g : static_cast<float>(__builtin_amdgcn_ubfe(q.x, c, 1u));
     };
     float v[LPR][U];
 #pragma unroll
     for (int p = 0; p < LPR; ++p)
 #pragma unroll
-        for (int u = 0; u < U; ++u) v[p][u] = operand(w[p][u], e0[p] + u * LPR < e1[p]);
+        for (int u = 0; u < U; ++u) v[p][u] = operand(w[p][u]);
     float mine = 0.f;
 #pragma unroll
     for (int p = 0; p < LPR; ++p) {
         float s2 = 0.f;
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (e0[p] + u * LPR < e1[p]) s2 = fmaf(static_cast<float>(w[p][u] >> 24), v[p][u], s2);
+        for (int u = 0; u < U; ++u) s2 = fmaf(static_cast<float>(w[p][u] >> 24), v[p][u], s2);
         for (int e = e0[p] + U * LPR; e < e1[p]; e += LPR) {
             const int word = packQ[e];
-            s2 = fmaf(static_cast<float>(word >> 24), operand(word, true), s2);
+            s2 = fmaf(static_cast<float>(word >> 24), operand(word), s2);
         }
         s2 = group_sum<LPR>(s2);
         if (sub == p) mine = s2;
@@ -509,10 +513,10 @@ void launch_primal_codes(hipStream_t s, int lpr, int n, const int *rpQ, const in
     const int nblk = (n + 63) / 64;
     const int waves = std::max(1, std::min(16, (nblk + 255) / 256));
     const int blocks = (nblk + waves - 1) / waves;
-    const size_t lds = static_cast<size_t>(nblk) * sizeof(uint4);
+    const size_t lds = static_cast<size_t>(nblk + 1) * sizeof(uint4);
     switch (lpr) {
 #define GF_CASE(L) case L: k_primal_codes<L><<<blocks, 64 * waves, lds, s>>>(n, rpQ, packQ, x_in, codes_in, codes_out, x_out, xbar, ct, tau1, two_so, rho, ctr); break;
-        GF_CASE(1) GF_CASE(2) GF_CASE(4) GF_CASE(8) GF_CASE(16)
+        GF_CASE(1) GF_CASE(2) GF_CASE(4)
 #undef GF_CASE
         default: break;
     }

@@ -44,7 +44,9 @@ CASES = {"two": (2, 1, 128, 0), "63": (63, 4, 5, 0), "64": (64, 9, 128, 0), "65"
          "lanes1": (3000, 1.2, 3, 0), "lanes2": (4097, 3, 3, 0), "lanes4": (5000, 6, 128, 0), "lanes8": (16385, 11, 1, 0),
          "lanes16": (7000, 30, 7, 0), "lanes32": (2000, 50, 7, 0), "star": (6000, 5, 4, 5000),
          "int32": (5000, 6, 129, 0), "int32_long": (3000, 30, 100000, 0), "largest": (1 << 19, 4, 2, 0),
-         "beyond": ((1 << 19) + 1, 4, 2, 0)}
+         "beyond": ((1 << 19) + 1, 4, 2, 0), "least": (1 << 17, 1.2, 3, 0), "below": ((1 << 17) - 1, 4, 3, 0),
+         "one_more": ((1 << 17) + 1, 2.5, 128, 0), "ragged": (150063, 10, 1, 0), "long": (140000, 24, 7, 90000),
+         "empty_rows": (200000, 0.2, 9, 40)}
 
 
 @pytest.mark.parametrize("name", list(CASES))
