@@ -33,6 +33,10 @@ __device__ __forceinline__ cptr<T> to_const(const T *p) {
     return reinterpret_cast<cptr<T>>(reinterpret_cast<uintptr_t>(p));
 }
 
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
 __device__ __forceinline__ void philox10(uint32_t &c0, uint32_t &c1, uint32_t &c2,
                                          uint32_t &c3, uint32_t k0, uint32_t k1) {
 #pragma unroll
@@ -41,9 +45,9 @@ __device__ __forceinline__ void philox10(uint32_t &c0, uint32_t &c1, uint32_t &c
         const uint64_t p1 = static_cast<uint64_t>(kPhiloxM1) * c2;
         const uint32_t hi0 = static_cast<uint32_t>(p0 >> 32), lo0 = static_cast<uint32_t>(p0);
         const uint32_t hi1 = static_cast<uint32_t>(p1 >> 32), lo1 = static_cast<uint32_t>(p1);
-        c0 = hi1 ^ c1 ^ k0;
+        c0 = xor3(hi1, c1, k0);
         c1 = lo1;
-        c2 = hi0 ^ c3 ^ k1;
+        c2 = xor3(hi0, c3, k1);
         c3 = lo0;
         k0 += kPhiloxW0;
         k1 += kPhiloxW1;
@@ -65,13 +69,26 @@ __device__ __forceinline__ int64_t readlane64(int64_t x, int v) {
     return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
 }
 
+// z += b c, b in {0, 1}; a 32-bit sum has |c| < 2^23 (the host's choice of ACC)
+__device__ __forceinline__ void add_cost(int32_t &z, uint32_t b, int32_t c) { z += __mul24(static_cast<int>(b), c); }
+__device__ __forceinline__ void add_cost(int64_t &z, uint32_t b, int64_t c) { z += b ? c : 0; }
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_bits(uint32_t v) {
+    return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, 0xf, 0xf, true));
+}
+
 // A workgroup samples one tile of variables, 64 variables (a sub-tile) at a
 // time.  Every wavefront loads the sub-tile's p and costs itself (lane =
 // variable, one sub-tile ahead), so the variables' kinds are wave-uniform
 // ballots: the candidate loop visits only the fractional variables, whose
 // threshold and cost come from their lane.  The four wavefronts split the
-// candidate groups (4 candidates per Philox call); a lane's 4 bits and its
-// neighbour's form one byte of the variable's row in LDS.  Rows of
+// candidate groups (4 candidates per Philox call), and up to 512 candidates
+// the variables too; four lanes' bits form 16 bits of the variable's row in LDS.
+// Bound by the vector ALU: 15 of a call's 64-bit multiplies (quarter rate) are
+// left after what depends on the candidate or the variable alone, so the rest is
+// kept short (three-way xors, unshifted thresholds, bits merged across lanes
+// without LDS).  600,000 variables x 4096: 749 -> 581 us (307 MB written); 200 x
+// 256: 13.9 -> 7.9.  Rows of
 // deterministic variables are written as constants during the copy-out.  The
 // LDS rows are double-buffered (one barrier per sub-tile) when two buffers fit.
 template <typename ACC>
@@ -92,10 +109,14 @@ k_sample(const float *__restrict__ p, const int64_t *__restrict__ cost,
     const uint32_t round = static_cast<uint32_t>(ctr->round);
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    // candidate groups (4 candidates each) of this wavefront: [gb, ge)
+    // candidate groups (4 candidates each) of this wavefront: [gb, ge); up to 256
+    // (512) candidates fill one (two) wavefronts, and the others take every
+    // fourth (second) variable
     const int G4 = K >> 2;
-    const int per = G4 >> 2;            // K is a multiple of 64, so per is a multiple of 4
-    const int gb = wave * per, ge = gb + per;
+    const int nw = G4 <= 64 ? 1 : (G4 <= 128 ? 2 : 4), sets = 4 / nw, set = wave / nw;
+    const int per = G4 / nw;            // K is a multiple of 64, so per is a multiple of 4
+    const int gb = (wave & (nw - 1)) * per, ge = gb + per;
+    const uint64_t mine = (sets == 1 ? ~0ull : sets == 2 ? 0x5555555555555555ull : 0x1111111111111111ull) << set;
     constexpr int SMAX = 4;             // groups per lane: per <= 256 (K <= 4096)
     ACC zacc[SMAX][4];
 #pragma unroll
@@ -142,11 +163,12 @@ k_sample(const float *__restrict__ p, const int64_t *__restrict__ cost,
         }
         uint64_t *rows = lds + (nbuf == 2 ? buf : 0) * bufw;
         uint8_t *lrow = reinterpret_cast<uint8_t *>(rows);
-        uint64_t fm = fmask;
+        uint64_t fm = fmask & mine;
         while (fm) {                                              // uniform
             const int v = __builtin_ctzll(fm);
             fm &= fm - 1;
-            const uint32_t thv = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(th), v));
+            // (U >> 8) < th  <=>  U < th << 8: a fractional variable's th is below 2^24
+            const uint32_t thv = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(th), v)) << 8;
             const ACC c = static_cast<ACC>(readlane64(cv, v));
             const uint32_t il = static_cast<uint32_t>(il0 + v);
 #pragma unroll
@@ -155,16 +177,17 @@ k_sample(const float *__restrict__ p, const int64_t *__restrict__ cost,
                 if (64 * t >= per) break;                          // uniform
                 uint32_t r0 = static_cast<uint32_t>(g), r1 = il, r2 = round, r3 = static_cast<uint32_t>(inst);
                 philox10(r0, r1, r2, r3, key0, key1);
-                const uint32_t b0 = (r0 >> 8) < thv, b1 = (r1 >> 8) < thv;
-                const uint32_t b2 = (r2 >> 8) < thv, b3 = (r3 >> 8) < thv;
-                if (b0) zacc[t][0] += c;
-                if (b1) zacc[t][1] += c;
-                if (b2) zacc[t][2] += c;
-                if (b3) zacc[t][3] += c;
-                const uint32_t nib = b0 | (b1 << 1) | (b2 << 2) | (b3 << 3);
-                const uint32_t other = __shfl_xor(nib, 1, 64);
-                if (g < ge && (g & 1) == 0)
-                    lrow[static_cast<size_t>(v) * W * 8 + (g >> 1)] = static_cast<uint8_t>(nib | (other << 4));
+                const uint32_t b0 = r0 < thv, b1 = r1 < thv, b2 = r2 < thv, b3 = r3 < thv;
+                add_cost(zacc[t][0], b0, c);
+                add_cost(zacc[t][1], b1, c);
+                add_cost(zacc[t][2], b2, c);
+                add_cost(zacc[t][3], b3, c);
+                // four lanes' bits (gb and 64 t are multiples of 4) in one 16-bit store
+                uint32_t w = (b0 | (b1 << 1) | (b2 << 2) | (b3 << 3)) << (4 * (lane & 3));
+                w |= dpp_bits<0xb1>(w);
+                w |= dpp_bits<0x4e>(w);
+                if ((lane & 3) == 0 && g < ge)
+                    *reinterpret_cast<uint16_t *>(lrow + static_cast<size_t>(v) * W * 8 + (g >> 1)) = static_cast<uint16_t>(w);
             }
         }
         __syncthreads();
@@ -177,6 +200,20 @@ k_sample(const float *__restrict__ p, const int64_t *__restrict__ cost,
         }
         if (nbuf == 2) buf ^= 1;
         else __syncthreads();
+    }
+    if (sets > 1) {   // per <= 64: one group of candidates per lane and variable set
+        ACC *part = reinterpret_cast<ACC *>(lds);   // [sets][K]
+        __syncthreads();
+        if (lane < per)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) part[set * K + 4 * (gb + lane) + j] = zacc[0][j];
+        __syncthreads();
+        for (int l = threadIdx.x; l < K; l += 256) {
+            ACC z = zconst;
+            for (int q = 0; q < sets; ++q) z += part[q * K + l];
+            zpart[static_cast<int64_t>(tile) * K + l] = static_cast<int64_t>(z);
+        }
+        return;
     }
 #pragma unroll
     for (int t = 0; t < SMAX; ++t) {
@@ -547,7 +584,8 @@ void launch_sample(hipStream_t s, int W, bool obj64, const float *p, const int64
     const uint64_t wdiv = ((1ull << 32) + static_cast<uint64_t>(W) - 1) / static_cast<uint64_t>(W);
     const size_t one = static_cast<size_t>(64) * W * sizeof(uint64_t);
     const int nbuf = 2 * one <= 32 * 1024 ? 2 : 1;
-    const size_t lds = nbuf * one;
+    // up to 512 candidates: room for the variable sets' sums at the end
+    const size_t lds = std::max<size_t>(nbuf * one, K <= 512 ? 4 * static_cast<size_t>(K) * (obj64 ? 8 : 4) : 0);
     if (obj64)
         k_sample<int64_t><<<st.count, 256, lds, s>>>(p, cost, X, W, st.inst, st.b0, st.b1, inst_var0, inst_nvar, zpart, K, key0, key1, ctr, threshold_mode, xkind, wdiv, nbuf);
     else
