@@ -1123,7 +1123,7 @@ int gfors_create_problem(const gfors_csr *A, const int64_t *b, const gfors_csr *
             int dev = 0, lds_max = 0;
             HIP_TRY(hipGetDevice(&dev));
             HIP_TRY(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-            P->lds_slice = primal_lds_slice(static_cast<size_t>(lds_max));
+            P->lds_slice = primal_lds_slice(static_cast<size_t>(lds_max), m);
         }
         auto classes = [](const std::vector<int> &o, const std::vector<int> &ptr, int64_t cnt, int &h, int &md) {
             int64_t k = 0;
@@ -1722,8 +1722,8 @@ static void launch_codes(gfors_problem *P, int lpr, int from, const float *x_in,
 // this problem's own data (HIP events, 1 warm-up + 5 timed launches each) and
 // keep the fastest.  Outputs go to buffers that carry no state at this point.
 // At creation (with_eval) the vectors hold a stand-in for an iterate under way
-// (15 % of xbar and 56 % of wy nonzero, the shares measured on the large set
-// cover): at x = 0, y = 0 the zero-skipping shapes cannot be told apart from
+// (15 % of xbar and 56 % of wy nonzero, the shares that the large set cover settles
+// at): at x = 0, y = 0 the zero-skipping shapes cannot be told apart from
 // the others, and on that problem the choice cost 45 us against 38 per primal
 // step.  A shape pays for the bitmap pass that it makes the step run.
 static int autotune(gfors_problem *P, bool with_eval) {
@@ -1804,6 +1804,7 @@ static int autotune(gfors_problem *P, bool with_eval) {
         float best = 1e30f;
         float *xs = P->xsave, *xb = reinterpret_cast<float *>(P->pv);
         if (with_eval) launch_fill_share(s, P->wy, 0.5f, 56, P->m);
+        if (P->m > 0 && P->by) launch_nzbits(s, P->wy, P->m, ceil_div(P->m, 64), P->by);   // for shapes after a dual that leaves it
         // the dual in use reads the bitmap of xbar / leaves the bitmap of wy
         const bool dual_reads = P->cfg.sell_dual && P->cfg.bits_dual >= 1 && P->cfg.bits_dual <= 3;
         const bool dual_leaves = P->m > 0 && P->cfg.slices_dual > 1;
@@ -1845,11 +1846,33 @@ static int autotune(gfors_problem *P, bool with_eval) {
             const float t = primal_time(1, 1, 1);
             if (t < best) { best = t; best_bits = b; P->cfg.lpr_primal = 1; P->cfg.slices_primal = 1; P->cfg.sell_primal = 1; }
         }
-        for (int b : {4, 5, 6, 7}) {
+        for (int b : {5, 6, 7}) {
             if (!bits_ok_primal(P, 1, 0, b)) continue;
             P->cfg.bits_primal = b;
             const float t = primal_time(1, 1, 0);
             if (t < best) { best = t; best_bits = b; P->cfg.lpr_primal = 1; P->cfg.slices_primal = 1; P->cfg.sell_primal = 0; }
+        }
+        if (P->n >= 256 * 1024 && bits_ok_primal(P, 1, 0, 4)) {   // a workgroup of it per CU
+            // staged slices against the best of the others, each after a dual step: alone
+            // their caches stay warm (600,000 variables of 3 rows: ahead alone, but
+            // 22.0 us a step against 20.8)
+            auto behind_dual = [&](int l, int sl, int se, int bits) {
+                P->cfg.bits_primal = bits;
+                return timeit([&] {
+                    launch_dual_cfg(P, P->cfg.lpr_dual, P->cfg.slices_dual, P->cfg.sell_dual, P->ybuf[P->cur],
+                                    P->ybuf[1 - P->cur]);
+                    if (with_eval) launch_fill_share(s, P->wy, 0.5f, 56, P->m);
+                    launch_nzbits(s, P->wy, P->m, ceil_div(P->m, 64), P->by);
+                    P->by_fresh = true;
+                    launch_primal_cfg(P, l, sl, se, P->xbuf[P->cur], xs, xb, P->ctr_scratch);
+                });
+            };
+            const float other = behind_dual(P->cfg.lpr_primal, P->cfg.slices_primal, P->cfg.sell_primal, best_bits);
+            if (behind_dual(1, 1, 0, 4) < other) {
+                best_bits = 4;
+                P->cfg.lpr_primal = P->cfg.slices_primal = 1;
+                P->cfg.sell_primal = 0;
+            }
         }
         P->cfg.bits_primal = best_bits;
     }

@@ -369,7 +369,7 @@ void launch_primal_block(hipStream_t s, const BlockView &b, const int *rp, const
 // Primal step with wy staged in LDS slices of SL rows (unit coefficients,
 // every variable in deg <= 8 rows, one instance, no Q); ell[u n + i] = the
 // u-th row of variable i (ascending).  Returns false for an unsupported deg.
-int primal_lds_slice(size_t lds_limit);
+int primal_lds_slice(size_t lds_limit, int64_t m);
 // Light rows / variables [i0, i0 + L) of D <= 8 entries each, indices entry-major
 // with the coefficient's sign (|a| = 1) in bit 31; one instance, no Q.  xbits:
 // nonzero bitmap of xbar (only when the range is every variable), or null.
