@@ -335,7 +335,13 @@ int gfors_read_throughput(void *hip_stream, const void *dev_buf, int64_t bytes, 
  * whose rows are those of the group's first variable shifted by their
  * distance to it (same coefficients): the 16 variables of a group read wy of
  * one entry as 16 consecutive floats (their sums are added in another order
- * than with a workgroup per variable). */
+ * than with a workgroup per variable).
+ * Two forms stand outside the eight entries and use only their lanes: runs of
+ * steps in one launch where every instance fits a workgroup (Q = 0), and steps
+ * over two-bit codes of x for one instance without rows, a symmetric Q of 8-bit
+ * values and 131,072 to 524,288 variables.  Both add the same terms in the same
+ * order as the launches described here, which gfors_set_launch_cfg and
+ * gfors_kernel_times use instead. */
 int gfors_get_launch_cfg(gfors_problem *P, int32_t *out);
 
 /* Re-run the autotuner on the current iterate (the zero-operand bitmap

@@ -81,9 +81,7 @@ static size_t carve(gfors_problem *P, Carver &cv, int64_t n, int64_t m1, int64_t
     P->rpQ = cv.take<int>(n + 1);
     P->ciQ = cv.take<int>(nnzQ);
     P->valQ = cv.take<int>(nnzQ);
-    P->rowQ = cv.take<int>(nnzQ);
-    P->packQ = cv.take<int>(nnzQ ? nnzQ + 1 : 0);
-    for (uint4 *&q : P->qcode) q = cv.take<uint4>(nnzQ && m == 0 ? (n + 63) / 64 : 0);
+    P->rowQ = P->packQ = cv.take<int>(nnzQ ? nnzQ + 1 : 0);   // one or the other
     P->rpU = cv.take<int>(nnzQ ? n + 1 : 1);
     P->ciU = cv.take<int>(nnzQ);
     P->valU = cv.take<int>(nnzQ);
@@ -687,11 +685,11 @@ int gfors_create_problem(const gfors_csr *A, const int64_t *b, const gfors_csr *
         if ((rc = upload(s, P->rpQ, rpQ.data(), n + 1))) return rc;
         if ((rc = upload(s, P->ciQ, ciQ.data(), P->nnzQ))) return rc;
         if ((rc = upload(s, P->valQ, valQ.data(), P->nnzQ))) return rc;
-        std::vector<int> rowQ(P->nnzQ);
-        for (int64_t i = 0; i < n; ++i)
+        std::vector<int> rowQ(P->qsym ? 0 : P->nnzQ);   // evaluated entries' rows (a symmetric Q: rowU)
+        for (int64_t i = 0; i < n && !P->qsym; ++i)
             for (int e = rpQ[i]; e < rpQ[i + 1]; ++e) rowQ[e] = static_cast<int>(i);
-        if ((rc = upload(s, P->rowQ, rowQ.data(), P->nnzQ))) return rc;
-        P->qpacked = n <= (int64_t{1} << 24) &&
+        if (!P->qsym && (rc = upload(s, P->rowQ, rowQ.data(), P->nnzQ))) return rc;
+        P->qpacked = P->qsym && n <= (int64_t{1} << 24) &&
                      std::all_of(valQ.begin(), valQ.end(), [](int v) { return v >= -128 && v <= 127; });
         // one more for the code kernel's padding: value 0 at the first index past the variables' blocks
         std::vector<int> packQ(P->qpacked ? P->nnzQ + 1 : 0, static_cast<int>(64 * ceil_div(n, 64)));
@@ -1259,6 +1257,10 @@ int gfors_create_problem(const gfors_csr *A, const int64_t *b, const gfors_csr *
     launch_fill_f32(s, reinterpret_cast<float *>(P->bx), 0.f, 2 * P->bx_words);
     launch_fill_f32(s, reinterpret_cast<float *>(P->by), 0.f, 2 * P->by_words);
     HIP_TRY(hipGetLastError());
+    if (P->qcode_ok) {   // in a vector of the power iteration (8 n bytes; two tables take n / 2)
+        P->qcode[0] = reinterpret_cast<uint4 *>(P->pu);
+        P->qcode[1] = P->qcode[0] + ceil_div(n, 64);
+    }
     // launch shapes: lanes per row ~ average row length (rounded to a power of two)
     auto pick = [](double avg) {
         int l = 1;

@@ -119,8 +119,8 @@ struct gfors_problem {
     int *rp = nullptr, *ci = nullptr, *val = nullptr;
     int *rpT = nullptr, *ciT = nullptr, *valT = nullptr;
     int *rpQ = nullptr, *ciQ = nullptr, *valQ = nullptr;
-    int *rowQ = nullptr;   // row of each Q entry (quadratic objective)
-    int *packQ = nullptr;  // qpacked: column (24 bits) and value (8) of each Q entry
+    int *rowQ = nullptr;   // row of each Q entry (quadratic objective; Q not symmetric)
+    int *packQ = nullptr;  // qpacked: column (24 bits) and value (8) of each Q entry, in rowQ's place
     bool qpacked = false;
     int qmag = 0;          // the magnitude that every evaluated Q entry has (0: they differ)
     // one instance without rows, Q packed: codes of x (two bits per variable), the

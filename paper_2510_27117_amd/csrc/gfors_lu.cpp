@@ -167,10 +167,10 @@ size_t lu_carve(gfors_problem *P, Carver &cv, const gftu::TuFactored &F, const g
         ds[q]->ent = cv.take<int>(static_cast<int64_t>(hs[q]->ent.size()));
         ds[q]->lvl = cv.take<int>(static_cast<int64_t>(hs[q]->lvl.size()));
     }
-    L.v64 = cv.take<double>(r);
-    L.t64 = cv.take<double>(r);
     L.w64a = cv.take<double>(nfull);
     L.w64b = cv.take<double>(nfull);
+    L.v64 = L.w64a;   // a step is done with these before its residuals need the vectors
+    L.t64 = L.w64b;
     L.w64c = cv.take<double>(nfull);
     L.XI = cv.take<int>(r * prm.K_max);
     L.rhs_orig = cv.take<int64_t>(m);
