@@ -1863,14 +1863,18 @@ static int autotune(gfors_problem *P, bool with_eval) {
                 return timeit([&] {
                     launch_dual_cfg(P, P->cfg.lpr_dual, P->cfg.slices_dual, P->cfg.sell_dual, P->ybuf[P->cur],
                                     P->ybuf[1 - P->cur]);
-                    if (with_eval) launch_fill_share(s, P->wy, 0.5f, 56, P->m);
-                    launch_nzbits(s, P->wy, P->m, ceil_div(P->m, 64), P->by);
-                    P->by_fresh = true;
+                    P->by_fresh = dual_leaves;
+                    if (with_eval) {
+                        launch_fill_share(s, P->wy, 0.5f, 56, P->m);
+                        launch_nzbits(s, P->wy, P->m, ceil_div(P->m, 64), P->by);
+                        P->by_fresh = true;
+                    }
                     launch_primal_cfg(P, l, sl, se, P->xbuf[P->cur], xs, xb, P->ctr_scratch);
                 });
             };
             const float other = behind_dual(P->cfg.lpr_primal, P->cfg.slices_primal, P->cfg.sell_primal, best_bits);
-            if (behind_dual(1, 1, 0, 4) < other) {
+            // clearly ahead: the passes over wy above favour the staged form a little
+            if (behind_dual(1, 1, 0, 4) < 0.96f * other) {
                 best_bits = 4;
                 P->cfg.lpr_primal = P->cfg.slices_primal = 1;
                 P->cfg.sell_primal = 0;
