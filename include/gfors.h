@@ -311,7 +311,7 @@ int gfors_read_throughput(void *hip_stream, const void *dev_buf, int64_t bytes, 
 /* Launch shapes in use: out[8] = {lanes per row of the dual SpMV, lanes per row
  * of the primal SpMV, column slices of the dual SpMV, slices of the primal,
  * SELL-64 layout for the dual (0/1), SELL-64 layout for the primal (0/1),
- * zero-operand skipping / layout variant of the dual (0..5), of the primal (0..7)}
+ * zero-operand skipping / layout variant of the dual (0..6), of the primal (0..9)}
  * (1 slice = fused kernel; with SELL the lanes-per-row entry is unused; dual
  * lanes per row 256 = a workgroup per row, longest rows first).  Skipping
  * keeps the nonzero bitmap of the gathered vector in LDS and issues only the
@@ -336,18 +336,18 @@ int gfors_read_throughput(void *hip_stream, const void *dev_buf, int64_t bytes, 
  * distance to it (same coefficients): the 16 variables of a group read wy of
  * one entry as 16 consecutive floats (their sums are added in another order
  * than with a workgroup per variable).
- * Two forms stand outside the eight entries and use only their lanes: runs of
- * steps in one launch where every instance fits a workgroup (Q = 0), and steps
+ * Dual 6 with primal 8 = runs of steps in one launch where every instance fits
+ * a workgroup (Q = 0), with the lanes of the first two entries; primal 9 = steps
  * over two-bit codes of x for one instance without rows, a symmetric Q of 8-bit
- * values and 131,072 to 524,288 variables.  Both add the same terms in the same
- * order as the launches described here, which gfors_set_launch_cfg and
- * gfors_kernel_times use instead. */
+ * values and 131,072 to 524,288 variables, on 1, 2 or 4 lanes.  Both add the
+ * same terms in the same order as the launches of the same lanes (dual 4 /
+ * primal 5 where rows are dense with 16-bit coefficients, else 0 / 0). */
 int gfors_get_launch_cfg(gfors_problem *P, int32_t *out);
 
 /* Re-run the autotuner on the current iterate (the zero-operand bitmap
  * variants only show their speed once x and y have reached the box bounds /
- * inactive duals).  The timed launches write no state.  Synchronises; drops
- * captured graphs. */
+ * inactive duals).  It chooses among all forms, whatever was set before.  The
+ * timed launches write no state.  Synchronises; drops captured graphs. */
 int gfors_autotune(gfors_problem *P);
 
 /* Force launch shapes (same 8-entry layout as gfors_get_launch_cfg).  Lanes per
@@ -357,7 +357,9 @@ int gfors_autotune(gfors_problem *P);
  * holds the SELL copy; skipping 1 only for the sliced SELL dual / the fused CSR
  * primal, 2 and 3 only with a SELL layout, all without Q and with bitmaps of at most
  * 64 KB; primal 4 to 7 and dual 4, 5 only with 1 slice, no SELL, and where the
- * problem qualifies.
+ * problem qualifies; dual 6 and primal 8 only together, and primal 9, likewise.
+ * What gfors_get_launch_cfg returned can be set again, on the same problem or on
+ * another that qualifies, and keeps its form.
  * E_ARG otherwise (nothing is changed).  Drops captured graphs. */
 int gfors_set_launch_cfg(gfors_problem *P, const int32_t *cfg);
 

@@ -280,6 +280,7 @@ static void launch_eval_general_rows(gfors_problem *P, int K);
 static int setup_resident(gfors_problem *P, const std::vector<int64_t> &off, const std::vector<int> &rp,
                           const std::vector<int> &rpT);
 static void resident_cfg(gfors_problem *P);
+static void codes_cfg(gfors_problem *P);
 static int setup_repair(gfors_problem *P, const gfors_csr *A, const int64_t *b, const gfors_csr *B,
                         const gfors_csr *Q, const int64_t *c);
 
@@ -1269,8 +1270,8 @@ int gfors_create_problem(const gfors_csr *A, const int64_t *b, const gfors_csr *
     };
     P->cfg.lpr_dual = pick(m ? static_cast<double>(P->nnzK) / m : 1.0);
     P->cfg.lpr_primal = pick(static_cast<double>(P->nnzK + P->nnzQ) / n);
-    P->qcode_on = P->qcode_ok && P->nnzQ <= kCodesPerRow * n;
-    if (P->qcode_on) P->cfg.lpr_primal = std::min(P->cfg.lpr_primal, kCodesLanes);
+    P->qcode_pays = P->qcode_ok && P->nnzQ <= kCodesPerRow * n;
+    if (P->qcode_pays) codes_cfg(P);
     if (P->slicedK) {
         P->cfg.slices_dual = kXcdSlices;
         P->cfg.lpr_dual = pick(static_cast<double>(P->nnzK) / m / kXcdSlices);
@@ -1346,6 +1347,16 @@ static void resident_cfg(gfors_problem *P) {
     P->cfg.lpr_dual = std::min(P->cfg.lpr_dual, 64);
     P->cfg.lpr_primal = std::min(P->cfg.lpr_primal, 64);
     P->res_on = true;
+}
+
+// Steps over codes of x, at the lanes that the mean row asks for.
+static void codes_cfg(gfors_problem *P) {
+    P->cfg.slices_primal = 1;
+    P->cfg.sell_primal = P->cfg.bits_primal = 0;
+    int l = 1;
+    while (l < kCodesLanes && 2 * l * P->n <= P->nnzQ) l *= 2;
+    P->cfg.lpr_primal = l;
+    P->qcode_on = true;
 }
 
 // nsteps steps from the buffers of parity `a` on the resident path, into the
@@ -1746,6 +1757,7 @@ static int autotune(gfors_problem *P, bool with_eval) {
     const int lprs[] = {1, 2, 4, 8, 16, 32, 64};
     P->cfg.bits_dual = P->cfg.bits_primal = 0;
     P->bx_fresh = P->by_fresh = false;
+    if (P->qcode_pays) codes_cfg(P);   // by rule, also where launches of k_primal were asked for before
     if (P->res_ok) {
         // lanes per row, then lanes per variable, of the resident steps
         resident_cfg(P);
@@ -2440,8 +2452,8 @@ int gfors_get_launch_cfg(gfors_problem *P, int32_t *out) {
     out[3] = P->cfg.slices_primal;
     out[4] = P->cfg.sell_dual;
     out[5] = P->cfg.sell_primal;
-    out[6] = P->cfg.bits_dual;
-    out[7] = P->cfg.bits_primal;
+    out[6] = P->res_on ? kCfgRunDual : P->cfg.bits_dual;
+    out[7] = P->res_on ? kCfgRunPrimal : P->qcode_on ? kCfgCodes : P->cfg.bits_primal;
     return GFORS_OK;
 }
 
@@ -2449,6 +2461,27 @@ int gfors_set_launch_cfg(gfors_problem *P, const int32_t *cfg) {
     if (!P || !cfg) return fail(GFORS_E_ARG, "bad argument");
     if (P->lu) return fail(GFORS_E_ARG, "not available on a factorised TU problem");
     auto pow2 = [](int v) { return v >= 1 && v <= 64 && (v & (v - 1)) == 0; };
+    const bool plain_layout = cfg[2] == 1 && cfg[3] == 1 && cfg[4] == 0 && cfg[5] == 0;
+    if (cfg[6] == kCfgRunDual || cfg[7] == kCfgRunPrimal) {
+        if (!(P->res_ok && cfg[6] == kCfgRunDual && cfg[7] == kCfgRunPrimal && plain_layout && pow2(cfg[0]) && pow2(cfg[1])))
+            return fail(GFORS_E_ARG, "dual 6 and primal 8 (runs of steps in one launch) go together, with 1 slice, no SELL and lanes "
+                                     "a power of two in [1, 64], where every instance fits a workgroup");
+        P->cfg.lpr_dual = cfg[0];
+        P->cfg.lpr_primal = cfg[1];
+        resident_cfg(P);
+        P->graphs_clear();
+        return GFORS_OK;
+    }
+    if (cfg[7] == kCfgCodes) {
+        if (!(P->qcode_ok && plain_layout && cfg[6] == 0 && pow2(cfg[0]) && pow2(cfg[1]) && cfg[1] <= kCodesLanes))
+            return fail(GFORS_E_ARG, "primal 9 (steps over codes of x) needs one instance without rows, a symmetric Q of 8-bit values, "
+                                     "131,072 to 524,288 variables, 1 slice, no SELL and 1, 2 or 4 lanes");
+        codes_cfg(P);
+        P->cfg.lpr_dual = cfg[0];
+        P->cfg.lpr_primal = cfg[1];
+        P->graphs_clear();
+        return GFORS_OK;
+    }
     const bool fused_dual = cfg[2] == 1 && cfg[4] == 0 && cfg[6] == 0;
     const bool block_dual = fused_dual && (cfg[0] == kLprBlock || pow2(cfg[0] - kLprBlock));
     const bool block_primal = cfg[3] == 1 && cfg[5] == 0 && cfg[7] == 0 && !P->hasQ && P->m > 0 &&

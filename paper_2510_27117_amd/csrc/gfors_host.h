@@ -48,6 +48,9 @@ constexpr int kQuadRows = 64;          // variables per Q tile (max): many tiles
 constexpr int kVarTile = 4096;        // variables per FP64 reduction tile
 constexpr int kRowNnz = 16384;        // nnz budget of a residual row tile
 constexpr int kRowRows = 2048;
+// entries of a launch configuration that stand for a whole form of the steps
+constexpr int kCfgRunDual = 6, kCfgRunPrimal = 8;   // runs of steps in one launch
+constexpr int kCfgCodes = 9;                        // steps over codes of x
 constexpr int kStepChunk = 32;         // steps per captured graph of gfors_pdhg_steps (even)
 constexpr int kMfmaRows = 32;          // rows per dense digit block (one 32 x 32 matrix-core tile)
 constexpr int kMfmaMaxSpan = 1 << 23;  // column span of a block: keeps int32 plane sums exact
@@ -124,9 +127,10 @@ struct gfors_problem {
     bool qpacked = false;
     int qmag = 0;          // the magnitude that every evaluated Q entry has (0: they differ)
     // one instance without rows, Q packed: codes of x (two bits per variable), the
-    // step kernel that uses them applies (qcode_ok), is chosen (qcode_on)
+    // step kernel that uses them applies (qcode_ok), is the faster one by its
+    // rule (qcode_pays), is in use (qcode_on)
     uint4 *qcode[2] = {nullptr, nullptr};
-    bool qcode_ok = false, qcode_on = false;
+    bool qcode_ok = false, qcode_pays = false, qcode_on = false;
     // the objective's evaluation over the upper triangle of a symmetric Q:
     // entries (i, k) with k > i doubled, the diagonal once
     bool qsym = false;

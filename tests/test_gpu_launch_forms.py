@@ -1,0 +1,133 @@
+"""The form of the steps that a launch configuration stands for: runs of steps in
+one launch (dual 6 / primal 8), steps over codes of x (primal 9), and the launches
+whose sums both reproduce.  A configuration that was read keeps its form when it
+is set, on the same problem or another one; the forms agree in every bit."""
+import numpy as np
+import pytest
+
+from paper_2510_27117_amd import instances as I
+from tests.test_gpu_q_codes import CASES, _box
+from tests.test_gpu_resident import NAMES, _problems
+
+pytestmark = pytest.mark.gpu
+
+RUN, CODES = (6, 8), (0, 9)
+
+
+@pytest.fixture(scope="module")
+def G():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2510_27117_amd import gfors
+    return gfors
+
+
+def _form(p):
+    c = p.launch_cfg()
+    return c["bits_dual"], c["bits_primal"]
+
+
+def _with(cfg, bits_dual, bits_primal, **more):
+    return {**cfg, "bits_dual": bits_dual, "bits_primal": bits_primal, **more}
+
+
+def _problem(kind):
+    if kind == "run":
+        return I.set_cover_bernoulli(200, 100, 0.05, seed=0), RUN
+    return _box(140000, 8, 3, 3), CODES
+
+
+@pytest.mark.parametrize("kind", ["run", "codes"])
+@pytest.mark.parametrize("tuned", [0, 1])
+def test_a_configuration_that_was_read_keeps_its_form(G, kind, tuned):
+    P, form = _problem(kind)
+    p = G.Problem(P, G.default_params(k_int=10, K_max=64, power_iters=20, autotune=tuned))
+    cfg = p.launch_cfg()
+    assert (cfg["bits_dual"], cfg["bits_primal"]) == form
+    p.set_launch_cfg(**cfg)
+    assert p.launch_cfg() == cfg
+    other = G.Problem(P, G.default_params(k_int=10, K_max=64, power_iters=20, autotune=0))
+    other.set_launch_cfg(**_with(cfg, 0, 0))             # launches, asked for by name
+    assert other.launch_cfg() == _with(cfg, 0, 0)
+    other.set_launch_cfg(**cfg)                          # a stored configuration brings its form along
+    assert other.launch_cfg() == cfg
+    other.set_launch_cfg(**_with(cfg, 0, 0))
+    other.autotune()
+    assert _form(other) == form
+    p.close()
+    other.close()
+
+
+def test_forms_are_refused_where_they_do_not_apply(G):
+    run, _ = _problem("run")
+    codes, _ = _problem("codes")
+    large = I.set_cover_columns(60_000, 6_000, 4, seed=1)
+    prm = G.default_params(k_int=10, K_max=64, power_iters=20, autotune=0)
+    for P, cfgs in ((run, [(4, 4, 1, 1, 0, 0, 6, 0), (4, 4, 1, 1, 0, 0, 0, 8), (3, 4, 1, 1, 0, 0, 6, 8),
+                           (256, 4, 1, 1, 0, 0, 6, 8), (4, 4, 1, 1, 1, 0, 6, 8), (4, 4, 1, 1, 0, 0, 0, 9),
+                           (4, 4, 1, 1, 0, 0, 7, 0), (4, 4, 1, 1, 0, 0, 0, 10)]),
+                    (codes, [(1, 8, 1, 1, 0, 0, 0, 9), (1, 4, 1, 1, 0, 0, 6, 9), (1, 4, 1, 1, 0, 0, 6, 8)]),
+                    (large, [(4, 4, 1, 1, 0, 0, 6, 8), (4, 4, 1, 1, 0, 0, 0, 9)])):
+        p = G.Problem(P, prm)
+        before = p.launch_cfg()
+        for cfg in cfgs:
+            with pytest.raises(G.GforsError):
+                p.set_launch_cfg(*cfg)
+            assert p.launch_cfg() == before
+        p.close()
+
+
+@pytest.mark.parametrize("name", NAMES + ["dense%d" % k for k in range(7)])
+def test_run_of_steps_equals_its_launches(G, name):
+    """Against the launches of the same lanes, from a state with every dual at work."""
+    P = _problems()[name]
+    prm = G.default_params(k_int=7, K_max=64, autotune=0)
+    a, b = G.Problem(P, prm), G.Problem(P, prm)
+    cfg = a.launch_cfg()
+    a.set_launch_cfg(**_with(cfg, *RUN))
+    # dense rows of 16-bit coefficients: the dense-block tiles, else lanes per row / variable
+    b.set_launch_cfg(**_with(cfg, *((4, 5) if name.startswith("dense") and name != "dense_int32" else (0, 0))))
+    assert _form(a) == RUN and _form(b) != RUN
+    rng = np.random.default_rng(5)
+    x, xp = rng.random(P.n), rng.random(P.n)
+    y = rng.standard_normal(P.m1 + P.m2)
+    y[: P.m1] = np.maximum(y[: P.m1], 0.0)
+    for q in (a, b):
+        q.set_state(x, xp, y, 0.05)
+    for steps, res in ((1, False), (2, True), (7, False), (1, True), (40, False)):
+        for q in (a, b):
+            q.pdhg_steps(steps, want_residuals=res)
+        sa, sb = a.get_state(), b.get_state()
+        for k in ("x", "x_prev", "y"):
+            assert np.array_equal(sa[k], sb[k]), (steps, k)
+        assert sa["k"] == sb["k"]
+        if res:
+            assert np.array_equal(a.residuals(), b.residuals())
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("name", ["largest", "least", "one_more", "ragged", "long", "empty_rows"])
+@pytest.mark.parametrize("lanes", [1, 2, 4])
+def test_codes_equal_the_kernel_that_gathers(G, name, lanes):
+    n, degree, vmax, star = CASES[name]
+    P = _box(n, degree, vmax, 3, star)
+    prm = G.default_params(k_int=7, K_max=64, autotune=0, power_iters=5)
+    a, b = G.Problem(P, prm), G.Problem(P, prm)
+    a.set_launch_cfg(1, lanes, 1, 1, 0, 0, *CODES)
+    b.set_launch_cfg(1, lanes, 1, 1, 0, 0, 0, 0)
+    assert _form(a) == CODES and _form(b) == (0, 0)
+    rng = np.random.default_rng(7)
+    x, xp = np.clip(rng.random(n) * 3 - 1, 0, 1).astype(np.float32), rng.random(n).astype(np.float32)
+    for p in (a, b):
+        p.set_state(x, xp, np.zeros(0), 0.01, k=3)
+    for steps, res in ((1, False), (2, True), (67, False)):
+        for p in (a, b):
+            p.pdhg_steps(steps, want_residuals=res)
+        for key in ("x", "x_prev"):
+            assert np.array_equal(a.get_state()[key], b.get_state()[key]), (steps, key)
+        if res:
+            assert np.array_equal(a.residuals(), b.residuals())
+    a.close()
+    b.close()
