@@ -696,7 +696,14 @@ int gfors_create_problem(const gfors_csr *A, const int64_t *b, const gfors_csr *
         std::vector<int> packQ(P->qpacked ? P->nnzQ + 1 : 0, static_cast<int>(64 * ceil_div(n, 64)));
         for (int64_t e = 0; e + 1 < static_cast<int64_t>(packQ.size()); ++e)
             packQ[e] = static_cast<int>(static_cast<uint32_t>(ciQ[e]) | static_cast<uint32_t>(valQ[e]) << 24);
-        P->qcode_ok = P->qpacked && P->T == 1 && P->m == 0 && n >= kMinCodes && n <= kMaxCodes;
+        int dev = 0, lds_max = 0;
+        HIP_TRY(hipGetDevice(&dev));
+        HIP_TRY(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
+        P->qcode_ok = P->qpacked && P->T == 1 && P->m == 0 && n >= kMinCodes && n <= kMaxCodes &&
+                      primal_codes_lds(n) <= static_cast<size_t>(lds_max);
+        int64_t longest = 0;
+        for (int64_t i = 0; i < n; ++i) longest = std::max<int64_t>(longest, rpQ[i + 1] - rpQ[i]);
+        P->qcode_pays = P->qcode_ok && P->nnzQ <= kCodesPerRow * n && longest <= kCodesLongest;
         if (P->qpacked && (rc = upload(s, P->packQ, packQ.data(), P->nnzQ + 1))) return rc;
         if ((rc = sync(P))) return rc;
         if (P->qsym) {
@@ -1270,7 +1277,6 @@ int gfors_create_problem(const gfors_csr *A, const int64_t *b, const gfors_csr *
     };
     P->cfg.lpr_dual = pick(m ? static_cast<double>(P->nnzK) / m : 1.0);
     P->cfg.lpr_primal = pick(static_cast<double>(P->nnzK + P->nnzQ) / n);
-    P->qcode_pays = P->qcode_ok && P->nnzQ <= kCodesPerRow * n;
     if (P->qcode_pays) codes_cfg(P);
     if (P->slicedK) {
         P->cfg.slices_dual = kXcdSlices;

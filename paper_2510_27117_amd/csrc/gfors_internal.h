@@ -247,9 +247,14 @@ __device__ __forceinline__ float primal_update_q(float s2, float ct, float rh, f
 // row.  A table that fits in LDS bounds n above; below, its latency does (us a step,
 // this kernel against k_primal, ten entries a row: 5.8 : 4.3 at 50,000 variables,
 // 6.3 : 6.6 at 100,000, 7.7 : 11.3 at 200,000, 17.6 : 25.5 at 500,000).  Longer rows
-// narrow the lead (40 entries: 28 : 36) and leave less to gain from 4 lanes.
-constexpr int64_t kMinCodes = 1 << 17, kMaxCodes = 128 * 1024 * 4, kCodesPerRow = 64;
+// narrow the lead (40 entries: 28 : 36) and leave less to gain from 4 lanes; a single
+// long row is walked by its 4 lanes alone while k_primal's tuned lanes go up to 64
+// (200,000 variables of ten entries and one row of 64, 128, 256, 1,024 entries:
+// 11.3 : 15.0, 14.4 : 15.0, 20.0 : 16.9, 56 : 25; 90,000 entries: 3,712 : 482).
+constexpr int64_t kMinCodes = 1 << 17, kMaxCodes = 128 * 1024 * 4, kCodesPerRow = 64, kCodesLongest = 128;
 constexpr int kCodesLanes = 4;
+// LDS of a workgroup: the codes of every block of 64 variables, and a block of zeros
+constexpr size_t primal_codes_lds(int64_t n) { return static_cast<size_t>((n + 63) / 64 + 1) * 16; }
 void launch_q_codes(hipStream_t s, int n, const float *x, uint4 *codes);
 void launch_primal_codes(hipStream_t s, int lpr, int n, const int *rpQ, const int *packQ, const float *x_in,
                          const uint4 *codes_in, uint4 *codes_out, float *x_out, float *xbar, const float *ct, float tau1,

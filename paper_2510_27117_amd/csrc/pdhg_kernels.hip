@@ -513,7 +513,7 @@ void launch_primal_codes(hipStream_t s, int lpr, int n, const int *rpQ, const in
     const int nblk = (n + 63) / 64;
     const int waves = std::max(1, std::min(16, (nblk + 255) / 256));
     const int blocks = (nblk + waves - 1) / waves;
-    const size_t lds = static_cast<size_t>(nblk + 1) * sizeof(uint4);
+    const size_t lds = primal_codes_lds(n);
     switch (lpr) {
 #define GF_CASE(L) case L: k_primal_codes<L><<<blocks, 64 * waves, lds, s>>>(n, rpQ, packQ, x_in, codes_in, codes_out, x_out, xbar, ct, tau1, two_so, rho, ctr); break;
         GF_CASE(1) GF_CASE(2) GF_CASE(4)

@@ -131,3 +131,25 @@ def test_codes_equal_the_kernel_that_gathers(G, name, lanes):
             assert np.array_equal(a.residuals(), b.residuals())
     a.close()
     b.close()
+
+
+def _hub(n, degree, star):
+    """About `degree` entries a row and exactly `star` in row 0."""
+    P = _box(n, degree, 3, 3)
+    rng = np.random.default_rng(1)
+    rows, col, val = np.repeat(np.arange(n), np.diff(P.Q.row_ptr)), np.asarray(P.Q.col), P.Q.values()
+    keep = (rows != 0) & (col != 0)
+    j = 1 + rng.permutation(n - 1)[:star]
+    zero, one = np.zeros(star, int), np.ones(star, int)
+    P.Q = I.csr_from_coo(n, n, np.concatenate([rows[keep], zero, j]), np.concatenate([col[keep], j, zero]),
+                         np.concatenate([val[keep], one, one]))
+    return P
+
+
+@pytest.mark.parametrize("tuned", [0, 1])
+@pytest.mark.parametrize("star, form", [(128, CODES), (129, (0, 0)), (60000, (0, 0))])
+def test_long_rows_keep_the_kernel_with_more_lanes(G, star, form, tuned):
+    """A row is walked by at most four lanes over codes: past 128 entries k_primal's lanes are ahead."""
+    p = G.Problem(_hub(135000, 6, star), G.default_params(k_int=10, K_max=64, power_iters=5, autotune=tuned))
+    assert _form(p) == form
+    p.close()
