@@ -220,9 +220,10 @@ struct ResidentArgs {
 };
 // What the launch needs to know of the problem: bytes of a stored coefficient
 // (0 when all are 1, 2 or 4), dense rows, the largest instance and its longest
-// row / variable, and the LDS that the form with the matrix in LDS takes.
+// row / variable, the LDS that the form with the matrix in LDS takes, and the
+// lanes per row / variable that its rule gives.
 struct ResidentShape {
-    int vb = 0, nv = 0, nr = 0, len_r = 0, len_c = 0;
+    int vb = 0, nv = 0, nr = 0, len_r = 0, len_c = 0, lpr_d = 1, lpr_p = 1;
     bool dense = false, dense16 = false;
     size_t lds = 0;
 };

@@ -108,6 +108,24 @@ def test_run_of_steps_equals_its_launches(G, name):
     b.close()
 
 
+@pytest.mark.parametrize("name, lanes", [("columns", (1, 1)), ("columns", (4, 1)), ("columns", (4, 2)), ("columns", (16, 8)),
+                                         ("batch", (1, 1)), ("batch", (4, 2)), ("batch", (64, 32)), ("cover", (2, 1))])
+def test_run_of_steps_at_other_lanes(G, name, lanes):
+    """Entries in registers (one or two rows / variables a group) and in LDS, by the lanes."""
+    P = I.set_cover_columns(1500, 500, 3, seed=9) if name == "columns" else _problems()[name]
+    prm = G.default_params(k_int=7, K_max=64, autotune=0)
+    a, b = G.Problem(P, prm), G.Problem(P, prm)
+    a.set_launch_cfg(*lanes, 1, 1, 0, 0, *RUN)
+    b.set_launch_cfg(*lanes, 1, 1, 0, 0, 0, 0)
+    for q in (a, b):
+        q.pdhg_steps(33, want_residuals=True)
+    for k in ("x", "x_prev", "y"):
+        assert np.array_equal(a.get_state()[k], b.get_state()[k]), k
+    assert np.array_equal(a.residuals(), b.residuals())
+    a.close()
+    b.close()
+
+
 @pytest.mark.parametrize("name", ["largest", "least", "one_more", "ragged", "long", "empty_rows"])
 @pytest.mark.parametrize("lanes", [1, 2, 4])
 def test_codes_equal_the_kernel_that_gathers(G, name, lanes):
@@ -152,4 +170,15 @@ def test_long_rows_keep_the_kernel_with_more_lanes(G, star, form, tuned):
     """A row is walked by at most four lanes over codes: past 128 entries k_primal's lanes are ahead."""
     p = G.Problem(_hub(135000, 6, star), G.default_params(k_int=10, K_max=64, power_iters=5, autotune=tuned))
     assert _form(p) == form
+    p.close()
+
+
+@pytest.mark.parametrize("name, lanes", [("long_rows", (8, 1)), ("two_per_group", (1, 1)), ("cover", (2, 1)),
+                                         ("batch", (8, 2)), ("tiny", (1, 1))])
+def test_lanes_of_a_run_cover_an_instance_in_one_pass(G, name, lanes):
+    """1,024 threads over the rows / variables of the largest instance: as many lanes as the mean
+    row asks for, up to one pass."""
+    p = G.Problem(_problems()[name], G.default_params(k_int=7, K_max=64, autotune=0))
+    c = p.launch_cfg()
+    assert _form(p) == RUN and (c["lpr_dual"], c["lpr_primal"]) == lanes
     p.close()
