@@ -1766,36 +1766,45 @@ static int autotune(gfors_problem *P, bool with_eval) {
     hipEvent_t e0, e1;
     HIP_TRY(hipEventCreate(&e0));
     HIP_TRY(hipEventCreate(&e1));
-    auto timeit = [&](const std::function<void()> &f) -> float {
+    auto timeit = [&](const std::function<void()> &f, int reps = 5) -> float {
         f();
         (void)hipEventRecord(e0, s);
-        for (int r = 0; r < 5; ++r) f();
+        for (int r = 0; r < reps; ++r) f();
         (void)hipEventRecord(e1, s);
         (void)hipEventSynchronize(e1);
         float ms = 0.f;
         (void)hipEventElapsedTime(&ms, e0, e1);
-        return ms / 5.f;
+        return ms / static_cast<float>(reps);
     };
     const int lprs[] = {1, 2, 4, 8, 16, 32, 64};
     P->cfg.bits_dual = P->cfg.bits_primal = 0;
     P->bx_fresh = P->by_fresh = false;
     if (P->qcode_pays) codes_cfg(P);   // by rule, also where launches of k_primal were asked for before
     if (P->res_ok) {
-        // lanes per row, then lanes per variable, of the resident steps
+        // the lanes by rule, and half and twice as many per row, then per variable
+        // (every number of lanes from 1 to 64 took five times as long as all of
+        // Preprocess: 20 x 120 facility location, created in 31 ms instead of 6)
         resident_cfg(P);
+        const ResidentShape &sh = P->rsh;
+        P->cfg.lpr_dual = sh.lpr_d;
+        P->cfg.lpr_primal = sh.lpr_p;
         float *xo = P->xsave, *xp = reinterpret_cast<float *>(P->pv), *xb = reinterpret_cast<float *>(P->pu);
         float *yo = reinterpret_cast<float *>(P->pw), *yp = yo + P->m, *wy = P->ybuf[1 - P->cur];
         float best = 1e30f;
         auto consider = [&](int ld, int lp) {
+            if (ld < 1 || lp < 1 || ld > 64 || lp > 64) return;
             const float t = timeit([&] { launch_resident(P, ld, lp, 16, P->xbuf[P->cur], P->ybuf[P->cur], xo, xp, yo, yp,
-                                                         xb, wy, nullptr, P->ctr_scratch); });
+                                                         xb, wy, nullptr, P->ctr_scratch); }, 2);
             if (t < best) { best = t; P->cfg.lpr_dual = ld; P->cfg.lpr_primal = lp; }
         };
-        const int lp0 = P->cfg.lpr_primal;
-        for (int l : lprs)
-            if (!P->rsh.dense16 && l < 2 * P->rsh.len_r) consider(l, lp0);
-        for (int l : lprs)
-            if (!P->rsh.dense16 && l < 2 * P->rsh.len_c && l != lp0) consider(P->cfg.lpr_dual, l);
+        if (!sh.dense16) {
+            consider(sh.lpr_d, sh.lpr_p);
+            consider(sh.lpr_d / 2, sh.lpr_p);
+            if (sh.lpr_d < sh.len_r) consider(2 * sh.lpr_d, sh.lpr_p);
+            const int ld = P->cfg.lpr_dual;
+            consider(ld, sh.lpr_p / 2);
+            if (sh.lpr_p < sh.len_c) consider(ld, 2 * sh.lpr_p);
+        }
     } else if (P->m > 0) {
         float best = 1e30f;
         if (with_eval) {

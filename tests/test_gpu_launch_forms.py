@@ -173,12 +173,15 @@ def test_long_rows_keep_the_kernel_with_more_lanes(G, star, form, tuned):
     p.close()
 
 
+@pytest.mark.parametrize("tuned", [0, 1])
 @pytest.mark.parametrize("name, lanes", [("long_rows", (8, 1)), ("two_per_group", (1, 1)), ("cover", (2, 1)),
                                          ("batch", (8, 2)), ("tiny", (1, 1))])
-def test_lanes_of_a_run_cover_an_instance_in_one_pass(G, name, lanes):
+def test_lanes_of_a_run_cover_an_instance_in_one_pass(G, name, lanes, tuned):
     """1,024 threads over the rows / variables of the largest instance: as many lanes as the mean
-    row asks for, up to one pass."""
-    p = G.Problem(_problems()[name], G.default_params(k_int=7, K_max=64, autotune=0))
+    row asks for, up to one pass.  Tuning looks at half and twice as many."""
+    p = G.Problem(_problems()[name], G.default_params(k_int=7, K_max=64, autotune=tuned))
     c = p.launch_cfg()
-    assert _form(p) == RUN and (c["lpr_dual"], c["lpr_primal"]) == lanes
+    assert _form(p) == RUN
+    for got, want in zip((c["lpr_dual"], c["lpr_primal"]), lanes):
+        assert got == want if not tuned else want / 2 <= got <= 2 * want
     p.close()
