@@ -1290,10 +1290,26 @@ int gfors_create_problem(const gfors_csr *A, const int64_t *b, const gfors_csr *
     return GFORS_OK;
 }
 
+// Whether steps of instances that fit a workgroup are faster there than as
+// launches over the whole chip.  Mostly: about a microsecond of LDS latency
+// against two dispatches.  Not where one of 256 CUs has too much to do.  us a
+// step in replayed graphs, in the workgroup : as (tuned) launches:
+//   sparse, few instances: 3,000 x 500 of 4 entries 3.7 : 4.7, 4,000 x 700 4.8 :
+//   4.6, 5,000 x 900 of 3 5.5 : 4.7, facility location 20 x 80 4.3 : 6.6, 20 x 120
+//   5.8 : 5.4; four of 5,000 x 900 5.5 : 5.6;
+//   dense int16 past the registers, whose wavefronts take every row: 2,000 x 30
+//   5.8 : 6.1, 1,500 x 40 7.2 : 6.2 (32 of them 7.6 : 7.9), 500 x 61 10.8 : 7.4 (32
+//   of them 11.0 : 9.7, 64 11.0 : 14.4); launches without tuning are as good on short
+//   rows only (2,000 x 38 7.6 : 16.3, 500 x 61 10.7 : 7.4).
+static bool resident_pays(const gfors_problem *P, bool tuned) {
+    const ResidentShape &sh = P->rsh;
+    if (sh.dense16) return resident16_regs(sh) || sh.nr <= 32 || P->T >= 64 || (!tuned && sh.nv > 1024);
+    return sh.dense || P->T >= 4 || sh.nv + sh.nr <= 4500;
+}
+
 // Whether every instance fits one workgroup (coefficients in its LDS, by rows
-// and by variables, dense rows once), and then its steps run there: no launch
-// per step.  Wherever it fits it is taken: an iteration costs about a
-// microsecond of LDS latency per instance against two dispatches.
+// and by variables, dense rows once), so that its steps can run there without a
+// launch per step.
 static int setup_resident(gfors_problem *P, const std::vector<int64_t> &off, const std::vector<int> &rp,
                           const std::vector<int> &rpT) {
     P->res_ok = P->res_on = false;
@@ -1348,26 +1364,23 @@ static int setup_resident(gfors_problem *P, const std::vector<int64_t> &off, con
         while (l < 64 && 2 * l <= avg && 2 * l * items <= kResidentThreads) l *= 2;
         return l;
     };
-    if (!sh.dense16) {
-        P->cfg.lpr_dual = one_pass(mr, static_cast<double>(P->nnzK) / P->m);
-        P->cfg.lpr_primal = one_pass(mv, static_cast<double>(P->nnzK) / P->n);
-    }
-    sh.lpr_d = P->cfg.lpr_dual;
-    sh.lpr_p = P->cfg.lpr_primal;
+    sh.lpr_d = sh.dense16 ? P->cfg.lpr_dual : one_pass(mr, static_cast<double>(P->nnzK) / P->m);
+    sh.lpr_p = sh.dense16 ? P->cfg.lpr_primal : one_pass(mv, static_cast<double>(P->nnzK) / P->n);
     P->rsh = sh;
     P->res_ok = true;
-    resident_cfg(P);
+    if (resident_pays(P, P->prm.autotune != 0)) resident_cfg(P);
     return GFORS_OK;
 }
 
-// The launch-per-step shapes whose sums the resident path reproduces.
+// Runs of steps at the lanes of their rule, and the launch-per-step shapes whose
+// sums they reproduce.
 static void resident_cfg(gfors_problem *P) {
     P->cfg.slices_dual = P->cfg.slices_primal = 1;
     P->cfg.sell_dual = P->cfg.sell_primal = 0;
     P->cfg.bits_dual = P->rsh.dense16 ? 4 : 0;
     P->cfg.bits_primal = P->rsh.dense16 ? 5 : 0;
-    P->cfg.lpr_dual = std::min(P->cfg.lpr_dual, 64);
-    P->cfg.lpr_primal = std::min(P->cfg.lpr_primal, 64);
+    P->cfg.lpr_dual = P->rsh.lpr_d;
+    P->cfg.lpr_primal = P->rsh.lpr_p;
     P->res_on = true;
 }
 
@@ -1779,15 +1792,15 @@ static int autotune(gfors_problem *P, bool with_eval) {
     const int lprs[] = {1, 2, 4, 8, 16, 32, 64};
     P->cfg.bits_dual = P->cfg.bits_primal = 0;
     P->bx_fresh = P->by_fresh = false;
+    const bool resident = P->res_ok && resident_pays(P, true);
+    P->res_on = false;
     if (P->qcode_pays) codes_cfg(P);   // by rule, also where launches of k_primal were asked for before
-    if (P->res_ok) {
+    if (resident) {
         // the lanes by rule, and half and twice as many per row, then per variable
         // (every number of lanes from 1 to 64 took five times as long as all of
         // Preprocess: 20 x 120 facility location, created in 31 ms instead of 6)
         resident_cfg(P);
         const ResidentShape &sh = P->rsh;
-        P->cfg.lpr_dual = sh.lpr_d;
-        P->cfg.lpr_primal = sh.lpr_p;
         float *xo = P->xsave, *xp = reinterpret_cast<float *>(P->pv), *xb = reinterpret_cast<float *>(P->pu);
         float *yo = reinterpret_cast<float *>(P->pw), *yp = yo + P->m, *wy = P->ybuf[1 - P->cur];
         float best = 1e30f;
@@ -1845,7 +1858,7 @@ static int autotune(gfors_problem *P, bool with_eval) {
         }
         P->cfg.bits_dual = best_bits;
     }
-    if (!P->res_ok && !P->qcode_on) {
+    if (!resident && !P->qcode_on) {
         float best = 1e30f;
         float *xs = P->xsave, *xb = reinterpret_cast<float *>(P->pv);
         if (with_eval) launch_fill_share(s, P->wy, 0.5f, 56, P->m);
@@ -1947,7 +1960,7 @@ static int autotune(gfors_problem *P, bool with_eval) {
         }
         P->eval_variant = bestv;
     }
-    if (with_eval && !P->res_ok) {   // the stand-in goes, the starting point comes back
+    if (with_eval && !resident) {   // the stand-in goes, the starting point comes back
         launch_fill_f32(s, P->xbar, static_cast<float>(P->prm.x0), P->n);
         launch_fill_f32(s, P->xbuf[P->cur], static_cast<float>(P->prm.x0), P->n);
         launch_fill_f32(s, P->wy, 0.f, P->m);
@@ -2497,9 +2510,9 @@ int gfors_set_launch_cfg(gfors_problem *P, const int32_t *cfg) {
         if (!(P->res_ok && cfg[6] == kCfgRunDual && cfg[7] == kCfgRunPrimal && plain_layout && pow2(cfg[0]) && pow2(cfg[1])))
             return fail(GFORS_E_ARG, "dual 6 and primal 8 (runs of steps in one launch) go together, with 1 slice, no SELL and lanes "
                                      "a power of two in [1, 64], where every instance fits a workgroup");
+        resident_cfg(P);
         P->cfg.lpr_dual = cfg[0];
         P->cfg.lpr_primal = cfg[1];
-        resident_cfg(P);
         P->graphs_clear();
         return GFORS_OK;
     }

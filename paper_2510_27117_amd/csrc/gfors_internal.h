@@ -227,6 +227,12 @@ struct ResidentShape {
     bool dense = false, dense16 = false;
     size_t lds = 0;
 };
+// Dense int16 rows: whether the coefficients stay in registers (eight columns of
+// up to 24, 16 or 8 rows a thread of one, two or four tiles), else in LDS.
+inline bool resident16_regs(const ResidentShape &sh) {
+    const int tiles = (sh.nv + 2047) / 2048;
+    return tiles == 1 ? sh.nr <= 24 : tiles == 2 ? sh.nr <= 16 : tiles <= 4 && sh.nr <= 8;
+}
 void launch_steps_resident(hipStream_t s, const ResidentArgs &A, int T, const ResidentShape &sh, int nsteps, int lpr_d,
                            int lpr_p);
 

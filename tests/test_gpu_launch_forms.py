@@ -185,3 +185,26 @@ def test_lanes_of_a_run_cover_an_instance_in_one_pass(G, name, lanes, tuned):
     for got, want in zip((c["lpr_dual"], c["lpr_primal"]), lanes):
         assert got == want if not tuned else want / 2 <= got <= 2 * want
     p.close()
+
+
+@pytest.mark.parametrize("P, untuned, tuned", [
+    (lambda: I.set_cover_columns(3000, 500, 4, 1), True, True),
+    (lambda: I.set_cover_columns(4000, 700, 4, 1), False, False),
+    (lambda: I.concat_instances([I.set_cover_columns(4000, 700, 4, s) for s in range(4)]), True, True),
+    (lambda: I.knapsack_multi(500, 61, 1), False, False),
+    (lambda: I.knapsack_multi(2000, 38, 1), True, False),
+    (lambda: I.knapsack_multi(500, 24, 1), True, True),
+    (lambda: I.knapsack_multi(6000, 9, 1), True, True),
+    (lambda: I.knapsack_multi(500, 60, 1, wmax=100_000), True, True),
+    (lambda: I.concat_instances([I.knapsack_multi(500, 61, s) for s in range(64)]), True, True)])
+def test_runs_only_where_a_workgroup_is_ahead_of_the_chip(G, P, untuned, tuned):
+    bip = P()
+    for at, want in ((0, untuned), (1, tuned)):
+        p = G.Problem(bip, G.default_params(k_int=7, K_max=64, power_iters=5, autotune=at))
+        assert (_form(p) == RUN) == want, at
+        cfg = p.launch_cfg()
+        p.set_launch_cfg(min(cfg["lpr_dual"], 64), min(cfg["lpr_primal"], 64), 1, 1, 0, 0, *RUN)   # it fits all the same
+        assert _form(p) == RUN
+        p.autotune()
+        assert (_form(p) == RUN) == tuned
+        p.close()
