@@ -211,6 +211,32 @@ def signed_index_bytes(bip, bits_dual, bits_primal, kb):
     return out
 
 
+def fused_step_bytes(bip, cfg, k_int, kb):
+    """Bytes per launch where one launch takes both products of a step: dense
+    16-bit rows (dual 4 with primal 5, launches of whole steps) read every
+    coefficient once a step and x, its costs, y and the row data once, and the
+    run opens with one launch of row sums; a run of k_int steps in one launch
+    (dual 6 with primal 8) moves the matrix by rows and by variables and the
+    state once per run, counted per step.  Returns kb updated."""
+    form = (cfg.get("bits_dual", 0), cfg.get("bits_primal", 0))
+    if form not in ((4, 5), (6, 8)):
+        return kb
+    mats = [M for M in (bip.A, bip.B) if M is not None]
+    n, m, nnz = bip.n, bip.m1 + bip.m2, sum(M.nnz for M in mats)
+    unit = all(M.val is None for M in mats)
+    small = all(np.abs(M.values().astype(np.int64)).max(initial=0) <= 32767 for M in mats)
+    out = dict(kb)
+    if form == (4, 5):
+        if small:
+            out["dual"] = 2 * nnz + 4 * n
+            out["primal"] = 2 * nnz + 16 * n + 20 * m
+        return out
+    out.pop("dual", None)
+    entry = 4 + (0 if unit else 2 if small else 4)
+    out["primal"] = (2 * entry * nnz + 4 * (n + m + 2) + 28 * n + 24 * m) / k_int
+    return out
+
+
 VALU_LANE_OPS = 256 * 64 * 2.4e9   # lanes x clock of the 256 CUs: one integer op per lane per clock
 MFMA_INT8_TOPS = 5000.0             # dense int8 matrix-core peak of the MI355X (TOP/s)
 
@@ -825,10 +851,11 @@ def run_workload(a):
 
     # per-kernel HIP-event durations (eager launches, same stream, state advances)
     kt = G.kernel_times(a.k_int, a.K)
-    per_step = {k: ms * (a.k_int if k in ("dual", "primal") else 1) for k, (ms, cnt) in kt.items() if cnt}
+    per_step = {k: ms * cnt for k, (ms, cnt) in kt.items() if cnt}
     kb = kernel_bytes(bip, a.K, indexed_entries(bip))
     lc = G.launch_cfg()
     kb = signed_index_bytes(bip, lc.get("bits_dual", 0), lc.get("bits_primal", 0), kb)
+    kb = fused_step_bytes(bip, lc, a.k_int, kb)
     dom = max((k for k in per_step if k in kb), key=lambda k: per_step[k])
     avg_ms = kt[dom][0]
     achieved = kb[dom] / (avg_ms * 1e-3) / 1e9

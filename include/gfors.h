@@ -283,7 +283,12 @@ int gfors_get_scales(gfors_problem *P, double *row_scale, double *obj_scale, dou
  * launches timed to launches[], if not NULL).  Kernel kinds, in order: dual
  * step, primal step, sampler, covering-row evaluation, general-row evaluation,
  * quadratic objective, candidate reduction, incumbent update, x_best copy.
- * A kind that did not run reports 0. */
+ * A kind that did not run reports 0.  The launches timed are those of an
+ * ordinary call, also where one launch takes more than one product: a whole
+ * step (dense 16-bit batches) counts as a primal step, the dual kind then holds
+ * the row sums that open the run of steps; a run of steps in one launch counts
+ * as that many primal steps of equal duration (launches[] is their number) and
+ * the dual kind as not run. */
 #define GFORS_NUM_KERNEL_TIMERS 9
 int gfors_kernel_times(gfors_problem *P, int32_t nsteps, int32_t K, double *avg_ms,
                        int32_t *launches);

@@ -1997,49 +1997,55 @@ static void enqueue_steps(gfors_problem *P, int nsteps, bool want_res, KTimer *t
     hipStream_t s = P->stream;
     // a sequence never relies on bitmaps written before it
     P->bx_fresh = P->by_fresh = false;
-    // per-launch timing keeps a launch per step (the same sums in the same order)
-    if (P->res_on && !tm) {
+    if (P->res_on) {
         const int a = P->cur, z = (P->cur + nsteps) & 1;
+        TB(1);
         launch_resident(P, P->cfg.lpr_dual, P->cfg.lpr_primal, nsteps, P->xbuf[a], P->ybuf[a], P->xbuf[z],
                         P->xbuf[1 - z], P->ybuf[z], P->ybuf[1 - z], P->xbar, P->wy, want_res ? P->xsave : nullptr,
                         P->ctr);
+        TE(1);
+        if (tm) tm->steps_per_run = nsteps;
         if (want_res) enqueue_residuals(P, 1 - z);
         P->cur = z;
         return;
     }
-    // dense int16 batches: a launch per step (the residual step and timed steps
-    // keep the two products apart; same sums in the same order).  The second
-    // buffer of tile sums lies in Preprocess's scratch.
+    // dense int16 batches: a launch per step (the residual step keeps the two
+    // products apart; same sums in the same order).  The second buffer of tile
+    // sums lies in Preprocess's scratch.
     const int joint = nsteps - (want_res ? 1 : 0);
-    if (joint > 0 && !tm && P->cfg.bits_dual == 4 && P->cfg.bits_primal == 5 && P->blk.pval &&
+    if (joint > 0 && P->cfg.bits_dual == 4 && P->cfg.bits_primal == 5 && P->blk.pval &&
         static_cast<int64_t>(P->blk.ntile) * 64 * 4 <= P->n * 8) {
         float *pp[2] = {P->blk.pp, reinterpret_cast<float *>(P->pu)};
+        TB(0);
         launch_dual_block_sums(s, P->blk, P->d_inst_var0, P->d_inst_nvar, P->xbar, pp[0]);
+        TE(0);
         for (int it = 0; it < joint; ++it) {
             const int a = P->cur, z = 1 - P->cur;
+            TB(1);
             launch_step_block(s, P->blk, static_cast<int>(P->m1), P->d_inst_var0, P->d_inst_nvar, pp[it & 1],
                               it + 1 < joint ? pp[1 - (it & 1)] : nullptr, P->omega, P->rt, P->di.tau2, P->ybuf[a],
                               P->ybuf[z], P->wy, P->xbuf[a], P->xbuf[z], P->xbar, P->ct, P->di.tau1, P->di.rho, P->ctr);
+            TE(1);
             P->cur = z;
         }
         nsteps -= joint;
     }
-    // codes of x from step to step (timed steps keep k_primal: the same sums)
-    const bool codes = P->qcode_on && !tm;
-    if (codes && nsteps > 0) launch_q_codes(s, static_cast<int>(P->n), P->xbuf[P->cur], P->qcode[0]);
+    // codes of x from step to step
     for (int it = 0; it < nsteps; ++it) {
         const bool res = want_res && it == nsteps - 1;
         if (res) launch_copy_f32(s, P->xsave, P->xbar, P->n);
         const int a = P->cur, bnext = 1 - P->cur;
-        TB(0);
-        if (P->m > 0)
+        if (P->m > 0) {
+            TB(0);
             launch_dual_cfg(P, P->cfg.lpr_dual, P->cfg.slices_dual, P->cfg.sell_dual, P->ybuf[a],
                             P->ybuf[bnext]);
-        TE(0);
+            TE(0);
+        }
         TB(1);
-        if (codes)
+        if (P->qcode_on) {
+            if (it == 0) launch_q_codes(s, static_cast<int>(P->n), P->xbuf[a], P->qcode[0]);
             launch_codes(P, P->cfg.lpr_primal, it & 1, P->xbuf[a], P->xbuf[bnext], P->xbar, P->ctr);
-        else
+        } else
             launch_primal_cfg(P, P->cfg.lpr_primal, P->cfg.slices_primal, P->cfg.sell_primal,
                               P->xbuf[a], P->xbuf[bnext], P->xbar, P->ctr);
         TE(1);
@@ -2094,27 +2100,33 @@ static void enqueue_eval(gfors_problem *P, int K, int threshold, KTimer *tm, int
     }
     hipStream_t s = P->stream;
     const int W = K / 64;
-    TB(3);
-    launch_eval_cover(s, P->n_cover, P->cover_ids, P->et, P->rows, P->rkind, P->rp, P->ci, P->X,
-                      P->xkind, W, P->vpart, K, P->pair_rows_mostly);
-    TE(3);
-    TB(4);
-    launch_eval_general_rows(P, K);
-    TE(4);
-    TB(5);
-    if (P->hasQ && P->qmag)
-        launch_eval_quad_bits(s, P->qt, P->qsym ? P->rpU : P->rpQ, P->qsym ? P->rowU : P->rowQ,
-                              P->qsym ? P->ciU : P->ciQ, P->qsym ? P->valU : P->valQ, P->X, P->xkind, W, P->qmag,
-                              P->zqpart, K);
-    else if (P->hasQ)
-        launch_eval_quad(s, P->qt, P->qsym ? P->rpU : P->rpQ, P->qsym ? P->rowU : P->rowQ,
-                         P->qsym ? P->ciU : P->ciQ, P->qsym ? P->valU : P->valQ, P->X, W, P->zqpart, K,
-                         P->q24);
-    TE(5);
-    TB(6);
-    launch_reduce_cand(s, P->T, K, P->red_S, P->et, P->vpart, P->st, P->zpart, P->qt, P->zqpart,
-                       P->hasQ ? 1 : 0, P->red_v, P->red_z, P->viol, P->z);
-    TE(6);
+    if (P->n_cover > 0) {
+        TB(3);
+        launch_eval_cover(s, P->n_cover, P->cover_ids, P->et, P->rows, P->rkind, P->rp, P->ci, P->X,
+                          P->xkind, W, P->vpart, K, P->pair_rows_mostly);
+        TE(3);
+    }
+    if (P->n_general > 0) {
+        TB(4);
+        launch_eval_general_rows(P, K);
+        TE(4);
+    }
+    if (P->hasQ) {
+        const int *rp = P->qsym ? P->rpU : P->rpQ, *row = P->qsym ? P->rowU : P->rowQ;
+        const int *ci = P->qsym ? P->ciU : P->ciQ, *val = P->qsym ? P->valU : P->valQ;
+        TB(5);
+        if (P->qmag)
+            launch_eval_quad_bits(s, P->qt, rp, row, ci, val, P->X, P->xkind, W, P->qmag, P->zqpart, K);
+        else
+            launch_eval_quad(s, P->qt, rp, row, ci, val, P->X, W, P->zqpart, K, P->q24);
+        TE(5);
+    }
+    if (P->red_S > 1) {   // else the incumbent update adds the few tiles itself
+        TB(6);
+        launch_reduce_cand(s, P->T, K, P->red_S, P->et, P->vpart, P->st, P->zpart, P->qt, P->zqpart,
+                           P->hasQ ? 1 : 0, P->red_v, P->red_z, P->viol, P->z);
+        TE(6);
+    }
     TB(7);
     const int advance = threshold ? 0 : (trigger ? 1 : 2);
     launch_argmin_update(s, P->T, K, W, P->red_S, P->et, P->vpart, P->st, P->zpart, P->qt, P->zqpart,
@@ -2418,7 +2430,8 @@ int gfors_kernel_times(gfors_problem *P, int32_t nsteps, int32_t K, double *avg_
             HIP_TRY(hipEventElapsedTime(&ms, p.first, p.second));
             tot += ms;
         }
-        const size_t cnt = tm.ev[id].size();
+        // a launch of a run of steps counts once per step
+        const size_t cnt = id == 1 && tm.steps_per_run ? tm.steps_per_run : tm.ev[id].size();
         avg_ms[id] = cnt ? tot / static_cast<double>(cnt) : 0.0;
         if (launches) launches[id] = static_cast<int32_t>(cnt);
     }

@@ -261,6 +261,7 @@ namespace gfh {
 struct KTimer {
     hipStream_t s;
     std::vector<std::pair<hipEvent_t, hipEvent_t>> ev[GFORS_NUM_KERNEL_TIMERS];
+    int steps_per_run = 0;   // steps that the one launch of kind 1 took (0: a launch per step)
     void b(int id) {
         hipEvent_t a, z;
         (void)hipEventCreate(&a);

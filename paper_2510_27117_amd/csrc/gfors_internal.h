@@ -467,8 +467,8 @@ void launch_reduce_cand(hipStream_t s, int T, int K, int S, const Tiles &et, con
                         const Tiles &st, const int64_t *zpart, const Tiles &qt,
                         const int64_t *zqpart, int has_q, int32_t *rv, int64_t *rz,
                         int32_t *viol, int64_t *z);
-// S: the reduction's tile slices; with S = 1 launch_reduce_cand does nothing and
-// the per-tile partials are added here.
+// S: the slices of launch_reduce_cand; with S = 1 that launch is left out and the
+// per-tile partials are added here.
 void launch_argmin_update(hipStream_t s, int T, int K, int W, int S, const Tiles &et, const int *vpart,
                           const Tiles &st, const int64_t *zpart, const Tiles &qt, const int64_t *zqpart, int has_q,
                           int32_t *viol, int64_t *z, DevInst di, DevCounters *ctr, int advance);

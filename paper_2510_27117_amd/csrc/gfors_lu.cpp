@@ -445,9 +445,9 @@ void lu_enqueue_steps(gfors_problem *P, int nsteps, bool want_res, KTimer *tm) {
         const bool res = want_res && it == nsteps - 1;
         if (res) launch_copy_f32(s, P->xsave, P->xbar, nfull);
         const int a = P->cur, bn = 1 - P->cur;
-        TB(0);
         LuHeavyArgs H;
         if (m > 0) {
+            TB(0);
             LuDualArgs A;
             A.m = m;
             A.m1 = H.m1 = m1;
@@ -474,8 +474,8 @@ void lu_enqueue_steps(gfors_problem *P, int nsteps, bool want_res, KTimer *tm) {
             H.first = L.hch_first;
             H.order = P->dual_order;
             H.part = L.hpart;
+            TE(0);
         }
-        TE(0);
         TB(1);
         // one workgroup takes the heavy rows' updates, the pivot gradient and the
         // transposed solves while the pivots fit its threads
@@ -552,10 +552,12 @@ void lu_enqueue_eval(gfors_problem *P, int K, int threshold, KTimer *tm, int tri
     launch_lu_eval_obj(s, r, K, L.c_tail, L.c0, L.XI, L.nqch, nk, L.qch_row, L.qch_e0, L.qch_e1, P->ciQ, P->valQ,
                        P->X, P->zqpart);
     TE(5);
-    TB(6);
-    launch_reduce_cand(s, 1, K, P->red_S, P->et, P->vpart, P->st, P->zpart, P->qt, P->zqpart, 1, P->red_v,
-                       P->red_z, P->viol, P->z);
-    TE(6);
+    if (P->red_S > 1) {   // else the incumbent update adds the few tiles itself
+        TB(6);
+        launch_reduce_cand(s, 1, K, P->red_S, P->et, P->vpart, P->st, P->zpart, P->qt, P->zqpart, 1, P->red_v,
+                           P->red_z, P->viol, P->z);
+        TE(6);
+    }
     TB(7);
     const int advance = threshold ? 0 : (trigger ? 1 : 2);
     launch_argmin_update(s, 1, K, W, P->red_S, P->et, P->vpart, P->st, P->zpart, P->qt, P->zqpart, 1, P->viol, P->z,

@@ -1587,7 +1587,6 @@ void launch_reduce_cand(hipStream_t s, int T, int K, int S, const Tiles &et, con
                         const Tiles &st, const int64_t *zpart, const Tiles &qt,
                         const int64_t *zqpart, int has_q, int32_t *rv, int64_t *rz,
                         int32_t *viol, int64_t *z) {
-    if (S == 1) return;   // launch_argmin_update adds the few tiles itself
     dim3 g1(T, (K + 255) / 256, S);
     k_reduce_cand1<<<g1, 256, 0, s>>>(K, S, et.first, vpart, st.first, zpart,
                                        has_q ? qt.first : st.first, zqpart, has_q, rv, rz);

@@ -88,3 +88,19 @@ def test_signed_index_variant_bytes_facility_location():
     groups = (nf + 15) // 16
     assert p7["primal"] == 4 * 2 * nf * nc + groups * (nc * (4 + 2) + 16) + 4 * m + 16 * n
     assert bench.signed_index_bytes(P, 0, 0, kb) == kb
+
+
+def test_fused_step_bytes():
+    """Whole steps in one launch: 2-byte coefficients once, x, cost, x out, xbar of 4 bytes a
+    variable and y, y out, omega, rt, omega y of 4 a row.  Runs of steps: the matrix twice
+    (index and coefficient), x, x_prev and xbar in or out, cost; y in and out twice, omega, rt,
+    omega y, over the steps of the run."""
+    P = I.concat_instances([I.knapsack_multi(50, 3, seed=4), I.knapsack_multi(70, 2, seed=5)])
+    kb = bench.kernel_bytes(P, 64, (0, 0))
+    n, m, nnz = P.n, P.m1, P.A.nnz
+    whole = bench.fused_step_bytes(P, {"bits_dual": 4, "bits_primal": 5}, 100, kb)
+    assert whole["primal"] == 2 * nnz + 16 * n + 20 * m and whole["dual"] == 2 * nnz + 4 * n
+    run = bench.fused_step_bytes(P, {"bits_dual": 6, "bits_primal": 8}, 100, kb)
+    assert "dual" not in run
+    assert run["primal"] == (2 * 6 * nnz + 4 * (n + m + 2) + 7 * 4 * n + 6 * 4 * m) / 100
+    assert bench.fused_step_bytes(P, {"bits_dual": 4, "bits_primal": 0}, 100, kb) == kb

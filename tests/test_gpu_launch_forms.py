@@ -208,3 +208,39 @@ def test_runs_only_where_a_workgroup_is_ahead_of_the_chip(G, P, untuned, tuned):
         p.autotune()
         assert (_form(p) == RUN) == tuned
         p.close()
+
+
+@pytest.mark.parametrize("name", ["run", "whole_steps", "codes", "rows_apart", "many_tiles"])
+def test_kernel_times_are_those_of_ordinary_calls(G, name):
+    """Kinds that ran, with their launches; the steps advance as pdhg_steps does, bit for bit."""
+    P, cfg, steps = {
+        "run": (lambda: _problem("run")[0], None, {"primal": 9}),
+        "whole_steps": (lambda: I.concat_instances([I.knapsack_multi(300, 7, seed=s) for s in range(3)]),
+                        (16, 4, 1, 1, 0, 0, 4, 5), {"dual": 1, "primal": 9}),
+        "codes": (lambda: _problem("codes")[0], None, {"primal": 9}),
+        "rows_apart": (lambda: I.facility_location(7, 40, 2), (4, 4, 1, 1, 0, 0, 0, 0), {"dual": 9, "primal": 9}),
+        "many_tiles": (lambda: I.set_cover_columns(90_000, 9_000, 4, 1), None, {"dual": 9, "primal": 9})}[name]
+    P = P()
+    a, b = (G.Problem(P, G.default_params(k_int=9, K_max=64, power_iters=5, autotune=0)) for _ in range(2))
+    for p in (a, b):
+        if cfg:
+            p.set_launch_cfg(*cfg)
+    kt = a.kernel_times(9, 64)
+    b.pdhg_steps(9)
+    b.sample_eval(64)
+    want = {**steps, "sample": 1, "argmin_update": 1, "extract_best": 1}
+    if P.Q is not None:
+        want["eval_quad"] = 1
+    got = {k: c for k, (ms, c) in kt.items() if c}
+    for k in ("eval_cover", "eval_general", "reduce_cand"):    # by the rows' kinds and the tiles
+        if k in got:
+            want[k] = 1
+    assert got == want
+    assert all((ms > 0) == (c > 0) for ms, c in kt.values())
+    assert ("eval_cover" in got or "eval_general" in got) == (P.m1 + P.m2 > 0)
+    assert ("reduce_cand" in got) == (name in ("codes", "many_tiles"))
+    assert not (name == "run" and "eval_general" in got) and not (name == "whole_steps" and "eval_cover" in got)
+    sa, sb = a.get_state(), b.get_state()
+    assert all(np.array_equal(sa[k], sb[k]) for k in ("x", "x_prev", "y")) and sa["k"] == sb["k"]
+    a.close()
+    b.close()
