@@ -1307,6 +1307,15 @@ static bool resident_pays(const gfors_problem *P, bool tuned) {
     return sh.dense || P->T >= 4 || sh.nv + sh.nr <= 4500;
 }
 
+// Whether a single step is worth a run of its own, which reads the whole matrix
+// into the workgroup first.  Not for dense int16 rows in LDS or over several
+// tiles, whose launches read it as fast with all CUs (us a call, run : launches:
+// 8,000 x 8 25.2 : 10.9, 3,000 x 8 11.6 : 10.1, 2,000 x 30 17.9 : 15.6, 600 of 4,000 x 8
+// 48 : 30; 2,000 x 24 10.5 : 13.9, 300 of 2,000 x 16 15.7 : 19.9).  Same sums.
+static bool resident_single_pays(const ResidentShape &sh) {
+    return !sh.dense16 || (resident16_regs(sh) && sh.nv <= kBlockCols);
+}
+
 // Whether every instance fits one workgroup (coefficients in its LDS, by rows
 // and by variables, dense rows once), so that its steps can run there without a
 // launch per step.
@@ -1997,7 +2006,7 @@ static void enqueue_steps(gfors_problem *P, int nsteps, bool want_res, KTimer *t
     hipStream_t s = P->stream;
     // a sequence never relies on bitmaps written before it
     P->bx_fresh = P->by_fresh = false;
-    if (P->res_on) {
+    if (P->res_on && !(nsteps == 1 && !resident_single_pays(P->rsh))) {
         const int a = P->cur, z = (P->cur + nsteps) & 1;
         TB(1);
         launch_resident(P, P->cfg.lpr_dual, P->cfg.lpr_primal, nsteps, P->xbuf[a], P->ybuf[a], P->xbuf[z],

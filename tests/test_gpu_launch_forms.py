@@ -244,3 +244,23 @@ def test_kernel_times_are_those_of_ordinary_calls(G, name):
     assert all(np.array_equal(sa[k], sb[k]) for k in ("x", "x_prev", "y")) and sa["k"] == sb["k"]
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("sizes, launches", [([(2048, 24)], False), ([(2049, 3)], True), ([(600, 25)], True),
+                                             ([(300, 5), (8000, 8)], True), ([(300, 5), (2000, 9)], False)])
+def test_single_steps_of_wide_dense_rows_are_launches(G, sizes, launches):
+    P = I.concat_instances([I.knapsack_multi(n, m, seed=n) for n, m in sizes])
+    a, b = (G.Problem(P, G.default_params(k_int=9, K_max=64, power_iters=5, autotune=0)) for _ in range(2))
+    assert _form(a) == RUN
+    kt = {n: a.kernel_times(n, 64) for n in (1, 2)}
+    assert kt[1]["dual"][1] == int(launches) and kt[1]["primal"][1] == 1
+    assert kt[2]["dual"][1] == 0 and kt[2]["primal"][1] == 2
+    a.reset()
+    for n, res in ((1, False), (1, True), (4, False), (1, False), (2, True)):
+        a.pdhg_steps(n, want_residuals=res)
+    b.pdhg_steps(9, want_residuals=True)
+    sa, sb = a.get_state(), b.get_state()
+    assert all(np.array_equal(sa[k], sb[k]) for k in ("x", "x_prev", "y")) and sa["k"] == sb["k"]
+    assert np.array_equal(a.residuals(), b.residuals())
+    a.close()
+    b.close()
