@@ -2181,14 +2181,18 @@ static hipGraphExec_t step_chunk_graph(gfors_problem *P) {
 int gfors_pdhg_steps(gfors_problem *P, int32_t nsteps, int32_t want_residuals) {
     if (!P || nsteps < 0) return fail(GFORS_E_ARG, "gfors_pdhg_steps: bad argument");
     if (nsteps == 0) return GFORS_OK;
-    // long runs replay a graph of kStepChunk steps: a launch costs the host
-    // about 4 us, more than the step's kernels take on mid-sized problems
-    // (20,011 x 1,999 set cover: 8.9 -> 7.0 us per step).  The residual step is
-    // launched by itself.
+    // Long runs replay a graph of kStepChunk steps: a launch costs the host about
+    // 4 us, as much as the step's kernels take on mid-sized problems, so replayed
+    // steps are 3 to 20 % faster.  Making the graph costs as much as is gained over
+    // 400 to 3,500 steps (set cover of 30,000 x 3,000, 100 steps: 556 us launched,
+    // 536 replayed, 1,242 with the graph made first; 20,011 x 1,999: 560, 534,
+    // 735), so it is made once a problem has launched about as many.  The residual
+    // step is launched by itself.
     int left = nsteps;
-    if (!P->res_on && left >= 2 * kStepChunk)
+    if (!P->res_on && left >= 2 * kStepChunk && P->steps_launched >= kStepsBeforeGraph)
         if (const hipGraphExec_t ge = step_chunk_graph(P))
             for (; left > kStepChunk; left -= kStepChunk) HIP_TRY(hipGraphLaunch(ge, P->stream));
+    P->steps_launched += left;
     enqueue_steps(P, left, want_residuals != 0);
     HIP_TRY(hipGetLastError());
     return GFORS_OK;

@@ -52,6 +52,7 @@ constexpr int kRowRows = 2048;
 constexpr int kCfgRunDual = 6, kCfgRunPrimal = 8;   // runs of steps in one launch
 constexpr int kCfgCodes = 9;                        // steps over codes of x
 constexpr int kStepChunk = 32;         // steps per captured graph of gfors_pdhg_steps (even)
+constexpr int kStepsBeforeGraph = 2048;   // steps launched one by one before that graph is made
 constexpr int kMfmaRows = 32;          // rows per dense digit block (one 32 x 32 matrix-core tile)
 constexpr int kMfmaMaxSpan = 1 << 23;  // column span of a block: keeps int32 plane sums exact
 
@@ -247,6 +248,7 @@ struct gfors_problem {
     // the reformulated matrix go through the LU of the pivot block; null otherwise
     gfh::LuForm *lu = nullptr;
 
+    int64_t steps_launched = 0;   // by gfors_pdhg_steps, outside graphs
     // graphs: key = (K, parity)
     std::map<std::pair<int, int>, hipGraphExec_t> graphs;
     void graphs_clear() {
