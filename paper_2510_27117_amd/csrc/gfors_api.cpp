@@ -24,6 +24,41 @@ std::string &err_slot() {
     thread_local std::string s;
     return s;
 }
+
+hipError_t takes_graph(hipStream_t stream) {
+    if (!stream || stream == hipStreamLegacy) return hipErrorStreamCaptureUnsupported;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(stream, &st);
+    if (e == hipSuccess) return st == hipStreamCaptureStatusNone ? hipSuccess : hipErrorStreamCaptureUnsupported;
+    (void)hipGetLastError();
+    return e;
+}
+
+hipError_t capture_graph(hipStream_t &stream, const std::function<void()> &f, hipGraphExec_t *exec) {
+    const hipStream_t given = stream;
+    hipStream_t own = nullptr;
+    hipGraph_t g = nullptr;
+    int now = 0, dev = 0;
+    hipError_t e = hipGetDevice(&now);
+    if (e == hipSuccess && hipStreamGetDevice(given, &dev) != hipSuccess) {
+        (void)hipGetLastError();
+        dev = now;
+    }
+    if (e == hipSuccess && dev != now) e = hipSetDevice(dev);
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&own, hipStreamNonBlocking);
+    if (dev != now) (void)hipSetDevice(now);
+    if (e == hipSuccess) e = hipStreamBeginCapture(own, hipStreamCaptureModeThreadLocal);
+    if (e == hipSuccess) {
+        stream = own;
+        f();
+        stream = given;
+        e = hipStreamEndCapture(own, &g);
+        if (e == hipSuccess) e = hipGraphInstantiate(exec, g, nullptr, nullptr, 0);
+    }
+    if (g) (void)hipGraphDestroy(g);
+    if (own) (void)hipStreamDestroy(own);
+    return e;
+}
 }  // namespace gfh
 
 using namespace gfh;
@@ -2148,33 +2183,23 @@ static void enqueue_eval(gfors_problem *P, int K, int threshold, KTimer *tm, int
 }
 
 // kStepChunk steps as one captured graph (the chunk is even, so the buffers'
-// parity is the same after it), or null where the stream cannot be captured
-// (the null stream, or a caller's capture under way): the steps are then
-// launched one by one.
+// parity is the same after it), or null where the stream takes no graph (the
+// null stream, or a caller's capture under way): the steps are then launched
+// one by one.
 static hipGraphExec_t step_chunk_graph(gfors_problem *P) {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (!P->stream || P->stream == hipStreamPerThread || P->stream == hipStreamLegacy) return nullptr;
-    if (hipStreamIsCapturing(P->stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
-        return nullptr;
-    }
+    if (P->stream == hipStreamPerThread || takes_graph(P->stream) != hipSuccess) return nullptr;
     const auto key = std::make_pair(-kStepChunk, P->cur);
     const auto it = P->graphs.find(key);
     if (it != P->graphs.end()) return it->second;
-    if (hipStreamBeginCapture(P->stream, hipStreamCaptureModeThreadLocal) != hipSuccess) {
+    hipGraphExec_t ge = nullptr;
+    const int cur0 = P->cur;
+    const hipError_t e = capture_graph(P->stream, [&] { enqueue_steps(P, kStepChunk, false); }, &ge);
+    P->cur = cur0;
+    if (e != hipSuccess) {
         (void)hipGetLastError();
         return nullptr;
     }
-    const int cur0 = P->cur;
-    enqueue_steps(P, kStepChunk, false);
-    P->cur = cur0;
-    hipGraph_t g = nullptr;
-    hipGraphExec_t ge = nullptr;
-    if (hipStreamEndCapture(P->stream, &g) != hipSuccess || !g || hipGraphInstantiate(&ge, g, nullptr, nullptr, 0) != hipSuccess)
-        ge = nullptr;
-    if (g) (void)hipGraphDestroy(g);
-    if (ge) P->graphs.emplace(key, ge);
-    else (void)hipGetLastError();
+    P->graphs.emplace(key, ge);
     return ge;
 }
 
@@ -2265,16 +2290,15 @@ int gfors_run_rounds(gfors_problem *P, int32_t nrounds, int32_t K, int32_t use_g
         auto it = P->graphs.find(key);
         const int cur0 = P->cur;
         if (it == P->graphs.end()) {
-            hipGraph_t g;
-            HIP_TRY(hipStreamBeginCapture(P->stream, hipStreamCaptureModeThreadLocal));
-            enqueue_steps(P, P->prm.k_int, false);
-            enqueue_sample_eval(P, K, nullptr, 0);
-            HIP_TRY(hipStreamEndCapture(P->stream, &g));
-            hipGraphExec_t ge;
-            HIP_TRY(hipGraphInstantiate(&ge, g, nullptr, nullptr, 0));
-            HIP_TRY(hipGraphDestroy(g));
-            it = P->graphs.emplace(key, ge).first;
+            HIP_TRY(takes_graph(P->stream));
+            hipGraphExec_t ge = nullptr;
+            const hipError_t e = capture_graph(P->stream, [&] {
+                enqueue_steps(P, P->prm.k_int, false);
+                enqueue_sample_eval(P, K, nullptr, 0);
+            }, &ge);
             P->cur = cur0;   // capture did not execute; replay below advances the state
+            HIP_TRY(e);
+            it = P->graphs.emplace(key, ge).first;
         }
         HIP_TRY(hipGraphLaunch(it->second, P->stream));
         P->cur = (cur0 + P->prm.k_int) & 1;

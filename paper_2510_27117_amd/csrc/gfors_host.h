@@ -357,6 +357,14 @@ inline int sync(gfors_problem *P) {
 }
 
 
+// Whether work captured elsewhere can be replayed on a stream: not on the null
+// stream, nor inside a caller's capture.
+hipError_t takes_graph(hipStream_t stream);
+// What f enqueues on `stream`, as an executable graph.  `stream` names a stream of
+// its own while f runs: whatever another thread enqueues meanwhile on the stream
+// that the problem was given stays out of the graph.
+hipError_t capture_graph(hipStream_t &stream, const std::function<void()> &f, hipGraphExec_t *exec);
+
 // Buffers of a problem carved from a workspace (measure mode when the carver
 // has no base) and the candidate-count rule; defined in gfors_api.cpp.
 size_t carve_problem(gfors_problem *P, Carver &cv, int64_t n, int64_t m1, int64_t m2,

@@ -337,8 +337,8 @@ int lu_device_norms(gfors_problem *P) {
 // as a replayed graph of sixteen: launched one by one they cost the host more
 // than the device, and every shape looks the same (the lift product of the
 // 90,000-variable quadratic assignment came out at 4 lanes per row and 12.6 us
-// instead of 64 and 4.7).  A stream that cannot be captured keeps the first figure.
-static float time_launches(hipStream_t s, hipEvent_t e0, hipEvent_t e1, const std::function<void()> &f) {
+// instead of 64 and 4.7).  A stream that takes no graph keeps the first figure.
+static float time_launches(hipStream_t &s, hipEvent_t e0, hipEvent_t e1, const std::function<void()> &f) {
     auto between = [&](const std::function<void()> &g) {
         float ms = 0.f;
         (void)hipEventRecord(e0, s);
@@ -350,22 +350,14 @@ static float time_launches(hipStream_t s, hipEvent_t e0, hipEvent_t e1, const st
     };
     f();
     float per = between([&] { for (int q = 0; q < 5; ++q) f(); }) / 5.f;
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (per >= 0.015f || !s || s == hipStreamPerThread || s == hipStreamLegacy ||
-        hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone)
-        return per;
+    if (per >= 0.015f || s == hipStreamPerThread || takes_graph(s) != hipSuccess) return per;
     constexpr int kReps = 16;
-    hipGraph_t g = nullptr;
     hipGraphExec_t ge = nullptr;
-    if (hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) == hipSuccess) {
-        for (int q = 0; q < kReps; ++q) f();
-        if (hipStreamEndCapture(s, &g) == hipSuccess && g && hipGraphInstantiate(&ge, g, nullptr, nullptr, 0) == hipSuccess) {
-            (void)hipGraphLaunch(ge, s);
-            per = between([&] { (void)hipGraphLaunch(ge, s); (void)hipGraphLaunch(ge, s); }) / (2.f * kReps);
-        }
+    if (capture_graph(s, [&] { for (int q = 0; q < kReps; ++q) f(); }, &ge) == hipSuccess) {
+        (void)hipGraphLaunch(ge, s);
+        per = between([&] { (void)hipGraphLaunch(ge, s); (void)hipGraphLaunch(ge, s); }) / (2.f * kReps);
+        (void)hipGraphExecDestroy(ge);
     }
-    if (ge) (void)hipGraphExecDestroy(ge);
-    if (g) (void)hipGraphDestroy(g);
     (void)hipGetLastError();
     return per;
 }

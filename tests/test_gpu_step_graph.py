@@ -1,6 +1,8 @@
 """Long runs of steps, which replay a captured graph once a problem has launched
 2,048 steps one by one, against the same steps launched singly: the same kernels in
 the same order, so every bit of the state, the counter and the residuals agrees."""
+import ctypes
+import threading
 import time
 
 import numpy as np
@@ -81,3 +83,49 @@ def test_first_long_run_of_a_problem_costs_no_graph(G):
             out.append(time.perf_counter() - t)
         p.close()
     assert min(first) <= 1.25 * min(later), (first, later)
+
+
+@pytest.mark.parametrize("what", ["rounds", "steps", "creation"])
+def test_a_given_stream_is_never_captured(G, what):
+    """Captures run on a stream of the library's own: what other threads enqueue meanwhile on the
+    stream that a problem was given (a step of another problem there) must not end in its graph.
+    Another thread asks all the while whether the given stream is being captured."""
+    import torch
+    hip = ctypes.CDLL("libamdhip64.so")
+    stream = torch.cuda.Stream()
+    handle, status = ctypes.c_void_p(stream.cuda_stream), ctypes.c_int(0)
+    asked, seen, stop = [0], [0], threading.Event()
+
+    def watch():
+        while not stop.is_set():
+            assert hip.hipStreamIsCapturing(handle, ctypes.byref(status)) == 0
+            asked[0] += 1
+            seen[0] += status.value != 0
+
+    prm = G.default_params(k_int=300, K_max=64, power_iters=5, autotune=0)
+    if what == "creation":                  # a factorised problem times its launches as replayed graphs
+        prm.autotune = 1
+        P = I.assignment_qap_like(40, seed=3, q_per_var=6.0, tree="random")
+        T = G.TUReformulation(P, P.meta["tu_pivots"], factored=True)
+    else:
+        p = G.Problem(I.set_cover_columns(20011, 1999, 5, 1), prm, stream=stream)
+        for _ in range(33):
+            p.pdhg_steps(63)
+        p.synchronize()
+    thread = threading.Thread(target=watch)
+    thread.start()
+    for odd in range(6):
+        if what == "rounds":
+            p.set_launch_cfg(**p.launch_cfg())      # drops the graphs: the next rounds capture again
+            p.run_rounds(1, 64)
+        elif what == "steps":
+            p.set_launch_cfg(**p.launch_cfg())
+            p.pdhg_steps(64 + odd % 2)
+        else:
+            T.problem(prm, stream=stream).close()
+    stream.synchronize()
+    stop.set()
+    thread.join()
+    assert asked[0] > 100 and seen[0] == 0, (asked, seen)
+    if what != "creation":
+        p.close()
