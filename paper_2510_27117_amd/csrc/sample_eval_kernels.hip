@@ -735,16 +735,75 @@ __device__ __forceinline__ void flush_planes(uint64_t (&c)[8], int np, uint32_t 
     for (int pl = 0; pl < 8; ++pl) c[pl] = 0;
 }
 
+// The same with a count per word: a shorter loop and fewer registers, twice the adds.
+__device__ __forceinline__ void flush_bits(uint64_t (&c)[8], uint32_t *cnt, int w) {
+    for (int b = 0; b < 64; ++b) {
+        uint32_t v = 0;
+#pragma unroll
+        for (int pl = 0; pl < 8; ++pl) v |= static_cast<uint32_t>((c[pl] >> b) & 1ull) << pl;
+        if (v) atomicAdd(&cnt[64 * w + b], v);
+    }
+#pragma unroll
+    for (int pl = 0; pl < 8; ++pl) c[pl] = 0;
+}
+
 // Word `sub` of variable c's candidates: variables the sampler found
 // deterministic (p = 0 / p = 1: all candidates 0 / 1) are answered from the
 // per-variable kind byte (an L2-resident n-byte array) instead of the 8n W-byte
 // candidate block.
 constexpr int kCoverBatch = 8;    // entries per load stage in the bitwise row evaluation (16 is slower)
 
-// Six wavefronts per SIMD for the long-row form (80 registers): the tiles of the
-// 2M x 200k set cover are then resident in one go (0.31 ms at four, 0.18 at six).
-template <int RU>
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(RU == 1 ? 6 : 4)))
+// Adds a 64-candidate mask to the bit-sliced counts (ripple carry).
+__device__ __forceinline__ void add_plane(uint64_t (&c)[8], uint64_t carry) {
+#pragma unroll
+    for (int pl = 0; pl < 8; ++pl) {
+        const uint64_t t = c[pl] & carry;
+        c[pl] ^= carry;
+        carry = t;
+    }
+}
+__device__ __forceinline__ uint64_t pair_viol(int k, uint64_t P, uint64_t Q) {
+    return ((k & 1) ? (~P & ~Q) : 0ull) | ((k & 2) ? (~P & Q) : 0ull) | ((k & 4) ? (P & ~Q) : 0ull) |
+           ((k & 8) ? (P & Q) : 0ull);
+}
+__device__ __forceinline__ uint64_t set_viol(int kind, uint64_t one, uint64_t two) {
+    return kind == kEvalCover ? ~one : (kind == kEvalAtMostOne ? two : (~one | two));
+}
+// A batch of a row's entries into the masks "at least one / at least two set",
+// which do not depend on their order: column indices, kind bytes and words each
+// loaded together.  WHOLE: all kCoverBatch entries lie before e1.
+template <bool WHOLE>
+__device__ __forceinline__ void cover_batch(int e, int e1, const int *__restrict__ ci, const uint64_t *__restrict__ X,
+                                            const uint8_t *__restrict__ xkind, int W, int sub, uint64_t &one, uint64_t &two) {
+    int cc[kCoverBatch];
+    uint8_t kk[kCoverBatch];
+    uint64_t xx[kCoverBatch];
+#pragma unroll
+    for (int v = 0; v < kCoverBatch; ++v) cc[v] = ci[WHOLE ? e + v : min(e + v, e1 - 1)];
+#pragma unroll
+    for (int v = 0; v < kCoverBatch; ++v) kk[v] = xkind[cc[v]];
+#pragma unroll
+    for (int v = 0; v < kCoverBatch; ++v) {
+        if (!WHOLE && e + v >= e1) kk[v] = 1;
+        xx[v] = kk[v] == 0 ? X[static_cast<int64_t>(cc[v]) * W + sub] : (kk[v] == 2 ? ~0ull : 0ull);
+    }
+#pragma unroll
+    for (int v = 0; v < kCoverBatch; ++v) {
+        two |= one & xx[v];
+        one |= xx[v];
+    }
+}
+// The workgroup's counters of a tile, a count per candidate.
+__device__ __forceinline__ void store_counts(const uint32_t *cnt, int lgWp, int K, int *__restrict__ vpart) {
+    for (int l = threadIdx.x; l < K; l += blockDim.x) {
+        const int w = l >> 6, b = l & 63;
+        vpart[l] = static_cast<int>((cnt[((2 * (b >> 2) + (b & 1)) << lgWp) + w] >> (16 * ((b >> 1) & 1))) & 0xffffu);
+    }
+}
+
+// Six wavefronts per SIMD (80 registers): the tiles of the 2M x 200k set cover are
+// then resident in one go (0.31 ms at four, 0.18 at six).
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6)))
 k_eval_cover(const int *__restrict__ tile_ids, const int *__restrict__ tb0,
              const int *__restrict__ tb1, const int *__restrict__ rows,
              const uint8_t *__restrict__ rkind, const int *__restrict__ rp,
@@ -770,115 +829,145 @@ k_eval_cover(const int *__restrict__ tile_ids, const int *__restrict__ tb0,
 #pragma unroll
     for (int pl = 0; pl < 8; ++pl) c[pl] = 0;
     int since = 0;
-    auto count = [&](uint64_t viol) {
-        uint64_t carry = part == 0 ? viol : 0ull;   // one of the row's parts counts it
-#pragma unroll
-        for (int pl = 0; pl < 8; ++pl) {
-            const uint64_t t = c[pl] & carry;
-            c[pl] ^= carry;
-            carry = t;
-        }
-        ++since;
-    };
-    auto pair_viol = [](int k, uint64_t P, uint64_t Q) {
-        return ((k & 1) ? (~P & ~Q) : 0ull) | ((k & 2) ? (~P & Q) : 0ull) | ((k & 4) ? (P & ~Q) : 0ull) |
-               ((k & 8) ? (P & Q) : 0ull);
-    };
-    // "at least one / at least two set" do not depend on the order of the
-    // entries: kCoverBatch at a time, their column indices, kind bytes and
-    // words each loaded together
-    auto row_viol = [&](int j, int kd) {
-        const int e1 = rp[j + 1], step = kCoverBatch << lgS;
-        uint64_t one = 0, two = 0;
-        auto batch = [&](int e, auto whole) {
-            int cc[kCoverBatch];
-            uint8_t kk[kCoverBatch];
-            uint64_t xx[kCoverBatch];
-#pragma unroll
-            for (int v = 0; v < kCoverBatch; ++v) cc[v] = ci[whole ? e + v : min(e + v, e1 - 1)];
-#pragma unroll
-            for (int v = 0; v < kCoverBatch; ++v) kk[v] = xkind[cc[v]];
-#pragma unroll
-            for (int v = 0; v < kCoverBatch; ++v) {
-                if (!whole && e + v >= e1) kk[v] = 1;
-                xx[v] = kk[v] == 0 ? X[static_cast<int64_t>(cc[v]) * W + sub] : (kk[v] == 2 ? ~0ull : 0ull);
-            }
-#pragma unroll
-            for (int v = 0; v < kCoverBatch; ++v) {
-                two |= one & xx[v];
-                one |= xx[v];
-            }
-        };
-        int e = rp[j] + kCoverBatch * part;
-        for (; e + kCoverBatch <= e1; e += step) batch(e, std::true_type());
-        if (e < e1) batch(e, std::false_type());
-        for (int d = 1 << lgWp; d < 1 << (lgWp + lgS); d <<= 1) {   // the parts of the row
-            const uint64_t o1 = __shfl_xor(static_cast<unsigned long long>(one), d, 64);
-            const uint64_t o2 = __shfl_xor(static_cast<unsigned long long>(two), d, 64);
-            two |= o2 | (one & o1);
-            one |= o1;
-        }
-        const int kind = kd >> 4;
-        return kind == kEvalCover ? ~one : (kind == kEvalAtMostOne ? two : (~one | two));
-    };
-    // RU rows per group and pass: their row data, and the two words of pair
-    // rows, are loaded together (a row's count does not depend on the order
-    // in which rows are added).  Four pay on pair rows (two entries, a chain
-    // of dependent loads each); on long covering rows they cost occupancy.
-    for (int rb = r0 + grp; rb < r1; rb += RU * ngrp) {
+    for (int rr = r0 + grp; rr < r1; rr += ngrp) {
         if (sub >= W) continue;
-        if (since > 255 - RU) {
+        if (since == 255) {
             flush_planes(c, 8, cnt, lgWp, sub);
             since = 0;
         }
-        int j[RU], kd[RU], c0[RU], c1[RU];
-        uint64_t P[RU], Q[RU];
-#pragma unroll
-        for (int u = 0; u < RU; ++u) j[u] = rb + u * ngrp < r1 ? rows[rb + u * ngrp] : -1;
-#pragma unroll
-        for (int u = 0; u < RU; ++u) {
-            kd[u] = j[u] >= 0 ? rkind[j[u]] : 0;
-            c0[u] = j[u] >= 0 ? rp[j[u]] : 0;
-            c1[u] = j[u] >= 0 ? rp[j[u] + 1] - 1 : 0;
+        const int j = rows[rr], kd = rkind[j];
+        uint64_t viol;
+        if ((kd >> 4) == kEvalPair) {
+            const int c0 = ci[rp[j]], c1 = ci[rp[j + 1] - 1];
+            const uint8_t k0 = xkind[c0], k1 = xkind[c1];
+            const uint64_t P = k0 == 0 ? X[static_cast<int64_t>(c0) * W + sub] : (k0 == 2 ? ~0ull : 0ull);
+            const uint64_t Q = k1 == 0 ? X[static_cast<int64_t>(c1) * W + sub] : (k1 == 2 ? ~0ull : 0ull);
+            viol = pair_viol(kd, P, Q);
+        } else {
+            const int e1 = rp[j + 1], step = kCoverBatch << lgS;
+            uint64_t one = 0, two = 0;
+            int e = rp[j] + kCoverBatch * part;
+            for (; e + kCoverBatch <= e1; e += step) cover_batch<true>(e, e1, ci, X, xkind, W, sub, one, two);
+            if (e < e1) cover_batch<false>(e, e1, ci, X, xkind, W, sub, one, two);
+            for (int d = 1 << lgWp; d < 1 << (lgWp + lgS); d <<= 1) {   // the parts of the row
+                const uint64_t o1 = __shfl_xor(static_cast<unsigned long long>(one), d, 64);
+                const uint64_t o2 = __shfl_xor(static_cast<unsigned long long>(two), d, 64);
+                two |= o2 | (one & o1);
+                one |= o1;
+            }
+            viol = set_viol(kd >> 4, one, two);
         }
-#pragma unroll
-        for (int u = 0; u < RU; ++u) {
-            const bool pr = j[u] >= 0 && (kd[u] >> 4) == kEvalPair;
-            c0[u] = pr ? ci[c0[u]] : -1;
-            c1[u] = pr ? ci[c1[u]] : -1;
-        }
-        uint8_t k0[RU], k1[RU];
-#pragma unroll
-        for (int u = 0; u < RU; ++u) {
-            k0[u] = c0[u] >= 0 ? xkind[c0[u]] : 1;
-            k1[u] = c1[u] >= 0 ? xkind[c1[u]] : 1;
-        }
-#pragma unroll
-        for (int u = 0; u < RU; ++u) {
-            P[u] = k0[u] == 0 ? X[static_cast<int64_t>(c0[u]) * W + sub] : (k0[u] == 2 ? ~0ull : 0ull);
-            Q[u] = k1[u] == 0 ? X[static_cast<int64_t>(c1[u]) * W + sub] : (k1[u] == 2 ? ~0ull : 0ull);
-        }
-        uint32_t others = 0;   // rows of the pass that are not pairs
-#pragma unroll
-        for (int u = 0; u < RU; ++u) {
-            if (c0[u] >= 0) count(pair_viol(kd[u], P[u], Q[u]));
-            else if (j[u] >= 0) others |= 1u << u;
-        }
-        while (others) {
-            const int u = __builtin_ctz(others);
-            others &= others - 1;
-            const int jj = rows[rb + u * ngrp];
-            count(row_viol(jj, rkind[jj]));
-        }
+        add_plane(c, part == 0 ? viol : 0ull);   // one of the row's parts counts it
+        ++since;
     }
     // planes in use: those of the most rows that a group of the workgroup can hold
     const int most = min(255, (r1 - r0 + ngrp - 1) / max(ngrp, 1));
     if (sub < W && since && part == 0) flush_planes(c, 32 - __clz(most), cnt, lgWp, sub);
     __syncthreads();
-    for (int l = threadIdx.x; l < K; l += blockDim.x) {
-        const int w = l >> 6, b = l & 63;
-        vpart[static_cast<int64_t>(tile) * K + l] =
-            static_cast<int>((cnt[((2 * (b >> 2) + (b & 1)) << lgWp) + w] >> (16 * ((b >> 1) & 1))) & 0xffffu);
+    store_counts(cnt, lgWp, K, vpart + static_cast<int64_t>(tile) * K);
+}
+
+// The same where most rows are pairs (one or two entries, a chain of dependent
+// loads each): four rows per group and pass, whose row data and two words are
+// loaded together.  A row's count does not depend on the order in which rows are
+// added.  The other rows stay in line with their group: set aside and shared
+// among lanes as above they cost this kernel a tenth of its time.
+// NT = 256 for many tiles: four wavefronts per SIMD and no spills (106 registers)
+// count for more there than the flush, which therefore is the short one.  400 x
+// 4,000 facility location, K = 1024: 217 us (flush_planes: 239; rows set aside
+// and flush_planes: 249), 1,000 x 10,000: 932 (1,045; 1,010).  NT = 1024 for few
+// tiles, where the flush is what takes the time: 100 x 900, K = 512, 34 (short
+// flush 39; 256 threads 69).
+template <int NT>
+__global__ void __launch_bounds__(NT)
+k_eval_pairs(const int *__restrict__ tile_ids, const int *__restrict__ tb0, const int *__restrict__ tb1,
+             const int *__restrict__ rows, const uint8_t *__restrict__ rkind, const int *__restrict__ rp,
+             const int *__restrict__ ci, const uint64_t *__restrict__ X, const uint8_t *__restrict__ xkind, int W, int lgWp,
+             int *__restrict__ vpart, int K) {
+    constexpr int U = 4;
+    constexpr bool kBits = NT == 256;
+    __shared__ uint32_t cnt[kBits ? 4096 : 32 * 64];
+    const int tile = tile_ids[blockIdx.x];
+    const int r0 = tb0[tile], r1 = tb1[tile];
+    for (int l = threadIdx.x; l < (kBits ? K : 32 << lgWp); l += blockDim.x) cnt[l] = 0;
+    __syncthreads();
+    const int sub = threadIdx.x & ((1 << lgWp) - 1);
+    const int grp = threadIdx.x >> lgWp, ngrp = blockDim.x >> lgWp;
+    uint64_t c[8];
+#pragma unroll
+    for (int pl = 0; pl < 8; ++pl) c[pl] = 0;
+    int since = 0;
+    auto flush = [&] {
+        if constexpr (kBits) flush_bits(c, cnt, sub);
+        else flush_planes(c, 8, cnt, lgWp, sub);
+        since = 0;
+    };
+    for (int rb = r0 + grp; rb < r1; rb += U * ngrp) {
+        if (sub < W) {
+            int j[U], kd[U], e0[U], e1[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) j[u] = rb + u * ngrp < r1 ? rows[rb + u * ngrp] : -1;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                kd[u] = j[u] >= 0 ? rkind[j[u]] : 0;
+                e0[u] = j[u] >= 0 ? rp[j[u]] : 0;
+                e1[u] = j[u] >= 0 ? rp[j[u] + 1] : 0;
+            }
+            uint64_t P[U], Q[U];
+            {
+                int c0[U], c1[U];
+                uint8_t k0[U], k1[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const bool pr = j[u] >= 0 && (kd[u] >> 4) == kEvalPair;
+                    c0[u] = pr ? ci[e0[u]] : -1;
+                    c1[u] = pr ? ci[e1[u] - 1] : -1;
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    k0[u] = c0[u] >= 0 ? xkind[c0[u]] : 1;
+                    k1[u] = c1[u] >= 0 ? xkind[c1[u]] : 1;
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    P[u] = k0[u] == 0 ? X[static_cast<int64_t>(c0[u]) * W + sub] : (k0[u] == 2 ? ~0ull : 0ull);
+                    Q[u] = k1[u] == 0 ? X[static_cast<int64_t>(c1[u]) * W + sub] : (k1[u] == 2 ? ~0ull : 0ull);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (j[u] < 0) break;
+                const int kind = kd[u] >> 4;
+                uint64_t viol;
+                if (kind == kEvalPair) {
+                    viol = pair_viol(kd[u], P[u], Q[u]);
+                } else {
+                    uint64_t one = 0, two = 0;
+                    int e = e0[u];
+                    const int ee1 = e1[u];
+                    for (; e + kCoverBatch <= ee1; e += kCoverBatch)
+                        cover_batch<true>(e, ee1, ci, X, xkind, W, sub, one, two);
+                    for (; e < ee1; ++e) {
+                        const int col = ci[e];
+                        const uint8_t k = xkind[col];
+                        const uint64_t x = k == 0 ? X[static_cast<int64_t>(col) * W + sub] : (k == 2 ? ~0ull : 0ull);
+                        two |= one & x;
+                        one |= x;
+                    }
+                    viol = set_viol(kind, one, two);
+                }
+                add_plane(c, viol);
+                if (++since == 255) flush();
+            }
+        }
+    }
+    if (sub < W && since) flush();
+    __syncthreads();
+    int *out = vpart + static_cast<int64_t>(tile) * K;
+    if constexpr (kBits) {
+        for (int l = threadIdx.x; l < K; l += NT) out[l] = static_cast<int>(cnt[l]);
+    } else {
+        store_counts(cnt, lgWp, K, out);
     }
 }
 
@@ -893,10 +982,12 @@ void launch_eval_cover(hipStream_t s, int ntiles, const int *tile_ids, const Til
     // second, nearly empty wave of workgroups trails)
     int threads = 256;
     while (threads < 1024 && static_cast<int64_t>(ntiles) * (2 * threads / 64) <= 4096) threads *= 2;
-    if (pair_rows)
-        k_eval_cover<4><<<ntiles, threads, 0, s>>>(tile_ids, et.b0, et.b1, rows, rkind, rp, ci, X, xkind, W, lg, vpart, K);
+    if (pair_rows && threads == 256)
+        k_eval_pairs<256><<<ntiles, 256, 0, s>>>(tile_ids, et.b0, et.b1, rows, rkind, rp, ci, X, xkind, W, lg, vpart, K);
+    else if (pair_rows)
+        k_eval_pairs<1024><<<ntiles, threads, 0, s>>>(tile_ids, et.b0, et.b1, rows, rkind, rp, ci, X, xkind, W, lg, vpart, K);
     else
-        k_eval_cover<1><<<ntiles, threads, 0, s>>>(tile_ids, et.b0, et.b1, rows, rkind, rp, ci, X, xkind, W, lg, vpart, K);
+        k_eval_cover<<<ntiles, threads, 0, s>>>(tile_ids, et.b0, et.b1, rows, rkind, rp, ci, X, xkind, W, lg, vpart, K);
 }
 
 // ---------------------------------------------------------------------------
