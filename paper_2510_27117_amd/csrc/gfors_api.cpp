@@ -116,7 +116,7 @@ static size_t carve(gfors_problem *P, Carver &cv, int64_t n, int64_t m1, int64_t
     P->rpQ = cv.take<int>(n + 1);
     P->ciQ = cv.take<int>(nnzQ);
     P->valQ = cv.take<int>(nnzQ);
-    P->rowQ = P->packQ = cv.take<int>(nnzQ ? nnzQ + 1 : 0);   // one or the other
+    P->rowQ = P->packQ = cv.take<int>(nnzQ);   // one or the other
     P->rpU = cv.take<int>(nnzQ ? n + 1 : 1);
     P->ciU = cv.take<int>(nnzQ);
     P->valU = cv.take<int>(nnzQ);
@@ -157,9 +157,7 @@ static size_t carve(gfors_problem *P, Carver &cv, int64_t n, int64_t m1, int64_t
     P->primal_order = cv.take<int>(n);
     P->cover_ids = cv.take<int>(b.et);
     P->general_ids = cv.take<int>(b.et);
-    // one instance: the 3D-assignment sampler's scratch; several: their row ranges
-    P->a3_part = T == 1 ? cv.take<int>(2 * kA3MaxN) : nullptr;
-    P->inst_rows = T > 1 ? cv.take<int>(2 * (static_cast<int64_t>(T) + 1)) : nullptr;
+    P->a3_part = cv.take<int>(2 * kA3MaxN);
     P->rep_rp = cv.take<int>(prm->repair_row0 >= 0 ? m1 + 1 : 1);
     P->rep_var = cv.take<int>(prm->repair_row0 >= 0 ? nnzK : 1);
     P->mf_cap = prm->eval_mfma && m > 0 ? mf_digit_cap(nnzK, m) : 0;
@@ -727,9 +725,8 @@ int gfors_create_problem(const gfors_csr *A, const int64_t *b, const gfors_csr *
         if (!P->qsym && (rc = upload(s, P->rowQ, rowQ.data(), P->nnzQ))) return rc;
         P->qpacked = P->qsym && n <= (int64_t{1} << 24) &&
                      std::all_of(valQ.begin(), valQ.end(), [](int v) { return v >= -128 && v <= 127; });
-        // one more for the code kernel's padding: value 0 at the first index past the variables' blocks
-        std::vector<int> packQ(P->qpacked ? P->nnzQ + 1 : 0, static_cast<int>(64 * ceil_div(n, 64)));
-        for (int64_t e = 0; e + 1 < static_cast<int64_t>(packQ.size()); ++e)
+        std::vector<int> packQ(P->qpacked ? P->nnzQ : 0);
+        for (size_t e = 0; e < packQ.size(); ++e)
             packQ[e] = static_cast<int>(static_cast<uint32_t>(ciQ[e]) | static_cast<uint32_t>(valQ[e]) << 24);
         int dev = 0, lds_max = 0;
         HIP_TRY(hipGetDevice(&dev));
@@ -739,7 +736,7 @@ int gfors_create_problem(const gfors_csr *A, const int64_t *b, const gfors_csr *
         int64_t longest = 0;
         for (int64_t i = 0; i < n; ++i) longest = std::max<int64_t>(longest, rpQ[i + 1] - rpQ[i]);
         P->qcode_pays = P->qcode_ok && P->nnzQ <= kCodesPerRow * n && longest <= kCodesLongest;
-        if (P->qpacked && (rc = upload(s, P->packQ, packQ.data(), P->nnzQ + 1))) return rc;
+        if (P->qpacked && (rc = upload(s, P->packQ, packQ.data(), P->nnzQ))) return rc;
         if ((rc = sync(P))) return rc;
         if (P->qsym) {
             const int64_t nu = static_cast<int64_t>(ciU.size());
@@ -1389,7 +1386,11 @@ static int setup_resident(gfors_problem *P, const std::vector<int64_t> &off, con
     sh.nr = static_cast<int>(mr);
     for (int64_t j = 0; j < P->m; ++j) sh.len_r = std::max(sh.len_r, rp[j + 1] - rp[j]);
     for (int64_t i = 0; i < P->n; ++i) sh.len_c = std::max(sh.len_c, rpT[i + 1] - rpT[i]);
-    if (P->inst_rows) {
+    if (T > 1 && !sh.dense16) {
+        // the instances' row ranges, in the place of the padded coefficients that
+        // only dense int16 rows have (two bytes for each of nnz + 8 m entries)
+        if (static_cast<size_t>(P->blk_pval_cap) * sizeof(int16_t) < 2 * (static_cast<size_t>(T) + 1) * sizeof(int)) return GFORS_OK;
+        P->inst_rows = reinterpret_cast<int *>(P->blk_pval);
         std::vector<int> ir(2 * (static_cast<size_t>(T) + 1));
         for (int t = 0; t <= T; ++t) {
             ir[2 * t] = static_cast<int>(off[3 * t + 1]);

@@ -224,7 +224,7 @@ struct gfors_problem {
     // problem qualifies, its shape, and whether that path is in use
     bool res_ok = false, res_on = false;
     ResidentShape rsh;
-    int *inst_rows = nullptr;   // [T+1][2] first inequality / equality row of each instance (T > 1)
+    int *inst_rows = nullptr;   // [T+1][2] first inequality / equality row of each instance (T > 1; in blk_pval)
     int16_t *val16 = nullptr, *sellT_val16 = nullptr;
     float *rowinv32 = nullptr;          // 1/||a_j|| (0 for a zero row): the GNN's edge weights
     float gnn_ictmax = 1.f, gnn_irtmax = 1.f;

@@ -188,7 +188,9 @@ size_t lu_carve(gfors_problem *P, Carver &cv, const gftu::TuFactored &F, const g
     L.hch_e0 = cv.take<int>(L.nhch);
     L.hch_e1 = cv.take<int>(L.nhch);
     L.hch_first = cv.take<int>(L.heavy_rows + 1);
-    L.hpart = cv.take<double>(L.nhch);
+    // free during steps: a vector of the power iteration (a row has a chunk for
+    // each kLuRowChunk entries, so hardly ever more chunks than rows or variables)
+    L.hpart = L.nhch <= std::max(nfull, m) ? P->pw : cv.take<double>(L.nhch);
     return cv.off;
 }
 

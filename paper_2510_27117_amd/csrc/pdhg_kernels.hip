@@ -443,14 +443,17 @@ k_primal_codes(int n, const int *__restrict__ rpQ, const int *__restrict__ packQ
     const float rh = static_cast<float>(rho[0]);
     int w[LPR][U];
     int e0[LPR], e1[LPR];
-    const int pad = rpQ[n];   // the entry after the last one: value 0 at a variable whose code is 0
+    // past a row's end (the last entry is loaded instead): value 0 at a variable whose code is 0
+    const int last = rpQ[n] - 1, pad = 64 * nblk;
 #pragma unroll
     for (int p = 0; p < LPR; ++p) {
         const int src = (lane & ~(LPR - 1)) + p;
         e0[p] = __shfl(r0, src, 64) + sub;
         e1[p] = __shfl(r1, src, 64);
 #pragma unroll
-        for (int u = 0; u < U; ++u) w[p][u] = packQ[e0[p] + u * LPR < e1[p] ? e0[p] + u * LPR : pad];
+        for (int u = 0; u < U; ++u) w[p][u] = packQ[min(e0[p] + u * LPR, last)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) w[p][u] = e0[p] + u * LPR < e1[p] ? w[p][u] : pad;
     }
     for (int t0 = threadIdx.x; t0 < nblk; t0 += 4 * blockDim.x) {
         uint4 q[4];
