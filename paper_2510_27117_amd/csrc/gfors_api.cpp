@@ -2732,14 +2732,14 @@ int gnn_run(gfors_gnn *G, gfors_problem *P, const float *x, const float *y, cons
         launch_gnn_mask(s, n, a.dHv, a.Hv[l + 1], a.dZ, G->part, kGnnMaxParts, glay + 8256 + 2 * 4096);
         launch_gnn_wgrad(s, n, a.Hv[l], a.Sv[l], a.dZ, G->part, kGnnMaxParts, glay + 8256, glay + 8256 + 4096);
         launch_gnn_dense_bwd_in(s, n, a.dZ, wbv, a.dHvp, a.dS, 0);
-        launch_gnn_spmm(s, true, false, 2, m, P->dual_order, P->gnn_rh, P->gnn_rm, P->rp, P->ci, val,
-                        P->rowinv32, a.dS, a.dHc);
+        launch_gnn_spmm_add(s, true, m, P->dual_order, P->gnn_rh, P->gnn_rm, P->rp, P->ci, val, P->rowinv32, a.dS,
+                            a.dHc);
         // constraint side of round l
         launch_gnn_mask(s, m, a.dHc, a.Hc[l + 1], a.dZ, G->part, kGnnMaxParts, glay + 2 * 4096);
         launch_gnn_wgrad(s, m, a.Hc[l], a.Sc[l], a.dZ, G->part, kGnnMaxParts, glay, glay + 4096);
         launch_gnn_dense_bwd_in(s, m, a.dZ, wbc, a.dHcp, a.dS, 0);
-        launch_gnn_spmm(s, false, false, 2, n, P->primal_order, P->gnn_ch, P->gnn_cm, P->rpT, P->ciT, valT,
-                        P->rowinv32, a.dS, a.dHvp);
+        launch_gnn_spmm_add(s, false, n, P->primal_order, P->gnn_ch, P->gnn_cm, P->rpT, P->ciT, valT, P->rowinv32,
+                            a.dS, a.dHvp);
         std::swap(a.dHv, a.dHvp);
         std::swap(a.dHc, a.dHcp);
     }

@@ -35,11 +35,10 @@ constexpr int kGnnShortLen = 16;     // short up to this many
 void launch_gnn_embed(hipStream_t s, int64_t n, int64_t m, int m1, const float *x, const float *y,
                       const float *ct, const float *rt, float ictmax, float irtmax,
                       const float *theta, uint16_t *Hv, uint16_t *Hc);
-// nodes in `order` (longest first): the first nheavy have >= 1024 entries, the
-// next nmedium more than 16, the rest at most 16
-void launch_gnn_spmm(hipStream_t s, bool rows, bool in_bf16, int out_mode, int64_t nrows,
-                     const int *order, int nheavy, int nmedium, const int *rp, const int *ci,
-                     const int *val, const float *rowinv, const void *in, void *out);
+// out += E in over all nodes of a side, in `order` (longest first): the first
+// nheavy have >= 1024 entries, the next nmedium more than 16, the rest at most 16
+void launch_gnn_spmm_add(hipStream_t s, bool rows, int64_t nrows, const int *order, int nheavy, int nmedium,
+                         const int *rp, const int *ci, const int *val, const float *rowinv, const float *in, float *out);
 // out = relu([H | S] W + bias) with S = E in of the side's nodes; S receives the
 // messages of the nheavy + nmedium long nodes, and of all of them with store_s
 void launch_gnn_layer(hipStream_t s, bool rows, int64_t N, const int *order, int nheavy, int nmedium, const int *rp,

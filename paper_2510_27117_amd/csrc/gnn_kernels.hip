@@ -97,14 +97,14 @@ k_gnn_embed(int64_t n, int64_t m, int nbv, int m1, const float *__restrict__ x, 
 // out_r = sum_e E_e in[col_e] with E_e = val_e * rowinv[row of the entry]:
 //   ROWS = true : CSR of [A; B]  (r = constraint row, col = variable, rowinv[r])
 //   ROWS = false: CSR of [A; B]^T (r = variable, col = row j,        rowinv[j])
-// IN_BF16: input features BF16 (else FP32); OUT: 0 store BF16, 1 store FP32,
-// 2 add into FP32.
+// IN_BF16: input features BF16 (else FP32); OUT: 0 store BF16, 2 add into FP32.
 //
 // Nodes come in `order`, longest first, in three classes by entry count:
 //   heavy  (>= kGnnHeavy)  a workgroup of 8 wavefronts per node;
 //   medium (> kGnnShort)   one wavefront per node;
-//   short                  16 lanes per node (four nodes per wavefront); forward
-//                          (BF16) messages of short nodes are k_gnn_layer's.
+//   short                  16 lanes per node (four nodes per wavefront); of the
+//                          backward (FP32) pass only: k_gnn_layer makes the
+//                          forward (BF16) messages of short nodes.
 // In the heavy and medium kernels a lane handles features 4f..4f+3 (f = lane
 // & 15) of entry slot q = lane >> 4, so one load instruction gathers four
 // neighbours' feature rows; eight such loads are issued before any is used.
@@ -310,27 +310,30 @@ k_gnn_spmm_short(int k0, int k1, const int *__restrict__ order, const int *__res
     }
 }
 
-void launch_gnn_spmm(hipStream_t s, bool rows, bool in_bf16, int out_mode, int64_t nrows,
-                     const int *order, int nheavy, int nmedium, const int *rp, const int *ci,
-                     const int *val, const float *rowinv, const void *in, void *out) {
-    if (nrows <= 0) return;
-    const int k1 = nheavy, k2 = nheavy + nmedium, k3 = static_cast<int>(nrows);
+// The nheavy + nmedium long nodes (the first of `order`).
+template <bool ROWS, bool IN_BF16, int OUT>
+static void spmm_long(hipStream_t s, const int *order, int nheavy, int nmedium, const int *rp, const int *ci,
+                      const int *val, const float *rowinv, const void *in, void *out) {
+    const int k1 = nheavy, k2 = nheavy + nmedium;
     const int bh = std::min(nheavy, 1024);
-    int64_t bm = (static_cast<int64_t>(nmedium) * 64 + 255) / 256;
-    if (bm > 8192) bm = 8192;
-    int64_t bs = (static_cast<int64_t>(k3 - k2) * 16 + 255) / 256;
-    if (bs > 16384) bs = 16384;
-#define GF_SP(R, IB, O)                                                                                          \
-    do {                                                                                                         \
-        if (bh > 0) k_gnn_spmm_heavy<R, IB, O><<<bh, 512, 0, s>>>(k1, order, rp, ci, val, rowinv, in, out);      \
-        if (bm > 0) k_gnn_spmm_medium<R, IB, O><<<static_cast<int>(bm), 256, 0, s>>>(k1, k2, order, rp, ci, val, rowinv, in, out); \
-        if (!IB && bs > 0) k_gnn_spmm_short<R, O><<<static_cast<int>(bs), 256, 0, s>>>(k2, k3, order, rp, ci, val, rowinv, in, out); \
-    } while (0)
-#define GF_SP2(R, IB) if (out_mode == 0) GF_SP(R, IB, 0); else if (out_mode == 1) GF_SP(R, IB, 1); else GF_SP(R, IB, 2)
-    if (rows) { if (in_bf16) { GF_SP2(true, true); } else { GF_SP2(true, false); } }
-    else { if (in_bf16) { GF_SP2(false, true); } else { GF_SP2(false, false); } }
-#undef GF_SP2
-#undef GF_SP
+    const int bm = static_cast<int>(std::min<int64_t>((static_cast<int64_t>(nmedium) * 64 + 255) / 256, 8192));
+    if (bh > 0) k_gnn_spmm_heavy<ROWS, IN_BF16, OUT><<<bh, 512, 0, s>>>(k1, order, rp, ci, val, rowinv, in, out);
+    if (bm > 0) k_gnn_spmm_medium<ROWS, IN_BF16, OUT><<<bm, 256, 0, s>>>(k1, k2, order, rp, ci, val, rowinv, in, out);
+}
+
+template <bool ROWS>
+static void spmm_add(hipStream_t s, int64_t nrows, const int *order, int nheavy, int nmedium, const int *rp, const int *ci,
+                     const int *val, const float *rowinv, const float *in, float *out) {
+    spmm_long<ROWS, false, 2>(s, order, nheavy, nmedium, rp, ci, val, rowinv, in, out);
+    const int k2 = nheavy + nmedium, k3 = static_cast<int>(nrows);
+    const int bs = static_cast<int>(std::min<int64_t>((static_cast<int64_t>(k3 - k2) * 16 + 255) / 256, 16384));
+    if (bs > 0) k_gnn_spmm_short<ROWS, 2><<<bs, 256, 0, s>>>(k2, k3, order, rp, ci, val, rowinv, in, out);
+}
+
+void launch_gnn_spmm_add(hipStream_t s, bool rows, int64_t nrows, const int *order, int nheavy, int nmedium,
+                         const int *rp, const int *ci, const int *val, const float *rowinv, const float *in, float *out) {
+    if (rows) spmm_add<true>(s, nrows, order, nheavy, nmedium, rp, ci, val, rowinv, in, out);
+    else spmm_add<false>(s, nrows, order, nheavy, nmedium, rp, ci, val, rowinv, in, out);
 }
 
 // ------------------------------------------------------------------ MFMA GEMM
@@ -589,7 +592,8 @@ void launch_gnn_layer(hipStream_t s, bool rows, int64_t N, const int *order, int
                       uint16_t *S, bool store_s, const uint16_t *BT, const float *bias, uint16_t *out) {
     if (N <= 0) return;
     const int64_t k2 = static_cast<int64_t>(nheavy) + nmedium;
-    launch_gnn_spmm(s, rows, true, 0, k2, order, nheavy, nmedium, rp, ci, val, rowinv, in, S);
+    if (rows) spmm_long<true, true, 0>(s, order, nheavy, nmedium, rp, ci, val, rowinv, in, S);
+    else spmm_long<false, true, 0>(s, order, nheavy, nmedium, rp, ci, val, rowinv, in, S);
     // enough workgroups to fill the device; each stages W once
     const int grid = std::min(gemm_grid(N), 2048);
     if (rows)
