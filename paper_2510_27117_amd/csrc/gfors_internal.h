@@ -536,9 +536,11 @@ void launch_lu_dual(hipStream_t s, int lpr, const LuDualArgs &A);
 void launch_lu_dual_heavy(hipStream_t s, const LuHeavyArgs &A);
 // One workgroup for what lies between the row sums and the primal step: the
 // heavy rows' updates, the pivot gradient and both transposed solves; and for
-// the lift's two solves.  lu_fits: whether a pair of solves qualifies.
+// the lift's two solves.  lu_fits: whether a pair of solves qualifies (not
+// without levels: there is nothing to save then).  lu_threads: its workgroup.
 constexpr int kLuOneMax = 1024;   // pivots of the one-workgroup form (a thread each)
 bool lu_fits(const LuSolve &a, const LuSolve &b);
+int lu_threads(int r);
 void launch_lu_mid(hipStream_t s, const LuHeavyArgs &H, int lpr, bool hasq, int r, int nk, const int *rpT,
                    const int *ciT, const int *valT, const float *wy, const int *rpQ, const int *ciQ, const int *valQ,
                    const float *x, const float *two_so, const LuSolve &a, const LuSolve &b, double *v);

@@ -67,6 +67,7 @@ struct LuForm {
     int heavy_rows = 0;   // lifted rows of kHeavyLen+ entries (a prefix of dual_order)
     // their chunks of kLuRowChunk entries (a workgroup each) and chunk sums
     int nhch = 0;
+    int64_t pivot_entries = 0;   // of the lifted rows and Q in the pivots' columns (their gradient)
     int *hch_row = nullptr, *hch_e0 = nullptr, *hch_e1 = nullptr, *hch_first = nullptr;
     double *hpart = nullptr;
     std::vector<int> h_hch_row, h_hch_e0, h_hch_e1, h_hch_first;
@@ -227,6 +228,8 @@ void lu_plan(gfors_problem *P, const gftu::TuFactored &F, const gfors_params &pr
         }
         L.nhch = static_cast<int>(L.h_hch_row.size());
     }
+    L.pivot_entries = std::count_if(F.KLci.begin(), F.KLci.end(), [&](int32_t c) { return c >= F.nk; });
+    if (L.hasQ) L.pivot_entries += F.QLrp[F.nk + F.r] - F.QLrp[F.nk];
     L.nslot = static_cast<int>(L.h_slot_row.size());
     L.nqch = static_cast<int>(L.h_qch_row.size());
     const gftu::HostTrsv *hs[4] = {&F.Lf, &F.Ub, &F.Utf, &F.Ltb};
@@ -364,6 +367,20 @@ static float time_launches(hipStream_t &s, hipEvent_t e0, hipEvent_t e1, const s
     return per;
 }
 
+// Whether one workgroup is ahead with what lies between the row sums and the
+// primal step.  It saves three launches and the levels' staging, but takes the
+// pivots' gradient alone: up to six entries a thread, more where the solves are
+// deep.  us a step, in one : apart (both forms give the same bits):
+//   399 pivots of a random tree, 4 entries of Q a variable 25.1 : 26.1, 20 29.8 :
+//   26.8, 40 34.0 : 26.8; 119 pivots and 400 of Q 51.9 : 28.0; 100 long rows 39.2 :
+//   28.3; 599 pivots, 10 of Q 40.1 : 39.0, 999 67.5 : 60.2; a path of 79 pivots 48.5 :
+//   55.6, of 299 138.6 : 163.9; 300 pivots without levels 14.7 : 13.9.
+static bool mid_fits(const LuForm &L) {
+    const LuSolve a = L.Utf.view(), b = L.Ltb.view();
+    const int64_t levels = static_cast<int64_t>(L.Utf.hlvl.size() + L.Ltb.hlvl.size()) - 2;
+    return lu_fits(a, b) && L.pivot_entries <= lu_threads(static_cast<int>(L.r)) * std::max<int64_t>(6, levels / 8);
+}
+
 // Lanes per row of the SpMV-like kernels of a step, timed on the problem
 // (time_launches); the state is reset after.
 int lu_autotune(gfors_problem *P) {
@@ -392,7 +409,7 @@ int lu_autotune(gfors_problem *P) {
         });
     if (r > 0) {
         best_of({1, 4, 16, 64}, L.lpr_tail, [&](int l) {
-            if (lu_fits(L.Utf.view(), L.Ltb.view()))
+            if (mid_fits(L))
                 launch_lu_mid(s, LuHeavyArgs(), l, L.hasQ, r, nk, P->rpT, P->ciT, P->valT, P->wy, P->rpQ, P->ciQ, P->valQ,
                               P->xbuf[0], P->di.two_so, L.Utf.view(), L.Ltb.view(), L.v64);
             else
@@ -471,10 +488,8 @@ void lu_enqueue_steps(gfors_problem *P, int nsteps, bool want_res, KTimer *tm) {
             TE(0);
         }
         TB(1);
-        // one workgroup takes the heavy rows' updates, the pivot gradient and the
-        // transposed solves while the pivots fit its threads
-        const bool mid = lu_fits(L.Utf.view(), L.Ltb.view());
-        if (mid) {
+        // the heavy rows' updates, the pivot gradient and the transposed solves
+        if (mid_fits(L)) {
             launch_lu_mid(s, H, L.lpr_tail, L.hasQ, r, nk, P->rpT, P->ciT, P->valT, P->wy, P->rpQ, P->ciQ, P->valQ,
                           P->xbuf[a], P->di.two_so, L.Utf.view(), L.Ltb.view(), L.v64);
         } else {

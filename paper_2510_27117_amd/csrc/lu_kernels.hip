@@ -536,7 +536,8 @@ k_lu_lift(int r, LuRun S1, LuRun S2, const double *__restrict__ t, LuOut out) {
 
 bool lu_fits(const LuSolve &a, const LuSolve &b) {
     auto one = [](const LuSolve &s) { return s.nseg == 0 || (s.nseg == 1 && !s.seg[0].wide && s.use_lds); };
-    return a.r > 0 && a.r <= kLuOneMax && one(a) && one(b) && a.use_lds && b.use_lds;
+    auto deep = [](const LuSolve &s) { return s.nseg > 0 && s.seg[0].b - s.seg[0].a > 1; };
+    return a.r > 0 && a.r <= kLuOneMax && one(a) && one(b) && a.use_lds && b.use_lds && (deep(a) || deep(b));
 }
 static LuRun lu_run_of(const LuSolve &s) {
     LuRun S;
@@ -552,7 +553,7 @@ static LuRun lu_run_of(const LuSolve &s) {
     }
     return S;
 }
-static int lu_threads(int r) { return r <= 256 ? 256 : (r <= 512 ? 512 : kLuOneMax); }
+int lu_threads(int r) { return r <= 256 ? 256 : (r <= 512 ? 512 : kLuOneMax); }
 
 void launch_lu_mid(hipStream_t s, const LuHeavyArgs &H, int lpr, bool hasq, int r, int nk, const int *rpT,
                    const int *ciT, const int *valT, const float *wy, const int *rpQ, const int *ciQ, const int *valQ,
