@@ -17,8 +17,11 @@
  *   - Device memory: the caller supplies ONE device workspace of at least
  *     gfors_workspace_bytes() bytes and a HIP stream; the library carves all of
  *     its device buffers out of that workspace, never frees it, and enqueues all
- *     device work on that stream.  The workspace must stay alive until
- *     gfors_destroy_problem().  Device pointers taken by a call (p_override,
+ *     device work on that stream.  (The HIP runtime keeps what an executable
+ *     graph needs: gfors_run_rounds with use_graph, and gfors_pdhg_steps once a
+ *     problem has launched 2,048 steps in calls of its own, make one for each of
+ *     the two state buffers.  Captures run on a stream of the library's own.)
+ *     The workspace must stay alive until gfors_destroy_problem().  Device pointers taken by a call (p_override,
  *     viol_dev, obj_dev) are read/written on the same stream.
  *   - Calls marked "async" only enqueue work; device faults surface as
  *     GFORS_E_HIP at the next synchronising call.  A handle is not thread-safe.
@@ -102,7 +105,7 @@ typedef struct {
  *                by a launch of its own (one thread per row); runs of narrower
  *                levels share one one-workgroup launch.  Default 4096, >= 1.
  *   lu_lds       factorised TU problems only: 1 (default) stages the solved
- *                vector in LDS for a one-workgroup run when it fits in 64 KiB;
+ *                vector in LDS for a one-workgroup run when it fits in 128 KiB;
  *                0 keeps it in global memory.  Results are identical. */
 typedef struct {
     double sigma, tau1, tau2;
@@ -473,7 +476,8 @@ int gfors_tu_factor_info(gfors_tu *U, int64_t *info);
  *     ||Q'|| are FP64 power iterations whose products lift v to
  *     (v, S v) and project with S^T (FP64 triangular solves);
  *   - each PDHG step solves with L, U (lift of x_k) and U^T, L^T (S^T of the
- *     pivot part of the gradient), in FP32, level by level;
+ *     pivot part of the gradient), level by level; sums, updates and solves
+ *     run in FP64 and are rounded once to the FP32 state;
  *   - EvalBest solves every candidate's pivot variables exactly (int32) and
  *     checks the original rows on the lifted integer point: the violation
  *     count and objective equal those of the explicit reformulated model;

@@ -1814,11 +1814,14 @@ static void launch_codes(gfors_problem *P, int lpr, int from, const float *x_in,
 // Autotuner: time every candidate launch shape of the dual and primal SpMV on
 // this problem's own data (HIP events, 1 warm-up + 5 timed launches each) and
 // keep the fastest.  Outputs go to buffers that carry no state at this point.
-// At creation (with_eval) the vectors hold a stand-in for an iterate under way
-// (15 % of xbar and 56 % of wy nonzero, the shares that the large set cover settles
-// at): at x = 0, y = 0 the zero-skipping shapes cannot be told apart from
-// the others, and on that problem the choice cost 45 us against 38 per primal
-// step.  A shape pays for the bitmap pass that it makes the step run.
+// At creation (with_eval) the vectors hold a stand-in for an iterate under way,
+// 15 % of xbar and 56 % of wy nonzero.  At x = 0, y = 0 every zero-skipping shape
+// skips all its gathers and looks better than it will be.  The shares are those
+// that the 2M x 200k set cover settles at after some twenty rounds (there the
+// choice at zero cost 45 us against 38 per primal step; its first steps have more
+// nonzeros and gain a few percent); a problem that settles elsewhere is tuned on its
+// own iterate by gfors_autotune.  A shape pays for the bitmap pass that it makes
+// the step run.
 static int autotune(gfors_problem *P, bool with_eval) {
     hipStream_t s = P->stream;
     hipEvent_t e0, e1;

@@ -21,10 +21,11 @@ namespace {
 // Sums of a step's rows, its updates and its solves run in FP64 and are rounded
 // once, to the FP32 state: the launches take some microseconds and wait on loads,
 // so the wider adds are free, and the order of the lanes no longer shows.  Error of
-// the duals after 300 steps against FP64 (2-norm, eight seeds each; FP32
-// throughout -> now): 90,000-variable quadratic assignment 1.7 - 28e-6 -> 0.2 -
-// 3.8e-6, 28,900 variables 0.2 - 15e-6 -> 0.3 - 0.8e-6, 1,600 0.3 - 1.0e-6 -> 0.2 -
-// 0.4e-6.
+// the duals after 300 steps against FP64 (2-norm, medians of eight seeds; FP32
+// throughout -> now): quadratic assignments of 100 variables 0.84e-6 -> 0.35e-6,
+// 1,600 1.9e-6 -> 0.42e-6, 6,400 1.7e-6 -> 0.38e-6, 28,900 4.2e-6 -> 0.50e-6.  What
+// is left is the rounding of the state itself, which decides on the smallest (36
+// variables: 0.17 - 5.7e-6 -> 0.50 - 6.6e-6, medians 0.79e-6 and 0.75e-6).
 __device__ __forceinline__ double dmad(int a, float x, double s) {
     return fma(static_cast<double>(a), static_cast<double>(x), s);
 }
