@@ -18,9 +18,10 @@
  *     gfors_workspace_bytes() bytes and a HIP stream; the library carves all of
  *     its device buffers out of that workspace, never frees it, and enqueues all
  *     device work on that stream.  (The HIP runtime keeps what an executable
- *     graph needs: gfors_run_rounds with use_graph, and gfors_pdhg_steps once a
- *     problem has launched 2,048 steps in calls of its own, make one for each of
- *     the two state buffers.  Captures run on a stream of the library's own.)
+ *     graph needs: gfors_run_rounds with use_graph, and gfors_pdhg_steps of 64
+ *     steps or more from a problem's second such call on, make one for each of
+ *     the two state buffers.  Captures run on streams of the library's own, up to
+ *     four of which are kept while any problem lives.)
  *     The workspace must stay alive until gfors_destroy_problem().  Device pointers taken by a call (p_override,
  *     viol_dev, obj_dev) are read/written on the same stream.
  *   - Calls marked "async" only enqueue work; device faults surface as

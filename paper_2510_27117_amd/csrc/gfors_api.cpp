@@ -34,20 +34,75 @@ hipError_t takes_graph(hipStream_t stream) {
     return e;
 }
 
+namespace {
+// Streams for captures, at most kIdle of them kept for the next one while any
+// problem lives: making one takes 0.25 ms (3 ms the first time in a process), as
+// much as making the graph itself.
+struct CaptureStreams {
+    static constexpr size_t kIdle = 4;
+    std::mutex m;
+    int holders = 0;
+    std::vector<std::pair<int, hipStream_t>> idle;   // device, stream
+};
+CaptureStreams &capture_streams() {
+    static CaptureStreams *c = new CaptureStreams;   // outlives every static object
+    return *c;
+}
+hipError_t take_capture_stream(int dev, hipStream_t *s) {
+    CaptureStreams &c = capture_streams();
+    {
+        std::lock_guard<std::mutex> lock(c.m);
+        for (size_t i = 0; i < c.idle.size(); ++i)
+            if (c.idle[i].first == dev) {
+                *s = c.idle[i].second;
+                c.idle.erase(c.idle.begin() + static_cast<std::ptrdiff_t>(i));
+                return hipSuccess;
+            }
+    }
+    int now = 0;
+    hipError_t e = hipGetDevice(&now);
+    if (e == hipSuccess && dev != now) e = hipSetDevice(dev);
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(s, hipStreamNonBlocking);
+    if (dev != now) (void)hipSetDevice(now);
+    return e;
+}
+void give_capture_stream(int dev, hipStream_t s) {
+    CaptureStreams &c = capture_streams();
+    {
+        std::lock_guard<std::mutex> lock(c.m);
+        if (c.holders > 0 && c.idle.size() < CaptureStreams::kIdle) {
+            c.idle.push_back({dev, s});
+            return;
+        }
+    }
+    (void)hipStreamDestroy(s);
+}
+}  // namespace
+
+CaptureHold::CaptureHold() {
+    CaptureStreams &c = capture_streams();
+    std::lock_guard<std::mutex> lock(c.m);
+    c.holders += 1;
+}
+CaptureHold::~CaptureHold() {
+    CaptureStreams &c = capture_streams();
+    std::vector<std::pair<int, hipStream_t>> gone;
+    {
+        std::lock_guard<std::mutex> lock(c.m);
+        if (--c.holders == 0) gone.swap(c.idle);
+    }
+    for (auto &p : gone) (void)hipStreamDestroy(p.second);
+}
+
 hipError_t capture_graph(hipStream_t &stream, const std::function<void()> &f, hipGraphExec_t *exec) {
     const hipStream_t given = stream;
     hipStream_t own = nullptr;
     hipGraph_t g = nullptr;
-    int now = 0, dev = 0;
-    hipError_t e = hipGetDevice(&now);
-    if (e == hipSuccess && hipStreamGetDevice(given, &dev) != hipSuccess) {
-        (void)hipGetLastError();
-        dev = now;
-    }
-    if (e == hipSuccess && dev != now) e = hipSetDevice(dev);
-    if (e == hipSuccess) e = hipStreamCreateWithFlags(&own, hipStreamNonBlocking);
-    if (dev != now) (void)hipSetDevice(now);
-    if (e == hipSuccess) e = hipStreamBeginCapture(own, hipStreamCaptureModeThreadLocal);
+    int dev = 0;
+    hipError_t e = hipStreamGetDevice(given, &dev);
+    if (e == hipSuccess) e = take_capture_stream(dev, &own);
+    if (e != hipSuccess) return e;
+    e = hipStreamBeginCapture(own, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
         stream = own;
         f();
@@ -56,7 +111,9 @@ hipError_t capture_graph(hipStream_t &stream, const std::function<void()> &f, hi
         if (e == hipSuccess) e = hipGraphInstantiate(exec, g, nullptr, nullptr, 0);
     }
     if (g) (void)hipGraphDestroy(g);
-    if (own) (void)hipStreamDestroy(own);
+    // a stream whose capture failed is not kept
+    if (e == hipSuccess) give_capture_stream(dev, own);
+    else (void)hipStreamDestroy(own);
     return e;
 }
 }  // namespace gfh
@@ -2210,13 +2267,12 @@ static hipGraphExec_t step_chunk_graph(gfors_problem *P) {
 int gfors_pdhg_steps(gfors_problem *P, int32_t nsteps, int32_t want_residuals) {
     if (!P || nsteps < 0) return fail(GFORS_E_ARG, "gfors_pdhg_steps: bad argument");
     if (nsteps == 0) return GFORS_OK;
-    // Long runs replay a graph of kStepChunk steps: a launch costs the host about
-    // 4 us, as much as the step's kernels take on mid-sized problems, so replayed
-    // steps are 3 to 20 % faster.  Making the graph costs as much as is gained over
-    // 400 to 3,500 steps (set cover of 30,000 x 3,000, 100 steps: 556 us launched,
-    // 536 replayed, 1,242 with the graph made first; 20,011 x 1,999: 560, 534,
-    // 735), so it is made once a problem has launched about as many.  The residual
-    // step is launched by itself.
+    // Long runs replay a graph of kStepChunk steps: two launches cost the host 5 to
+    // 8 us, as much as the step's kernels take on mid-sized problems (100 steps of a
+    // set cover of 20,011 x 1,999: 580 us launched, 541 replayed with a fast host,
+    // 920 and 700 with a slow one).  Making the graph takes about 0.25 ms, so the
+    // first kStepsBeforeGraph steps of a problem, a single long run among them, are
+    // launched.  The residual step is launched by itself.
     int left = nsteps;
     if (!P->res_on && left >= 2 * kStepChunk && P->steps_launched >= kStepsBeforeGraph)
         if (const hipGraphExec_t ge = step_chunk_graph(P))

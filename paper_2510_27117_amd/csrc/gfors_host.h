@@ -52,7 +52,7 @@ constexpr int kRowRows = 2048;
 constexpr int kCfgRunDual = 6, kCfgRunPrimal = 8;   // runs of steps in one launch
 constexpr int kCfgCodes = 9;                        // steps over codes of x
 constexpr int kStepChunk = 32;         // steps per captured graph of gfors_pdhg_steps (even)
-constexpr int kStepsBeforeGraph = 2048;   // steps launched one by one before that graph is made
+constexpr int kStepsBeforeGraph = 64;    // steps launched one by one before that graph is made
 constexpr int kMfmaRows = 32;          // rows per dense digit block (one 32 x 32 matrix-core tile)
 constexpr int kMfmaMaxSpan = 1 << 23;  // column span of a block: keeps int32 plane sums exact
 
@@ -103,7 +103,18 @@ struct Carver {
 
 using namespace gfors;
 
+namespace gfh {
+// Streams for captures are kept for reuse while at least one of these exists.
+struct CaptureHold {
+    CaptureHold();
+    ~CaptureHold();
+    CaptureHold(const CaptureHold &) = delete;
+    CaptureHold &operator=(const CaptureHold &) = delete;
+};
+}  // namespace gfh
+
 struct gfors_problem {
+    gfh::CaptureHold capture_hold;
     hipStream_t stream = nullptr;
     gfors_params prm{};
     int64_t n = 0, m1 = 0, m2 = 0, m = 0, nnzK = 0, nnzQ = 0;

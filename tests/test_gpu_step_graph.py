@@ -1,5 +1,5 @@
 """Long runs of steps, which replay a captured graph once a problem has launched
-2,048 steps one by one, against the same steps launched singly: the same kernels in
+64 steps one by one, against the same steps launched singly: the same kernels in
 the same order, so every bit of the state, the counter and the residuals agrees."""
 import ctypes
 import threading
@@ -44,8 +44,8 @@ def _pair(G, kind):
 @pytest.mark.parametrize("kind", ["csr", "bitmaps", "sliced", "whole_steps", "codes", "factorised"])
 def test_replayed_runs_equal_single_steps(G, kind):
     a, b = _pair(G, kind)
-    for p in (a, b):                        # past the first 2,048 steps (in runs too short for a graph)
-        for _ in range(33):
+    for p in (a, b):                        # past the steps that are launched first (in runs too short for a graph)
+        for _ in range(2):
             p.pdhg_steps(63)
     for odd in (0, 1):                      # from both buffers
         for p in (a, b):
@@ -109,7 +109,7 @@ def test_a_given_stream_is_never_captured(G, what):
         T = G.TUReformulation(P, P.meta["tu_pivots"], factored=True)
     else:
         p = G.Problem(I.set_cover_columns(20011, 1999, 5, 1), prm, stream=stream)
-        for _ in range(33):
+        for _ in range(2):
             p.pdhg_steps(63)
         p.synchronize()
     thread = threading.Thread(target=watch)
@@ -129,3 +129,26 @@ def test_a_given_stream_is_never_captured(G, what):
     assert asked[0] > 100 and seen[0] == 0, (asked, seen)
     if what != "creation":
         p.close()
+
+
+def test_captures_on_several_threads_and_after_the_last_problem(G):
+    """Capture streams are shared by problems and threads and given back with the last problem."""
+    P = I.set_cover_columns(20011, 1999, 5, 1)
+    prm = G.default_params(k_int=10, K_max=64, power_iters=5, autotune=0)
+    for _ in range(2):
+        probs, out = [G.Problem(P, prm) for _ in range(6)], [None] * 6
+
+        def work(i):
+            for odd in range(4):
+                probs[i].pdhg_steps(64 + odd % 2)
+                probs[i].run_rounds(1, 64)
+            out[i] = probs[i].get_state()["x"]
+
+        threads = [threading.Thread(target=work, args=(i,)) for i in range(6)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        assert all(o is not None and np.array_equal(o, out[0]) for o in out)
+        for p in probs:
+            p.close()
