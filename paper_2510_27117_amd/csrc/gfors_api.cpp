@@ -1901,26 +1901,26 @@ static int autotune(gfors_problem *P, bool with_eval) {
     P->res_on = false;
     if (P->qcode_pays) codes_cfg(P);   // by rule, also where launches of k_primal were asked for before
     if (resident) {
-        // the lanes by rule, and half and twice as many per row, then per variable
-        // (every number of lanes from 1 to 64 took five times as long as all of
-        // Preprocess: 20 x 120 facility location, created in 31 ms instead of 6)
+        // the lanes by rule, and twice as many per row, then per variable.  (Every
+        // number of lanes from 1 to 64 took five times as long as all of Preprocess:
+        // 20 x 120 facility location, created in 31 ms instead of 6.  Fewer than the
+        // rule's are within 0.1 us of it where they win and add up more terms one by
+        // one: 200 x 100 set cover, 2,000 steps, 0.93e-6 -> 1.0e-6 of x off.)
         resident_cfg(P);
         const ResidentShape &sh = P->rsh;
         float *xo = P->xsave, *xp = reinterpret_cast<float *>(P->pv), *xb = reinterpret_cast<float *>(P->pu);
         float *yo = reinterpret_cast<float *>(P->pw), *yp = yo + P->m, *wy = P->ybuf[1 - P->cur];
         float best = 1e30f;
         auto consider = [&](int ld, int lp) {
-            if (ld < 1 || lp < 1 || ld > 64 || lp > 64) return;
+            if (ld > 64 || lp > 64) return;
             const float t = timeit([&] { launch_resident(P, ld, lp, 16, P->xbuf[P->cur], P->ybuf[P->cur], xo, xp, yo, yp,
                                                          xb, wy, nullptr, P->ctr_scratch); }, 2);
             if (t < best) { best = t; P->cfg.lpr_dual = ld; P->cfg.lpr_primal = lp; }
         };
         if (!sh.dense16) {
             consider(sh.lpr_d, sh.lpr_p);
-            consider(sh.lpr_d / 2, sh.lpr_p);
             if (sh.lpr_d < sh.len_r) consider(2 * sh.lpr_d, sh.lpr_p);
             const int ld = P->cfg.lpr_dual;
-            consider(ld, sh.lpr_p / 2);
             if (sh.lpr_p < sh.len_c) consider(ld, 2 * sh.lpr_p);
         }
     } else if (P->m > 0) {

@@ -178,12 +178,12 @@ def test_long_rows_keep_the_kernel_with_more_lanes(G, star, form, tuned):
                                          ("batch", (8, 2)), ("tiny", (1, 1))])
 def test_lanes_of_a_run_cover_an_instance_in_one_pass(G, name, lanes, tuned):
     """1,024 threads over the rows / variables of the largest instance: as many lanes as the mean
-    row asks for, up to one pass.  Tuning looks at half and twice as many."""
+    row asks for, up to one pass.  Tuning looks at twice as many."""
     p = G.Problem(_problems()[name], G.default_params(k_int=7, K_max=64, autotune=tuned))
     c = p.launch_cfg()
     assert _form(p) == RUN
     for got, want in zip((c["lpr_dual"], c["lpr_primal"]), lanes):
-        assert got == want if not tuned else want / 2 <= got <= 2 * want
+        assert got == want if not tuned else got in (want, 2 * want)
     p.close()
 
 
