@@ -256,6 +256,17 @@ def quad_eval_entries(bip):
     return int(np.count_nonzero(np.asarray(Q.col) >= rows))
 
 
+def quad_candidates_per_op(bip):
+    """Candidates that one lane operation of the objective's evaluation serves:
+    64 where every evaluated entry has one magnitude (they are counted
+    bitwise), else 1."""
+    Q = bip.Q
+    v = np.abs(Q.values().astype(np.int64))
+    rows = np.repeat(np.arange(Q.nrows), np.diff(Q.row_ptr))
+    v = v * np.where(rows == np.asarray(Q.col), 1, 2) if quad_eval_entries(bip) < Q.nnz else v
+    return 64 if v.size and v[0] > 0 and np.all(v == v[0]) else 1
+
+
 def general_row_nnz(bip):
     """Entries of the rows evaluated lane = candidate (not as bitwise functions
     of the candidate words: covering, at-most-one, exactly-one and rows of one
@@ -873,7 +884,9 @@ def run_workload(a):
         pass
     # the device's bare streaming-read rate (1,024 workgroups, 512 MiB), next to the published peak
     stream_ref = gfors.read_throughput(512 << 20, 1024) / 1e9
-    roofline = {"bound": "hbm", "kernel": dom, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
+    # a run of steps in one launch waits on LDS and barriers, whatever it moves
+    run_form = (lc.get("bits_dual"), lc.get("bits_primal")) == (6, 8) and dom == "primal"
+    roofline = {"bound": "latency" if run_form else "hbm", "kernel": dom, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "measured_stream_read_gbs": round(stream_ref, 1),
                 "frac_of_measured_stream_read": round(achieved / stream_ref, 4) if stream_ref > 0 else None,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
@@ -920,6 +933,10 @@ def run_workload(a):
             eval_alu = {"bound": "alu", "kernel": k, "achieved": round(ach, 1), "peak": VALU_LANE_OPS,
                         "unit": "entry-candidate products/s", "frac": round(ach / VALU_LANE_OPS, 4),
                         "products_per_launch": prods, "avg_launch_ms": kt[k][0]}
+            if k == "eval_quad" and quad_candidates_per_op(bip) > 1:
+                # counted 64 candidates at a time: a product costs a 64th of a lane operation
+                eval_alu["candidates_per_lane_op"] = quad_candidates_per_op(bip)
+                eval_alu["frac"] = round(ach / quad_candidates_per_op(bip) / VALU_LANE_OPS, 4)
     kernels = {k: {"avg_ms": round(ms, 5), "launches": cnt,
                    "gbs": (round(kb[k] / (ms * 1e-3) / 1e9, 1) if k in kb and ms > 0 else None)}
                for k, (ms, cnt) in kt.items() if cnt}

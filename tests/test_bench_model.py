@@ -104,3 +104,19 @@ def test_fused_step_bytes():
     assert "dual" not in run
     assert run["primal"] == (2 * 6 * nnz + 4 * (n + m + 2) + 7 * 4 * n + 6 * 4 * m) / 100
     assert bench.fused_step_bytes(P, {"bits_dual": 4, "bits_primal": 0}, 100, kb) == kb
+
+
+def test_quad_candidates_per_op():
+    """Max cut's entries are counted 64 candidates at a time; two magnitudes are not, and a
+    diagonal entry (counted once) has to be twice the others (each pair counted doubled)."""
+    P = I.max_cut_er(300, 6.0, seed=5)
+    assert bench.quad_candidates_per_op(P) == 64
+    val = P.Q.values().copy()
+    val[np.asarray(P.Q.col) == 0] *= 2
+    val[:P.Q.row_ptr[1]] *= 2
+    P.Q = I.CSR(P.Q.nrows, P.Q.ncols, P.Q.row_ptr, P.Q.col, val)
+    assert bench.quad_candidates_per_op(P) == 1
+    D = np.array([[2, 1, 0], [1, 0, -1], [0, -1, -2]])
+    assert bench.quad_candidates_per_op(I.from_dense([1, 1, 1], Q=D)) == 64
+    D[0, 0] = 1
+    assert bench.quad_candidates_per_op(I.from_dense([1, 1, 1], Q=D)) == 1
