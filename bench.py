@@ -122,6 +122,16 @@ def constant_degree(bip):
     return bool(cnt[0] > 0 and np.all(cnt == cnt[0]))
 
 
+def packed_q(bip):
+    """Whether the primal step reads an entry of Q as one 4-byte word: Q
+    symmetric, values of 8 bits, indices of 24."""
+    Q = bip.Q
+    if Q is None or not Q.nnz or Q.nrows > 1 << 24:
+        return False
+    v = Q.values()
+    return -128 <= v.min() and v.max() <= 127 and quad_eval_entries(bip) < Q.nnz
+
+
 def kernel_bytes(bip, K, idx=None):
     """Algorithmic HBM bytes per launch: every array the kernel must touch,
     counted once (gathered vectors by their unique size); indices only where
@@ -146,7 +156,7 @@ def kernel_bytes(bip, K, idx=None):
         # same number of rows (then the kernels compute the ranges)
         prim += (0 if constant_degree(bip) else 4 * (n + 1)) + 4 * ic + vb * nnzK + 4 * m
     if nnzQ:
-        prim += 4 * (n + 1) + 8 * nnzQ
+        prim += 4 * (n + 1) + (4 if packed_q(bip) else 8) * nnzQ
     out["primal"] = prim
     out["sample"] = 8 * n * W + 4 * n + 8 * n          # candidate words + p + cost
     if m:

@@ -120,3 +120,12 @@ def test_quad_candidates_per_op():
     assert bench.quad_candidates_per_op(I.from_dense([1, 1, 1], Q=D)) == 64
     D[0, 0] = 1
     assert bench.quad_candidates_per_op(I.from_dense([1, 1, 1], Q=D)) == 1
+
+
+def test_packed_q_bytes():
+    """Symmetric 8-bit Q: a word of index and value per entry, else index and int32 value."""
+    P = I.max_cut_er(300, 6.0, seed=5)
+    n, nnz = P.n, P.Q.nnz
+    assert bench.kernel_bytes(P, 64)["primal"] == 16 * n + 4 * (n + 1) + 4 * nnz
+    P.Q = I.CSR(n, n, P.Q.row_ptr, P.Q.col, P.Q.values() * 200)
+    assert bench.kernel_bytes(P, 64)["primal"] == 16 * n + 4 * (n + 1) + 8 * nnz
