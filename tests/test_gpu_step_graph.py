@@ -69,20 +69,24 @@ def test_replayed_runs_equal_single_steps(G, kind):
 
 
 def test_first_long_run_of_a_problem_costs_no_graph(G):
-    """100 steps took 556 us alone and 700 to 1,240 with the graph made first."""
+    """A problem's first 64 steps in one call against 32 and 32, which are launches on every host
+    (replays are faster than launches where the host is slow, so they are no measure here); after
+    60 steps in short calls, since a new stream's first launches cost more."""
     P = I.set_cover_columns(30_000, 3_000, 3, seed=0)
-    first, later = [], []
+    first, halves = [], []
     for _ in range(8):
         p = G.Problem(P, G.default_params(k_int=10, K_max=64, power_iters=5))
-        p.pdhg_steps(3)
-        p.synchronize()
-        for out in (first, later, later):
+        for _ in range(2):
+            p.pdhg_steps(30)
+            p.synchronize()
+        for out, runs in ((first, (64,)), (halves, (32, 32)), (halves, (32, 32))):
             t = time.perf_counter()
-            p.pdhg_steps(100)
+            for steps in runs:
+                p.pdhg_steps(steps)
             p.synchronize()
             out.append(time.perf_counter() - t)
         p.close()
-    assert min(first) <= 1.25 * min(later), (first, later)
+    assert min(first) <= 1.25 * min(halves), (first, halves)
 
 
 @pytest.mark.parametrize("what", ["rounds", "steps", "creation"])
